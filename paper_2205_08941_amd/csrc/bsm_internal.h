@@ -196,8 +196,6 @@ void launch_product_pair_a_f64(Context *ctx, const Plan *plan, double alpha, con
                                double beta, const bsm_pattern_s *PC, double *C, double *C2);
 // A transposed ring plan (variant 4) of G rows, cached apart from the plans get_plan_kind picks.
 Plan *get_transposed_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C, int G);
-void build_plan(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC,
-                Plan *plan, int G, int waves, int transposed = 0);
 // prec BSM_F64: the FP64 product; BSM_F32 / BSM_BF16: operands rounded to that
 // precision, FP32 accumulation, FP64 result.
 void launch_product_mixed(Context *ctx, const Plan *plan, int prec, double alpha, const bsm_pattern_s *PA,

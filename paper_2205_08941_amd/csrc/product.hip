@@ -36,7 +36,7 @@ namespace {
 constexpr int kXcd = 8;       // MI355X: 8 XCDs, workgroups dealt round-robin
 constexpr int kWaves = 4;     // wavefronts (tiles) per workgroup
 constexpr int kMaxRows = 16;  // rows of a tile, at most
-constexpr int kPlanChunks = 4;   // planner threads per tile (chunks of the k range)
+constexpr int kPlanThreads = 256;   // threads of a planner workgroup
 
 __device__ inline int64_t logical_workgroup(int64_t nwg_padded)
 {
@@ -194,245 +194,355 @@ __global__ __launch_bounds__(64) void k_product_mfma_bf16(
 }
 
 // ---------------------------------------------------------------- planner
-// One thread per row group: size of the union of the group's rows of P_C.
-__global__ void k_group_union(int n, int G, const int *__restrict__ rpC, const int *__restrict__ cC,
-                              int jt, int *__restrict__ ntile)
+// One workgroup per row group (tile headers) or per tile (entries), all over
+// windows of atoms held as bit masks in LDS.  Bound by the reads of the pattern
+// rows it merges (from L2: a group's tiles share them) and, per entry written,
+// 4 (G + JT) bytes.  A thread per group or tile that merged its rows one column
+// at a time (the former planner) spent its time in dependent loads on a nearly
+// empty chip: the 16 A x 16 A -> 16 A plan of 4096 atoms took 137 ms, one of the
+// 216-atom frames 5 ms.
+// The section compiles as plain C++ too, where a workgroup is one thread: the
+// planner's checks on the CPU run it that way.
+#if defined(__HIPCC__)
+#define BSM_PLAN_SHARED __shared__
+// a launch's workgroups in rows of gridDim.x (its threads along x must stay below 2^32)
+__device__ inline int64_t plan_item() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+__device__ inline void plan_sync() { __syncthreads(); }
+__device__ inline void plan_or(unsigned *p, unsigned v) { atomicOr(p, v); }
+__device__ inline void plan_or(unsigned long long *p, unsigned long long v) { atomicOr(p, v); }
+// exclusive sum over the workgroup's threads, and the total; every thread calls it
+__device__ inline unsigned plan_scan(unsigned v, unsigned &total)
 {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    const int ng = (n + G - 1) / G;
-    if (g >= ng) return;
-    int p[kMaxRows], pe[kMaxRows];
-    const int i0 = g * G, gr = min(G, n - i0);
-    for (int a = 0; a < gr; ++a) {
-        p[a] = rpC[i0 + a];
-        pe[a] = rpC[i0 + a + 1];
+    __shared__ unsigned part[kPlanThreads / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    unsigned x = v;
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned y = __shfl_up(x, off, 64);
+        if (lane >= off) x += y;
     }
-    int cnt = 0;
-    while (true) {
-        int m = 0x7fffffff;
-        for (int a = 0; a < gr; ++a)
-            if (p[a] < pe[a]) m = min(m, cC[p[a]]);
-        if (m == 0x7fffffff) break;
-        for (int a = 0; a < gr; ++a)
-            if (p[a] < pe[a] && cC[p[a]] == m) ++p[a];
-        ++cnt;
+    if (lane == 63) part[w] = x;
+    __syncthreads();
+    unsigned base = 0, tot = 0;
+    for (int q = 0; q < kPlanThreads / 64; ++q) {
+        if (q < w) base += part[q];
+        tot += part[q];
     }
-    ntile[g] = (cnt + jt - 1) / jt;
+    __syncthreads();
+    total = tot;
+    return base + x - v;
+}
+#else
+#define BSM_PLAN_SHARED static
+#define __launch_bounds__(n)
+constexpr int kPlanThreads = 1;
+inline int64_t plan_item() { return blockIdx.x; }
+inline void plan_sync() {}
+inline void plan_or(unsigned *p, unsigned v) { *p |= v; }
+inline void plan_or(unsigned long long *p, unsigned long long v) { *p |= v; }
+inline unsigned plan_scan(unsigned v, unsigned &total)
+{
+    total = v;
+    return 0;
+}
+#endif
+
+constexpr int kUnionWords = 4096;   // bit words of a column window (131072 atoms)
+constexpr int kEntryWindow = 1024;  // atoms k of an entry window
+
+// Columns of the group's rows of P_C (slots lo..hi) inside the window that starts
+// at k0, as bits in `bits`; the words used are cleared first.
+__device__ inline void union_bits(unsigned *bits, int words, int k0, int lo, int hi, const int *__restrict__ cC)
+{
+    const int t = threadIdx.x, nt = blockDim.x;
+    for (int w = t; w < words; w += nt) bits[w] = 0u;
+    plan_sync();
+    for (int p = lo + t; p < hi; p += nt) {
+        const int d = cC[p] - k0;
+        if (d >= 0 && d < 32 * words) plan_or(&bits[d >> 5], 1u << (d & 31));
+    }
+    plan_sync();
 }
 
-// One thread per row group: write the tile headers of its runs.  The group's
+// One workgroup per row group: tiles that the union of the group's rows of P_C takes.
+__global__ __launch_bounds__(kPlanThreads) void k_group_union(int n, int G, const int *__restrict__ rpC,
+                                                              const int *__restrict__ cC, int jt,
+                                                              int *__restrict__ ntile)
+{
+    BSM_PLAN_SHARED unsigned bits[kUnionWords];
+    const int g = blockIdx.x;
+    const int i0 = g * G, gr = min(G, n - i0);
+    const int lo = rpC[i0], hi = rpC[i0 + gr];   // the group's rows follow each other
+    unsigned cnt = 0;
+    for (int k0 = 0; k0 < n; k0 += 32 * kUnionWords) {
+        const int words = min(kUnionWords, (n - k0 + 31) / 32);
+        union_bits(bits, words, k0, lo, hi, cC);
+        for (int w = threadIdx.x; w < words; w += blockDim.x) cnt += __popc(bits[w]);
+        plan_sync();
+    }
+    unsigned total;
+    plan_scan(cnt, total);
+    if (threadIdx.x == 0) ntile[g] = ((int)total + jt - 1) / jt;
+}
+
+// One workgroup per row group: write the tile headers of its runs.  The group's
 // union of P_C columns is cut into runs of jt columns, in ascending column order
 // (order 0) or grouped by the set of the group's rows whose P_C row holds the
 // column (order 1: row sets in descending bit order, ascending columns inside a
 // set).  With order 1 a tile's columns share their output rows, so a row
 // multiplies in a tile only where it has outputs; the two orders give the same
-// products.  scr (order 1 only): per plan 5 + G arrays of ntiles * jt ints, each
-// group using its tiles' range: union columns, row sets and union positions in
-// ping-pong pairs, and the C slots of every (column, row) found by the merge.
-__global__ void k_group_tiles(int n, int G, int jt, int order, const int *__restrict__ rpC,
-                              const int *__restrict__ cC, const int64_t *__restrict__ toff, int64_t ntiles,
-                              int *__restrict__ hdr, int *__restrict__ tcols, int *__restrict__ scr)
+// products.  scr: per plan 5 + G arrays of ntiles * jt ints, each group using its
+// tiles' range: union columns, row sets and union positions in ping-pong pairs,
+// and the C slots of every (column, row).  Order 1 sorts the union positions by a
+// stable radix sort on 4 row-set bits at a time, each thread counting and placing
+// a run of consecutive positions.
+__global__ __launch_bounds__(kPlanThreads) void k_group_tiles(int n, int G, int jt, int order,
+                                                              const int *__restrict__ rpC,
+                                                              const int *__restrict__ cC,
+                                                              const int64_t *__restrict__ toff, int64_t ntiles,
+                                                              int *__restrict__ hdr, int *__restrict__ tcols,
+                                                              int *__restrict__ scr)
 {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    const int ng = (n + G - 1) / G;
-    if (g >= ng) return;
+    BSM_PLAN_SHARED unsigned bits[kUnionWords], first[kUnionWords];
+    BSM_PLAN_SHARED unsigned hist[16 * kPlanThreads];
+    const int g = blockIdx.x, t = threadIdx.x, nt = blockDim.x;
     const int hs = G + G * jt;
-    int p[kMaxRows], pe[kMaxRows];
     const int i0 = g * G, gr = min(G, n - i0);
-    for (int a = 0; a < gr; ++a) {
-        p[a] = rpC[i0 + a];
-        pe[a] = rpC[i0 + a + 1];
-    }
-    const int64_t t0 = toff[g], cap = ntiles * jt;
-    auto open_tile = [&](int64_t t) {
-        int *h = hdr + t * hs;
-        for (int a = 0; a < G; ++a) h[a] = (a < gr) ? i0 + a : -1;
-        for (int x = 0; x < G * jt; ++x) h[G + x] = -1;
-        for (int x = 0; x < jt; ++x) tcols[t * jt + x] = -1;
-    };
-    if (order == 0) {
-        int64_t t = t0;
-        int q = 0;
-        while (true) {
-            int m = 0x7fffffff;
-            for (int a = 0; a < gr; ++a)
-                if (p[a] < pe[a]) m = min(m, cC[p[a]]);
-            if (m == 0x7fffffff) break;
-            if (q == 0) open_tile(t);
-            int *h = hdr + t * hs;
-            tcols[t * jt + q] = m;
-            for (int a = 0; a < gr; ++a)
-                if (p[a] < pe[a] && cC[p[a]] == m) {
-                    h[G + a * jt + q] = p[a];
-                    ++p[a];
-                }
-            if (++q == jt) {
-                q = 0;
-                ++t;
-            }
-        }
-        return;
-    }
-    // order 1: union with row sets and slots, then a stable radix sort of the
-    // union positions on the row-set bits (least significant first, rows present
-    // before rows absent at each bit)
-    const int64_t o = t0 * jt;
+    const int lo = rpC[i0], hi = rpC[i0 + gr];
+    const int64_t t0 = toff[g], cap = ntiles * jt, o = t0 * jt;
+    const int room = (int)(toff[g + 1] - t0) * jt;   // columns of the group's tiles
     int *col = scr + o, *m0 = scr + cap + o, *m1 = scr + 2 * cap + o, *x0 = scr + 3 * cap + o,
         *x1 = scr + 4 * cap + o, *sl = scr + 5 * cap + o * G;
-    int cnt = 0;
-    while (true) {
-        int m = 0x7fffffff;
-        for (int a = 0; a < gr; ++a)
-            if (p[a] < pe[a]) m = min(m, cC[p[a]]);
-        if (m == 0x7fffffff) break;
-        int set = 0;
-        for (int a = 0; a < G; ++a) {
-            int slot = -1;
-            if (a < gr && p[a] < pe[a] && cC[p[a]] == m) {
-                set |= 1 << a;
-                slot = p[a]++;
-            }
-            sl[(int64_t)cnt * G + a] = slot;
+    for (int64_t e = t; e < (int64_t)room * G; e += nt) sl[e] = -1;
+    // the union's columns in ascending order, and every (column, row)'s C slot
+    unsigned cnt = 0;
+    for (int k0 = 0; k0 < n; k0 += 32 * kUnionWords) {
+        const int words = min(kUnionWords, (n - k0 + 31) / 32);
+        union_bits(bits, words, k0, lo, hi, cC);
+        const int per = (words + nt - 1) / nt, w0 = min(words, t * per), w1 = min(words, w0 + per);
+        unsigned mine = 0, total;
+        for (int w = w0; w < w1; ++w) mine += __popc(bits[w]);
+        unsigned run = cnt + plan_scan(mine, total);
+        for (int w = w0; w < w1; ++w) {
+            first[w] = run;
+            run += __popc(bits[w]);
         }
-        col[cnt] = m;
-        m0[cnt] = set;
-        x0[cnt] = cnt;
-        ++cnt;
+        plan_sync();
+        for (int p = lo + t; p < hi; p += nt) {
+            const int k = cC[p], d = k - k0;
+            if (d < 0 || d >= 32 * words) continue;
+            int a = 0;
+            while (p >= rpC[i0 + a + 1]) ++a;
+            const int u = (int)(first[d >> 5] + __popc(bits[d >> 5] & ((1u << (d & 31)) - 1u)));
+            col[u] = k;
+            sl[(int64_t)u * G + a] = p;
+        }
+        cnt += total;
+        plan_sync();
     }
-    for (int bit = 0; bit < gr; ++bit) {
-        int w = 0;
-        for (int x = 0; x < cnt; ++x)
-            if ((m0[x] >> bit) & 1) {
-                m1[w] = m0[x];
-                x1[w++] = x0[x];
+    const int nu = (int)cnt;
+    if (order == 1) {
+        for (int u = t; u < nu; u += nt) {
+            int set = 0;
+            for (int a = 0; a < gr; ++a) set |= (sl[(int64_t)u * G + a] >= 0 ? 1 : 0) << a;
+            m0[u] = set;
+            x0[u] = u;
+        }
+        plan_sync();
+        const int seg = (nu + nt - 1) / nt, s0 = min(nu, t * seg), s1 = min(nu, s0 + seg);
+        for (int bit = 0; bit < gr; bit += 4) {
+            for (int v = 0; v < 16; ++v) hist[v * nt + t] = 0u;
+            for (int x = s0; x < s1; ++x) hist[(15 - ((m0[x] >> bit) & 15)) * nt + t] += 1u;
+            plan_sync();
+            // positions: digit by digit (present rows first), thread by thread
+            unsigned mine = 0, total;
+            for (int v = 0; v < 16; ++v) mine += hist[16 * t + v];
+            unsigned run = plan_scan(mine, total);
+            for (int v = 0; v < 16; ++v) {
+                const unsigned h = hist[16 * t + v];
+                hist[16 * t + v] = run;
+                run += h;
             }
-        for (int x = 0; x < cnt; ++x)
-            if (!((m0[x] >> bit) & 1)) {
-                m1[w] = m0[x];
-                x1[w++] = x0[x];
+            plan_sync();
+            for (int x = s0; x < s1; ++x) {
+                const int m = m0[x];
+                const unsigned w = hist[(15 - ((m >> bit) & 15)) * nt + t]++;
+                m1[w] = m;
+                x1[w] = x0[x];
             }
-        int *tm = m0, *tx = x0;
-        m0 = m1;
-        x0 = x1;
-        m1 = tm;
-        x1 = tx;
+            plan_sync();
+            int *tm = m0, *tx = x0;
+            m0 = m1;
+            x0 = x1;
+            m1 = tm;
+            x1 = tx;
+        }
     }
-    for (int x = 0; x < cnt; ++x) {
-        const int64_t t = t0 + x / jt;
+    for (int x = t; x < room; x += nt) {
+        const int64_t tile = t0 + x / jt;
         const int q = x % jt;
-        if (q == 0) open_tile(t);
-        int *h = hdr + t * hs;
-        const int u = x0[x];
-        tcols[t * jt + q] = col[u];
-        for (int a = 0; a < gr; ++a) h[G + a * jt + q] = sl[(int64_t)u * G + a];
+        int *h = hdr + tile * hs;
+        if (q == 0)
+            for (int a = 0; a < G; ++a) h[a] = (a < gr) ? i0 + a : -1;
+        const int u = x < nu ? (order == 1 ? x0[x] : x) : -1;
+        tcols[tile * jt + q] = u >= 0 ? col[u] : -1;
+        for (int a = 0; a < G; ++a) h[G + a * jt + q] = u >= 0 ? sl[(int64_t)u * G + a] : -1;
     }
 }
 
-// One thread per (tile, chunk of k): walk the union over the tile's rows of P_A
-// (k ascending) for k in [c n / nch, (c + 1) n / nch); keep k when some
-// (i_a, k, j) triple exists.  MODE 0 counts entries and triples per (tile,
-// chunk), MODE 1 writes the entries; a tile's chunks follow each other, so its
-// entries stay in ascending k.  The tile's last chunk writes the padding entry
-// that makes the tile's count even (its count includes it, k_pad_counts).  W = 2 (tiles shared by two waves): each entry is two
-// halves, one per wave and its jt / 2 columns, each with the A slots of the rows
-// that have a live triple in those columns and then those columns' B slots.
+// One workgroup per (tile, chunk of k in [c n / nch, (c + 1) n / nch)): the k for
+// which some (i_a, k, j) triple exists, in ascending order.  MODE 0 counts
+// entries and triples per (tile, chunk), MODE 1 writes the entries; a tile's
+// chunks follow each other, so its entries stay in ascending k.  The tile's last
+// chunk writes the padding entry that makes the tile's count even (its count
+// includes it, k_pad_counts).  Each window of kEntryWindow atoms is held as two
+// masks per k, the rows a with (i_a, k) in P_A and the columns x with (k, j_x) in
+// P_B, filled from the tile's G + jt pattern rows, 64 threads to a row.  An A row
+// (B column) of an entry with no live triple would only meet zero blocks or
+// outputs outside P_C: it is dropped, so that the kernels neither copy nor
+// multiply it.  W = 2 (tiles shared by two waves): each entry is two halves, one
+// per wave and its jt / 2 columns, each with the A slots of the rows that have a
+// live triple in those columns and then those columns' B slots.
 template <int MODE>
-__global__ void k_tile_entries(int64_t ntiles, int nch, int natoms, int G, int jt, int W, int tr,
-                               const int *__restrict__ hdr,
-                               const int *__restrict__ tcols, const int *__restrict__ rpA,
-                               const int *__restrict__ cA, const int *__restrict__ tmA,
-                               const int *__restrict__ rpB, const int *__restrict__ cB,
-                               const int *__restrict__ tmB, int64_t *__restrict__ nent,
-                               unsigned long long *__restrict__ triples, unsigned long long *__restrict__ rowwork,
-                               const int64_t *__restrict__ ebeg, int *__restrict__ ent)
+__global__ __launch_bounds__(kPlanThreads) void k_tile_entries(
+    int64_t ntiles, int nch, int natoms, int G, int jt, int W, int tr, const int *__restrict__ hdr,
+    const int *__restrict__ tcols, const int *__restrict__ rpA, const int *__restrict__ cA,
+    const int *__restrict__ tmA, const int *__restrict__ rpB, const int *__restrict__ cB,
+    const int *__restrict__ tmB, int64_t *__restrict__ nent, unsigned long long *__restrict__ triples,
+    unsigned long long *__restrict__ rowwork, const int64_t *__restrict__ ebeg, int *__restrict__ ent)
 {
-    const int64_t tc = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int kRows = kMaxRows + 64;
+    BSM_PLAN_SHARED unsigned am[kEntryWindow];             // rows present; then rows live (per half)
+    BSM_PLAN_SHARED unsigned long long bm[kEntryWindow];   // columns present; then columns live
+    BSM_PLAN_SHARED int eidx[MODE == 1 ? kEntryWindow : 1];
+    BSM_PLAN_SHARED int beg[kRows], end[kRows], nxt[kRows];
+    BSM_PLAN_SHARED unsigned long long cmask[kMaxRows];    // columns with an output in row a
+    const int64_t tc = plan_item();
     if (tc >= ntiles * nch) return;
     const int64_t t = tc / nch;
     const int c = (int)(tc - t * nch);
     const int k0 = (int)((int64_t)c * natoms / nch), k1 = (int)((int64_t)(c + 1) * natoms / nch);
-    const int hs = G + G * jt, es = W * G + jt, jh = jt / W;
+    const int hs = G + G * jt, es = W * G + jt, jh = jt / W, nr = G + jt;
     const int *h = hdr + t * hs;
-    int pa[kMaxRows], pae[kMaxRows], pb[64], pbe[64], jcol[64];
-    // first position in cols[lo, hi) at or past value v
-    auto lower = [](const int *__restrict__ cols, int lo, int hi, int v) {
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (cols[mid] < v) lo = mid + 1;
-            else hi = mid;
-        }
-        return lo;
-    };
-    for (int a = 0; a < G; ++a) {
-        const int i = h[a];
-        pa[a] = (i >= 0) ? lower(cA, rpA[i], rpA[i + 1], k0) : 0;
-        pae[a] = (i >= 0) ? lower(cA, pa[a], rpA[i + 1], k1) : 0;
-    }
-    for (int x = 0; x < jt; ++x) {
-        const int j = tcols[t * jt + x];
-        jcol[x] = j;
-        pb[x] = (j >= 0) ? lower(cB, rpB[j], rpB[j + 1], k0) : 0;
-        pbe[x] = (j >= 0) ? lower(cB, pb[x], rpB[j + 1], k1) : 0;
-    }
-    int64_t w = (MODE == 1) ? ebeg[tc] : 0;
-    int64_t cnt = 0;
-    unsigned long long tri = 0, rw = 0;
-    while (true) {
-        int k = 0x7fffffff;
-        for (int a = 0; a < G; ++a)
-            if (pa[a] < pae[a]) k = min(k, cA[pa[a]]);
-        if (k == 0x7fffffff) break;
-        int aslot[kMaxRows];
-        for (int a = 0; a < G; ++a) {
-            aslot[a] = -1;
-            if (pa[a] < pae[a] && cA[pa[a]] == k) aslot[a] = tr ? tmA[pa[a]++] : pa[a]++;   // tr: slot of (k, i)
-        }
-        int bslot[64];
-        int ntri = 0;
-        for (int x = 0; x < jt; ++x) {
-            bslot[x] = -1;
-            if (jcol[x] < 0) continue;
-            while (pb[x] < pbe[x] && cB[pb[x]] < k) ++pb[x];
-            if (pb[x] < pbe[x] && cB[pb[x]] == k) bslot[x] = tr ? pb[x] : tmB[pb[x]];   // (k, j); tr: (j, k)
-            if (bslot[x] < 0) continue;
-            for (int a = 0; a < G; ++a) ntri += (aslot[a] >= 0 && h[G + a * jt + x] >= 0) ? 1 : 0;
-        }
-        if (ntri == 0) continue;
-        // A row (B column) blocks with no live triple in this entry would only
-        // meet zero blocks or outputs outside P_C: drop them, so that the kernels
-        // neither copy nor multiply them
-        unsigned rowlive[2] = {0u, 0u};
-        unsigned long long collive = 0;
-        for (int x = 0; x < jt; ++x) {
-            if (bslot[x] < 0) continue;
-            for (int a = 0; a < G; ++a)
-                if (aslot[a] >= 0 && h[G + a * jt + x] >= 0) {
-                    rowlive[x / jh] |= 1u << a;
-                    collive |= 1ull << x;
-                }
-        }
-        for (int x = 0; x < jt; ++x)
-            if (!((collive >> x) & 1ull)) bslot[x] = -1;
-        if (MODE == 1) {
-            int *e = ent + w * es;
-            for (int hf = 0; hf < W; ++hf, e += G + jh) {
-                for (int a = 0; a < G; ++a) e[a] = ((rowlive[hf] >> a) & 1u) ? aslot[a] : -1;
-                for (int x = 0; x < jh; ++x) e[G + x] = bslot[hf * jh + x];
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int sub = nt >= 64 ? 64 : nt, lane = tid % sub, grp = tid / sub, ngrp = nt / sub;
+    for (int r = tid; r < nr; r += nt) {
+        const int i = r < G ? h[r] : tcols[t * jt + (r - G)];
+        const int *cols = r < G ? cA : cB, *rp = r < G ? rpA : rpB;
+        int lo = i >= 0 ? rp[i] : 0;
+        const int e = i >= 0 ? rp[i + 1] : 0;
+        if (k0 > 0) {   // first position at or past k0
+            int hi = e;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (cols[mid] < k0) lo = mid + 1;
+                else hi = mid;
             }
         }
-        ++w;
-        ++cnt;
-        tri += ntri;
-        for (int hf = 0; hf < W; ++hf) rw += __popc(rowlive[hf]);   // rows multiplied
+        beg[r] = lo;
+        end[r] = e;
     }
-    if (MODE == 1 && c == nch - 1 && w < ebeg[tc + 1]) {   // the padding entry: multiplies nothing
-        int *e = ent + w * es;
-        for (int x = 0; x < es; ++x) e[x] = -1;
+    for (int a = tid; a < G; a += nt) {
+        unsigned long long m = 0;
+        for (int x = 0; x < jt; ++x)
+            if (h[G + a * jt + x] >= 0) m |= 1ull << x;
+        cmask[a] = m;
     }
-    if (MODE == 0) {
-        nent[tc] = cnt;
-        atomicAdd(triples, tri);   // integers: order-independent
-        atomicAdd(rowwork, rw);
+    plan_sync();
+    const unsigned long long half0 = W == 1 ? ~0ull : (1ull << jh) - 1ull;
+    int64_t w = (MODE == 1) ? ebeg[tc] : 0;
+    unsigned cnt = 0, tri = 0, rw = 0;
+    for (int kw = k0; kw < k1; kw += kEntryWindow) {
+        const int ke = min(k1, kw + kEntryWindow), len = ke - kw;
+        for (int d = tid; d < len; d += nt) {
+            am[d] = 0u;
+            bm[d] = 0ull;
+        }
+        plan_sync();
+        for (int r = grp; r < nr; r += ngrp) {
+            const int *cols = r < G ? cA : cB;
+            const int b0 = beg[r], b1 = end[r];
+            for (int p = b0 + lane; p <= b1; p += sub) {
+                const int k = p < b1 ? cols[p] : 0x7fffffff;
+                if (k >= ke) {   // the first position past the window starts the next one
+                    if (p == b0 || cols[p - 1] < ke) nxt[r] = p;
+                    break;
+                }
+                if (r < G) plan_or(&am[k - kw], 1u << r);
+                else plan_or(&bm[k - kw], 1ull << (r - G));
+            }
+        }
+        plan_sync();
+        // each thread takes a run of consecutive k
+        const int per = (len + nt - 1) / nt, d0 = min(len, tid * per), d1 = min(len, d0 + per);
+        unsigned mine = 0;
+        for (int d = d0; d < d1; ++d) {
+            const unsigned ra = am[d];
+            const unsigned long long cb = bm[d];
+            unsigned live = 0;   // rows live in the first half, from bit 16 in the second
+            unsigned long long cl = 0;
+            if (ra != 0u && cb != 0ull)
+                for (int a = 0; a < G; ++a) {
+                    if (!((ra >> a) & 1u)) continue;
+                    const unsigned long long m = cmask[a] & cb;
+                    if (m == 0ull) continue;
+                    cl |= m;
+                    if (m & half0) live |= 1u << a;
+                    if (m & ~half0) live |= 0x10000u << a;
+                    if (MODE == 0) tri += (unsigned)(__popc((unsigned)m) + __popc((unsigned)(m >> 32)));
+                }
+            mine += cl != 0ull ? 1u : 0u;
+            if (MODE == 0) rw += (unsigned)__popc(live);   // rows multiplied
+            if (MODE == 1) {
+                am[d] = live;
+                bm[d] = cl;
+            }
+        }
+        if (MODE == 0) {
+            cnt += mine;
+        } else {
+            unsigned total;
+            unsigned e = plan_scan(mine, total);
+            for (int d = d0; d < d1; ++d) eidx[d] = bm[d] != 0ull ? (int)e++ : -1;
+            int *ew = ent + w * es;
+            for (int64_t x = tid; x < (int64_t)total * es; x += nt) ew[x] = -1;
+            plan_sync();
+            for (int r = grp; r < nr; r += ngrp) {
+                const int *cols = r < G ? cA : cB, *tm = r < G ? tmA : tmB;
+                const int b0 = beg[r], b1 = nxt[r];
+                for (int p = b0 + lane; p < b1; p += sub) {
+                    const int d = cols[p] - kw, q = eidx[d];
+                    if (q < 0) continue;
+                    int *eq = ew + (int64_t)q * es;
+                    if (r < G) {
+                        const unsigned live = am[d] >> r;
+                        const int s = tr ? tm[p] : p;   // slot of (i, k); tr: of (k, i)
+                        if (live & 1u) eq[r] = s;
+                        if (live & 0x10000u) eq[G + jh + r] = s;
+                    } else {
+                        const int x = r - G, hf = x / jh;
+                        if ((bm[d] >> x) & 1ull) eq[hf * (G + jh) + G + x - hf * jh] = tr ? p : tm[p];   // (k, j); tr: (j, k)
+                    }
+                }
+            }
+            w += total;
+        }
+        plan_sync();
+        for (int r = tid; r < nr; r += nt) beg[r] = nxt[r];
+        plan_sync();
+    }
+    if (MODE == 1) {
+        if (c == nch - 1 && w < ebeg[tc + 1])   // the padding entry: multiplies nothing
+            for (int x = tid; x < es; x += nt) ent[w * es + x] = -1;
+    } else {
+        unsigned scnt, stri, srw;
+        plan_scan(cnt, scnt);
+        plan_scan(tri, stri);
+        plan_scan(rw, srw);
+        if (tid == 0) {
+            nent[tc] = scnt;
+            atomicAdd(triples, (unsigned long long)stri);   // integers: order-independent
+            atomicAdd(rowwork, (unsigned long long)srw);
+        }
     }
 }
 
@@ -667,118 +777,140 @@ void launch_b32(hipStream_t st, const Plan *plan, const float *A, const float *B
 int default_rows_per_wave(int b) { return b >= 5 ? 4 : (b == 4 ? 4 : 2); }
 int default_variant(int b) { return (b == 9 || b == 4) ? 4 : 0; }
 
-void build_plan(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC,
-                Plan *plan, int G, int waves, int transposed)
+namespace {
+// What the two stages of building a plan share: the tiles of P_C (the same for the
+// direct and the transposed plan of a product) and the entry ranges of a counted plan.
+struct TileSet {
+    int G = 0, waves = 1, jt = 0, ng = 0;
+    int64_t nt = 0;
+    DevBuf ntile, ntile64, toff, hdr, tcols, scr;
+};
+// Workgroups of a launch over the tiles
+dim3 tile_grid(int64_t nt)
 {
-    // transposed: plan D = B^T A^T on P_C (C = D^T); the kernel's A operand is B
-    // (rows over P_B, which is symmetric), its B operand is A
-    BSM_REQUIRE(!transposed || waves == 1, BSM_EINVAL, "transposed plans use one-wave tiles");
-    if (transposed) std::swap(PA, PB);
+    const int64_t x = std::min<int64_t>(nt, 1 << 22);
+    return dim3((unsigned)x, (unsigned)((nt + x - 1) / x));
+}
+struct EntryCount {
+    DevBuf nent, totals, ebeg;
+    int64_t ne = 0;
+    unsigned long long ntri[2] = {0, 0};   // triples, rows multiplied
+};
+
+// Launch order: within each span of `span` consecutive row groups, chunk position
+// first, so that the groups' tiles over similar columns run together and share B
+// blocks in L2.  One workgroup per row group, one thread per tile of it.
+__global__ void k_tile_order(int ng, int span, const int *__restrict__ ntile, const int64_t *__restrict__ toff,
+                             int *__restrict__ order)
+{
+    const int g = blockIdx.x, g0 = g - g % span, g1 = min(ng, g0 + span);
+    for (int q = threadIdx.x; q < ntile[g]; q += blockDim.x) {
+        int64_t pos = toff[g0];
+        for (int o = g0; o < g1; ++o) pos += min(ntile[o], q) + ((o < g && ntile[o] > q) ? 1 : 0);
+        order[pos] = (int)(toff[g] + q);
+    }
+}
+
+void make_tiles(Context *ctx, const bsm_pattern_s *PC, int G, int waves, TileSet &ts)
+{
     hipStream_t st = ctx->stream;
     const int n = PC->natoms, jt = waves * (64 / PC->b);
     BSM_REQUIRE(G == 2 || G == 4 || G == 8 || G == kMaxRows, BSM_EINVAL, "rows per tile must be 2, 4, 8 or 16");
     BSM_REQUIRE(waves == 1 || (waves == 2 && G <= 8), BSM_EINVAL, "two waves per tile take at most 8 rows");
-    plan->G = G;
-    plan->waves = waves;
-    plan->jt = jt;
     const int ng = (n + G - 1) / G;
-    const int hs = G + G * jt, es = waves * G + jt;
-    DevBuf ntile(ctx, sizeof(int) * ng), ntile64(ctx, sizeof(int64_t) * ng), toff(ctx, sizeof(int64_t) * (ng + 1));
-    k_group_union<<<(ng + 127) / 128, 128, 0, st>>>(n, G, PC->rowptr.as<int>(), PC->cols.as<int>(), jt,
-                                                    ntile.as<int>());
-    k_int_to_i64<<<(ng + 255) / 256, 256, 0, st>>>(ng, ntile.as<int>(), ntile64.as<int64_t>());
-    k_scan64<<<1, 1024, 0, st>>>(ng, ntile64.as<int64_t>(), toff.as<int64_t>());
-    int64_t nt = 0;
-    BSM_HIP_TRY(hipMemcpyAsync(&nt, toff.as<int64_t>() + ng, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    ts.G = G;
+    ts.waves = waves;
+    ts.jt = jt;
+    ts.ng = ng;
+    ts.ntile = DevBuf(ctx, sizeof(int) * ng);
+    ts.ntile64 = DevBuf(ctx, sizeof(int64_t) * ng);
+    ts.toff = DevBuf(ctx, sizeof(int64_t) * (ng + 1));
+    k_group_union<<<ng, kPlanThreads, 0, st>>>(n, G, PC->rowptr.as<int>(), PC->cols.as<int>(), jt, ts.ntile.as<int>());
+    k_int_to_i64<<<(ng + 255) / 256, 256, 0, st>>>(ng, ts.ntile.as<int>(), ts.ntile64.as<int64_t>());
+    k_scan64<<<1, 1024, 0, st>>>(ng, ts.ntile64.as<int64_t>(), ts.toff.as<int64_t>());
+    BSM_HIP_TRY(hipMemcpyAsync(&ts.nt, ts.toff.as<int64_t>() + ng, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     BSM_HIP_TRY(hipStreamSynchronize(st));
-    plan->ntiles = nt;
+    const int64_t nt = ts.nt;
     BSM_REQUIRE(nt < (int64_t)INT32_MAX, BSM_EINVAL, "too many product tiles");
-    {
-        // launch order: within each span of `span` consecutive row groups, chunk
-        // position first, so that the groups' tiles over similar columns run
-        // together and share B blocks in L2
-        std::vector<int> cnt(ng);
-        std::vector<int64_t> off(ng + 1);
-        BSM_HIP_TRY(hipMemcpyAsync(cnt.data(), ntile.ptr, sizeof(int) * ng, hipMemcpyDeviceToHost, st));
-        BSM_HIP_TRY(hipMemcpyAsync(off.data(), toff.ptr, sizeof(int64_t) * (ng + 1), hipMemcpyDeviceToHost, st));
-        BSM_HIP_TRY(hipStreamSynchronize(st));
-        std::vector<int> order;
-        order.reserve((size_t)nt);
-        const int span = std::max(1, ctx->group_span);
-        for (int g0 = 0; g0 < ng; g0 += span) {
-            const int g1 = std::min(ng, g0 + span);
-            int qmax = 0;
-            for (int g = g0; g < g1; ++g) qmax = std::max(qmax, cnt[g]);
-            for (int q = 0; q < qmax; ++q)
-                for (int g = g0; g < g1; ++g)
-                    if (q < cnt[g]) order.push_back((int)(off[g] + q));
-        }
-        plan->order = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt));
-        if (nt > 0)
-            BSM_HIP_TRY(hipMemcpyAsync(plan->order.ptr, order.data(), sizeof(int) * (size_t)nt, hipMemcpyHostToDevice, st));
-        BSM_HIP_TRY(hipStreamSynchronize(st));
-        plan->span = span;
-    }
-    plan->hdr = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt * hs));
-    DevBuf tcols(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt * jt));
-    {
-        const int order = ctx->column_order;
-        const size_t scrn = order == 1 ? (size_t)std::max<int64_t>(1, (5 + G) * nt * jt) : 1;
-        DevBuf scr(ctx, sizeof(int) * scrn);
-        k_group_tiles<<<(ng + 127) / 128, 128, 0, st>>>(n, G, jt, order, PC->rowptr.as<int>(), PC->cols.as<int>(),
-                                                        toff.as<int64_t>(), nt, plan->hdr.as<int>(),
-                                                        tcols.as<int>(), scr.as<int>());
-        BSM_HIP_TRY(hipStreamSynchronize(st));   // before the sort buffers are freed
-    }
-    // entries are planned per (tile, chunk of k) for parallelism; kPlanChunks chunks per tile
-    const int nch = kPlanChunks;
-    const int64_t ntc = nt * nch;
-    DevBuf nent(ctx, sizeof(int64_t) * (size_t)std::max<int64_t>(1, ntc)), tri(ctx, 2 * sizeof(unsigned long long));
-    DevBuf ebeg_tc(ctx, sizeof(int64_t) * (size_t)(ntc + 1));
-    plan->ebeg = DevBuf(ctx, sizeof(int64_t) * (size_t)(nt + 1));
-    BSM_HIP_TRY(hipMemsetAsync(tri.ptr, 0, 2 * sizeof(unsigned long long), st));
-    BSM_HIP_TRY(hipMemsetAsync(plan->ebeg.ptr, 0, sizeof(int64_t) * (size_t)(nt + 1), st));
-    int64_t ne = 0;
-    unsigned long long ntri[2] = {0, 0};   // triples, rows multiplied
-    if (nt > 0) {
-        const unsigned grid = (unsigned)((ntc + 127) / 128);
-        k_tile_entries<0><<<grid, 128, 0, st>>>(nt, nch, PA->natoms, G, jt, waves, transposed, plan->hdr.as<int>(),
-                                                tcols.as<int>(), PA->rowptr.as<int>(), PA->cols.as<int>(),
-                                                PA->tmap.as<int>(), PB->rowptr.as<int>(), PB->cols.as<int>(),
-                                                PB->tmap.as<int>(), nent.as<int64_t>(),
-                                                tri.as<unsigned long long>(), tri.as<unsigned long long>() + 1,
-                                                nullptr, nullptr);
-        k_pad_counts<<<(unsigned)((nt + 127) / 128), 128, 0, st>>>(nt, nch, nent.as<int64_t>());
-        k_scan64<<<1, 1024, 0, st>>>(ntc, nent.as<int64_t>(), ebeg_tc.as<int64_t>());
-        k_tile_ebeg<<<(unsigned)((nt + 1 + 127) / 128), 128, 0, st>>>(nt, nch, ebeg_tc.as<int64_t>(),
-                                                                      plan->ebeg.as<int64_t>());
-        BSM_HIP_TRY(hipMemcpyAsync(&ne, ebeg_tc.as<int64_t>() + ntc, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        BSM_HIP_TRY(hipMemcpyAsync(ntri, tri.ptr, sizeof(ntri), hipMemcpyDeviceToHost, st));
-        BSM_HIP_TRY(hipStreamSynchronize(st));
-        plan->ent = DevBuf(ctx, sizeof(int) * (size_t)((ne + 4) * es));   // 4 spare entries
-        BSM_HIP_TRY(hipMemsetAsync(plan->ent.as<int>() + ne * es, 0xff, sizeof(int) * 4 * es, st));
-        k_tile_entries<1><<<grid, 128, 0, st>>>(nt, nch, PA->natoms, G, jt, waves, transposed, plan->hdr.as<int>(),
-                                                tcols.as<int>(), PA->rowptr.as<int>(), PA->cols.as<int>(),
-                                                PA->tmap.as<int>(), PB->rowptr.as<int>(), PB->cols.as<int>(),
-                                                PB->tmap.as<int>(), nullptr, nullptr, nullptr,
-                                                ebeg_tc.as<int64_t>(), plan->ent.as<int>());
-        BSM_HIP_TRY(hipGetLastError());
-    } else {
-        plan->ent = DevBuf(ctx, sizeof(int) * 4 * es);
-        BSM_HIP_TRY(hipMemsetAsync(plan->ent.ptr, 0xff, sizeof(int) * 4 * es, st));
-    }
-    BSM_HIP_TRY(hipStreamSynchronize(st));
-    plan->nentries = ne;
-    plan->triples = (int64_t)ntri[0];
-    plan->rowwork = (int64_t)ntri[1];
-    plan->flops = 2.0 * (double)PC->b * PC->b * PC->b * (double)ntri[0];
-    plan->transposed = transposed;
-    if (transposed && nt > 0) {   // outputs go to the slot of (j, i)
-        k_map_cslots<<<(unsigned)((nt + 127) / 128), 128, 0, st>>>(nt, G, jt, PC->tmap.as<int>(), plan->hdr.as<int>());
-        BSM_HIP_TRY(hipGetLastError());
-        BSM_HIP_TRY(hipStreamSynchronize(st));
-    }
+    ts.hdr = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt * (G + G * jt)));
+    ts.tcols = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt * jt));
+    ts.scr = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, (5 + G) * nt * jt));
+    k_group_tiles<<<ng, kPlanThreads, 0, st>>>(n, G, jt, ctx->column_order, PC->rowptr.as<int>(), PC->cols.as<int>(),
+                                               ts.toff.as<int64_t>(), nt, ts.hdr.as<int>(), ts.tcols.as<int>(),
+                                               ts.scr.as<int>());
+    BSM_HIP_TRY(hipGetLastError());
 }
+
+// The entry ranges of the plan over `ts`, its flops and its estimated work.
+// transposed: plan D = B^T A^T on P_C (C = D^T); the kernel's A operand is B (rows
+// over P_B, which is symmetric), its B operand is A.
+void count_entries(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC,
+                   const TileSet &ts, int transposed, Plan *plan, EntryCount &ec)
+{
+    BSM_REQUIRE(!transposed || ts.waves == 1, BSM_EINVAL, "transposed plans use one-wave tiles");
+    if (transposed) std::swap(PA, PB);
+    hipStream_t st = ctx->stream;
+    const int64_t nt = ts.nt;
+    plan->G = ts.G;
+    plan->waves = ts.waves;
+    plan->jt = ts.jt;
+    plan->ntiles = nt;
+    plan->transposed = transposed;
+    plan->ebeg = DevBuf(ctx, sizeof(int64_t) * (size_t)(nt + 1));
+    BSM_HIP_TRY(hipMemsetAsync(plan->ebeg.ptr, 0, sizeof(int64_t) * (size_t)(nt + 1), st));
+    if (nt > 0) {
+        ec.nent = DevBuf(ctx, sizeof(int64_t) * (size_t)nt);
+        ec.totals = DevBuf(ctx, 2 * sizeof(unsigned long long));
+        ec.ebeg = DevBuf(ctx, sizeof(int64_t) * (size_t)(nt + 1));
+        unsigned long long *tri = ec.totals.as<unsigned long long>();
+        BSM_HIP_TRY(hipMemsetAsync(tri, 0, 2 * sizeof(unsigned long long), st));
+        k_tile_entries<0><<<tile_grid(nt), kPlanThreads, 0, st>>>(
+            nt, 1, PA->natoms, ts.G, ts.jt, ts.waves, transposed, ts.hdr.as<int>(), ts.tcols.as<int>(),
+            PA->rowptr.as<int>(), PA->cols.as<int>(), PA->tmap.as<int>(), PB->rowptr.as<int>(), PB->cols.as<int>(),
+            PB->tmap.as<int>(), ec.nent.as<int64_t>(), tri, tri + 1, nullptr, nullptr);
+        k_pad_counts<<<(unsigned)((nt + 127) / 128), 128, 0, st>>>(nt, 1, ec.nent.as<int64_t>());
+        k_scan64<<<1, 1024, 0, st>>>(nt, ec.nent.as<int64_t>(), ec.ebeg.as<int64_t>());
+        k_tile_ebeg<<<(unsigned)((nt + 1 + 127) / 128), 128, 0, st>>>(nt, 1, ec.ebeg.as<int64_t>(),
+                                                                      plan->ebeg.as<int64_t>());
+        BSM_HIP_TRY(hipMemcpyAsync(&ec.ne, ec.ebeg.as<int64_t>() + nt, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        BSM_HIP_TRY(hipMemcpyAsync(ec.ntri, tri, sizeof(ec.ntri), hipMemcpyDeviceToHost, st));
+        BSM_HIP_TRY(hipStreamSynchronize(st));
+    }
+    plan->nentries = ec.ne;
+    plan->triples = (int64_t)ec.ntri[0];
+    plan->rowwork = (int64_t)ec.ntri[1];
+    plan->flops = 2.0 * (double)PC->b * PC->b * PC->b * (double)ec.ntri[0];
+}
+
+// Write a counted plan's entries; takes the tile headers (and, transposed, moves
+// their C slots to (j, i)).
+void fill_entries(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC,
+                  TileSet &ts, Plan *plan, const EntryCount &ec)
+{
+    const int transposed = plan->transposed, es = ts.waves * ts.G + ts.jt;
+    if (transposed) std::swap(PA, PB);
+    hipStream_t st = ctx->stream;
+    const int64_t nt = ts.nt, ne = ec.ne;
+    plan->span = std::max(1, ctx->group_span);
+    plan->order = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt));
+    plan->ent = DevBuf(ctx, sizeof(int) * (size_t)((ne + 4) * es));   // 4 spare entries
+    BSM_HIP_TRY(hipMemsetAsync(plan->ent.as<int>() + ne * es, 0xff, sizeof(int) * 4 * es, st));
+    if (nt > 0) {
+        k_tile_order<<<ts.ng, 256, 0, st>>>(ts.ng, plan->span, ts.ntile.as<int>(), ts.toff.as<int64_t>(),
+                                            plan->order.as<int>());
+        k_tile_entries<1><<<tile_grid(nt), kPlanThreads, 0, st>>>(
+            nt, 1, PA->natoms, ts.G, ts.jt, ts.waves, transposed, ts.hdr.as<int>(), ts.tcols.as<int>(),
+            PA->rowptr.as<int>(), PA->cols.as<int>(), PA->tmap.as<int>(), PB->rowptr.as<int>(), PB->cols.as<int>(),
+            PB->tmap.as<int>(), nullptr, nullptr, nullptr, ec.ebeg.as<int64_t>(), plan->ent.as<int>());
+        if (transposed)   // outputs go to the slot of (j, i)
+            k_map_cslots<<<(unsigned)((nt + 127) / 128), 128, 0, st>>>(nt, ts.G, ts.jt, PC->tmap.as<int>(),
+                                                                       ts.hdr.as<int>());
+        BSM_HIP_TRY(hipGetLastError());
+    }
+    plan->hdr = std::move(ts.hdr);
+    BSM_HIP_TRY(hipStreamSynchronize(st));   // before the stages' buffers are freed
+}
+}  // namespace
 
 void launch_product_f64(Context *ctx, const Plan *plan, double alpha, const bsm_pattern_s *PA,
                         const double *A, const bsm_pattern_s *PB, const double *Bm, double beta,
@@ -999,8 +1131,8 @@ void launch_product_mixed(Context *ctx, const Plan *plan, int prec, double alpha
 // measurement.
 static double plan_cost(const Plan *p) { return (double)p->rowwork + 4.5 * (double)p->nentries; }
 
-static std::unique_ptr<Plan> new_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B,
-                                      const bsm_pattern_s *C, int variant, int G, int transposed)
+static std::unique_ptr<Plan> named_plan(const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C,
+                                        int variant)
 {
     std::unique_ptr<Plan> plan(new Plan());
     plan->ids[0] = A->id;
@@ -1011,8 +1143,28 @@ static std::unique_ptr<Plan> new_plan(Context *ctx, const bsm_pattern_s *A, cons
     plan->cutoffs[2] = C->cutoff;
     plan->natoms = C->natoms;
     plan->b = C->b;
-    build_plan(ctx, A, B, C, plan.get(), G, variant == 5 ? 2 : 1, transposed);
     plan->variant = variant;
+    return plan;
+}
+
+// direct, transposed, or (both) the one with the smaller estimated cost: both are
+// counted over the same tiles, one is written
+static std::unique_ptr<Plan> new_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B,
+                                      const bsm_pattern_s *C, int variant, int G, bool direct, bool transposed)
+{
+    TileSet ts;
+    make_tiles(ctx, C, G, variant == 5 ? 2 : 1, ts);
+    std::unique_ptr<Plan> plan;
+    EntryCount ec;
+    for (int tr = direct ? 0 : 1; tr <= (transposed ? 1 : 0); ++tr) {
+        std::unique_ptr<Plan> p = named_plan(A, B, C, variant);
+        EntryCount e;
+        count_entries(ctx, A, B, C, ts, tr, p.get(), e);
+        if (plan && !(plan_cost(p.get()) < plan_cost(plan.get()))) continue;
+        plan = std::move(p);
+        ec = std::move(e);
+    }
+    fill_entries(ctx, A, B, C, ts, plan.get(), ec);
     return plan;
 }
 
@@ -1021,7 +1173,7 @@ Plan *get_transposed_plan(Context *ctx, const bsm_pattern_s *A, const bsm_patter
     auto key = std::make_tuple(A->id, B->id, C->id, 4, G, 2);
     auto it = ctx->plans.find(key);
     if (it != ctx->plans.end()) return it->second.get();
-    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, 4, G, 1);
+    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, 4, G, false, true);
     Plan *raw = plan.get();
     ctx->plans[key] = std::move(plan);
     return raw;
@@ -1038,12 +1190,7 @@ Plan *get_plan_kind(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B
     auto key = std::make_tuple(A->id, B->id, C->id, variant, G, try_t ? 1 : 0);
     auto it = ctx->plans.find(key);
     if (it != ctx->plans.end()) return it->second.get();
-    auto make = [&](int transposed) { return new_plan(ctx, A, B, C, variant, G, transposed); };
-    std::unique_ptr<Plan> plan = ctx->transposed_plans == 2 && try_t ? make(1) : make(0);
-    if (try_t && ctx->transposed_plans == 1) {
-        std::unique_ptr<Plan> alt = make(1);
-        if (plan_cost(alt.get()) < plan_cost(plan.get())) plan = std::move(alt);
-    }
+    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, variant, G, !(try_t && ctx->transposed_plans == 2), try_t);
     Plan *raw = plan.get();
     ctx->plans[key] = std::move(plan);
     return raw;
