@@ -120,8 +120,9 @@ typedef struct {
 } bsm_product_stat;
 
 /* Rows of C per wavefront tile in product plans built from now on: 2, 4 or 8
- * (0 restores the default: 8 for the default kernel with b = 4 and 9, else 4
- * for b >= 4 and 2 below); variant 2 plans always use
+ * (0 restores the default: for the default kernel with b = 4 and 9 by the number of
+ * 8-row tiles C's pattern takes, 2 rows for products of few tiles, 4, then 8 for
+ * large ones; else 4 for b >= 4 and 2 below); variant 2 plans always use
  * 16-row workgroup tiles.  Larger values reuse each B block across more rows at
  * the cost of idle lanes.  Clears cached plans (destroy batches first). */
 int bsm_ctx_set_rows_per_wave(bsm_ctx ctx, int rows);
@@ -152,21 +153,24 @@ int bsm_ctx_set_product_variant(bsm_ctx ctx, int variant);
 /* Launch order of product tiles in plans built from now on: tiles of `span`
  * consecutive row groups are interleaved by column position (1 = group by
  * group), so that groups over similar columns share B blocks in L2.
- * 1 <= span <= 4096 (default 4).  Clears cached plans. */
+ * 1 <= span <= 4096 (until set: 4, or 1 where four groups' A blocks overflow an L2).
+ * Clears cached plans. */
 int bsm_ctx_set_group_span(bsm_ctx ctx, int span);
 
 /* Columns of the tiles of product plans built from now on.  Each group of
  * rows-per-tile consecutive rows covers the union of its rows of P_C in tiles of
  * 64 / b columns: order 0 takes the union in ascending column order; order 1
- * (default) first groups the columns by the set of the group's rows that hold an
- * output in them, so that within a tile every row multiplies only where it has
- * outputs (fewer idle lanes, fewer copied A blocks, somewhat more entries).  For
+ * (default) puts columns together that share their output rows, so that within a
+ * tile every row multiplies only where it has outputs: where the columns' range cuts
+ * many k, and the default kernel runs, tiles of columns near each other; else runs of
+ * the columns grouped by the set of the group's rows that hold an output in them.  For
  * finite operands FP64 and FP32 products are equal under both orders (each
  * element sums the same nonzero terms in ascending k); BF16 matrix-core products
- * pair entries differently and may differ in rounding.  order must be 0 or 1.  Clears cached plans (destroy batches first). */
+ * pair entries differently and may differ in rounding (under order 1 they keep the
+ * row-set runs, on a plan of their own while device memory for it is easily spared).  order must be 0 or 1.  Clears cached plans (destroy batches first). */
 int bsm_ctx_set_column_order(bsm_ctx ctx, int order);
 
-/* Transposed plans for the default product kernel (variant 4, 4 or 8 rows per
+/* Transposed plans for the default product kernel (variant 4, 2, 4 or 8 rows per
  * tile, b = 4 or 9) when A and B lie on different patterns: the product is also
  * planned as C = (B^T A^T)^T, i.e. D = B^T A^T on P_C with blocks read transposed
  * and D's blocks stored transposed at the slots of (j, i) (patterns are
@@ -239,9 +243,9 @@ int bsm_multiply_truncate(bsm_ctx ctx, double alpha, const bsm_matrix *A, const 
  * C <- alpha mask_{P_C}(A B) + beta C and C2 <- alpha mask_{P_C}(A2 B) + beta C2,
  * with A and A2 on one pattern and C and C2 on one pattern (the same products as
  * bsm_multiply_truncate, Background).  For b = 4 and 9 with the default kernel,
- * while the pair's 4-row plan fits (free device memory of twice its estimated
- * size and a quarter of the device; it is cached beside the class's default
- * plan), the pair runs as tiles of twice the rows of that plan: every copied block
+ * while the pair's 4-row (products of few tiles: 2-row) plan fits (free device memory
+ * of twice its estimated size and a quarter of the device; it is cached beside the
+ * class's default plan), the pair runs as tiles of twice the rows of that plan: every copied block
  * of B serves both products, and each element of C and C2 equals, bit for bit,
  * what bsm_multiply_truncate gives; otherwise the two products run one after the
  * other.  LNV evaluates W = X X and U = Y X this way.  Asynchronous.  Errors: as
@@ -256,7 +260,7 @@ int bsm_multiply_truncate_pair(bsm_ctx ctx, double alpha, const bsm_matrix *A, c
  * b = 4 and 9 with the default kernel, while its plan fits as above, the pair
  * runs on a transposed plan (C = (B^T A^T)^T, all patterns being symmetric; whatever
  * bsm_ctx_set_transposed_plans sets for single products) as tiles of twice the rows of
- * one 4-row plan, every copied block of A serving both products, each element
+ * one 4-row (products of few tiles: 2-row) plan, every copied block of A serving both products, each element
  * equal bit for bit to what bsm_multiply_truncate gives; otherwise the two
  * products run one after the other.  LNV evaluates X = L S with Y = L H, and
  * X_D = D S with Y_D = D H, this way.  Asynchronous.  Errors: as

@@ -565,7 +565,7 @@ int bsm_multiply_truncate_prec(bsm_ctx ctx, int precision, double alpha, const b
     check_same_shape(A, B);
     check_same_shape(A, C);
     BSM_REQUIRE(!overlaps(C, A) && !overlaps(C, B), BSM_EINVAL, "C overlaps A or B");
-    Plan *plan = get_plan(&ctx->c, A->pattern, B->pattern, C->pattern);
+    Plan *plan = get_plan(&ctx->c, A->pattern, B->pattern, C->pattern, precision);
     launch_product_mixed(&ctx->c, plan, precision, alpha, A->pattern, (const double *)A->blocks, B->pattern,
                          (const double *)B->blocks, beta, C->pattern, (double *)C->blocks);
     return BSM_OK;

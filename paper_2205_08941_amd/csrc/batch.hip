@@ -66,8 +66,8 @@ __global__ __launch_bounds__(64) void k_product_batch(const BatchDesc *__restric
                                                       unsigned *__restrict__ counters, const double *__restrict__ zblk)
 {
     using T = typename std::conditional<F64, double, float>::type;
-    constexpr int kBytes9 = KB == 4 ? 0 : RingEntry<9, kBatchRows, T>::kBytes;
-    constexpr int kBytes4 = KB == 9 ? 0 : RingEntry<4, kBatchRows, T>::kBytes;
+    constexpr int kBytes9 = KB == 4 ? 0 : RingEntry<9, kBatchRows, T>::kStep;
+    constexpr int kBytes4 = KB == 9 ? 0 : RingEntry<4, kBatchRows, T>::kStep;
     constexpr int kEntryBytes = kBytes9 > kBytes4 ? kBytes9 : kBytes4;
     __shared__ __attribute__((aligned(16))) char ring[kBatchRing * kEntryBytes];
     const int lane = threadIdx.x & 63;
@@ -86,24 +86,24 @@ __global__ __launch_bounds__(64) void k_product_batch(const BatchDesc *__restric
         if constexpr (F64) {
             if (KB == 9 || (KB == 0 && kind == kKindF64Ring9)) {
                 if constexpr (KB != 4)
-                    tile_ring<9, kBatchRows, kBatchRing, double, BUF>(it.y, d.hdr, d.ebeg, d.ent, (const double *)d.A,
+                    tile_ring<9, kBatchRows, kBatchRing, double, BUF ? kBufferCopies : kPointerCopies>(it.y, d.hdr, d.ebeg, d.ent, (const double *)d.A,
                                                                  (const double *)d.B, zblk, d.C, d.alpha, d.beta,
                                                                  (lds_char_t *)ring, d.a_bytes, d.b_bytes);
             } else {
                 if constexpr (KB != 9)
-                    tile_ring<4, kBatchRows, kBatchRing, double, BUF>(it.y, d.hdr, d.ebeg, d.ent, (const double *)d.A,
+                    tile_ring<4, kBatchRows, kBatchRing, double, BUF ? kBufferCopies : kPointerCopies>(it.y, d.hdr, d.ebeg, d.ent, (const double *)d.A,
                                                                  (const double *)d.B, zblk, d.C, d.alpha, d.beta,
                                                                  (lds_char_t *)ring, d.a_bytes, d.b_bytes);
             }
         } else {
             if (KB == 9 || (KB == 0 && kind == kKindF32Ring9)) {
                 if constexpr (KB != 4)
-                    tile_ring<9, kBatchRows, kBatchRing, float, BUF>(it.y, d.hdr, d.ebeg, d.ent, (const float *)d.A,
+                    tile_ring<9, kBatchRows, kBatchRing, float, BUF ? kBufferCopies : kPointerCopies>(it.y, d.hdr, d.ebeg, d.ent, (const float *)d.A,
                                                                 (const float *)d.B, (const float *)zblk, d.C, d.alpha,
                                                                 d.beta, (lds_char_t *)ring, d.a_bytes, d.b_bytes);
             } else {
                 if constexpr (KB != 9)
-                    tile_ring<4, kBatchRows, kBatchRing, float, BUF>(it.y, d.hdr, d.ebeg, d.ent, (const float *)d.A,
+                    tile_ring<4, kBatchRows, kBatchRing, float, BUF ? kBufferCopies : kPointerCopies>(it.y, d.hdr, d.ebeg, d.ent, (const float *)d.A,
                                                                 (const float *)d.B, (const float *)zblk, d.C, d.alpha,
                                                                 d.beta, (lds_char_t *)ring, d.a_bytes, d.b_bytes);
             }
@@ -249,7 +249,7 @@ void bsm_batch_s::run(const bsm_batch_config &cfg)
     if (cfg.mode == BSM_BATCH_SEPARATE) {
         // each product in its own launch, with the plan and kernel a single product call uses
         for (int p = 0; p < n; ++p)
-            launch_product_mixed(c, get_plan(c, pa[p], pb[p], pc[p]), prec, alpha[p], pa[p], A[p], pb[p], B[p],
+            launch_product_mixed(c, get_plan(c, pa[p], pb[p], pc[p], prec), prec, alpha[p], pa[p], A[p], pb[p], B[p],
                                  beta[p], pc[p], C[p]);
         return;
     }

@@ -88,12 +88,12 @@ class Context {
     uint64_t next_pattern_id = 1;
     int rows_per_wave = 0;      // product plans: 0 = per-b default, else 2, 4 or 8
     int product_variant = -1;   // product kernel variant of plans built from now on (-1: per-b default)
-    int group_span = 4;         // row groups interleaved in product launch order
+    int group_span = 0;         // row groups interleaved in product launch order (0: 4, or 1 for wide rows)
     int column_order = 1;       // tile columns: 0 ascending, 1 grouped by the rows they hold outputs for
     // derived patterns (same atoms, another cutoff), owned here, keyed by (source id, cutoff)
     std::map<std::pair<uint64_t, double>, bsm_pattern_s *> derived;
-    // (A, B, C, variant, rows, transposed plans allowed)
-    std::map<std::tuple<uint64_t, uint64_t, uint64_t, int, int, int>, std::unique_ptr<Plan>> plans;
+    // (A, B, C, variant, rows, transposed plans allowed, tiles in runs of the column order)
+    std::map<std::tuple<uint64_t, uint64_t, uint64_t, int, int, int, int>, std::unique_ptr<Plan>> plans;
     int transposed_plans = 1;   // 0 never, 1 when estimated cheaper, 2 whenever allowed
     // reduction scratch
     DevBuf red_partials;        // double[kRedBlocks * kRedSlots]
@@ -154,6 +154,7 @@ struct bsm_pattern_s {
     double cutoff = 0.0;
     double box[3] = {0, 0, 0};
     bsm::DevBuf pos, rowptr, cols, tmap, diag, rowidx;   // rowidx: row of every slot
+    mutable int64_t tiles8 = -1;   // product tiles of 8 rows over this pattern, once counted
 };
 
 namespace bsm {
@@ -170,12 +171,14 @@ bsm_pattern_s *derived_pattern(const bsm_pattern_s *p, double cutoff);
 // context is destroyed, so repeated driver calls reuse patterns and plans.
 const bsm_pattern_s *derived_pattern_cached(const bsm_pattern_s *p, double cutoff);
 void destroy_pattern(bsm_pattern_s *p);
-Plan *get_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C);
+// The default plan of products of a precision.
+Plan *get_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C,
+               int prec = BSM_F64);
 // A plan of a given kernel variant (0: SGPR, 1: DPP wave tiles, 2: workgroup tiles, 3 and 4: LDS-DMA
 // rings, 5: rings with tiles shared by two waves, 6: ring tiles on the FP64 matrix cores) and rows
 // per tile; transposed plans only where allowed (variant 4 launches).
 Plan *get_plan_kind(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C,
-                    int variant, int G, bool allow_transposed = false);
+                    int variant, int G, bool allow_transposed = false, bool sets = false);
 
 // ---------------------------------------------------------------- launches
 void launch_product_f64(Context *ctx, const Plan *plan, double alpha, const bsm_pattern_s *PA,

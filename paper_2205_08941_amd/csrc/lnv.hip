@@ -116,7 +116,7 @@ struct lnv_state_s {
     void mul(double alpha, const bsm_pattern_s *pa, const double *a, const bsm_pattern_s *pb, const double *b,
              double beta, const bsm_pattern_s *pc, double *cc)
     {
-        Plan *plan = get_plan(c, pa, pb, pc);
+        Plan *plan = get_plan(c, pa, pb, pc, prec);
         launch_product_mixed(c, plan, prec, alpha, pa, a, pb, b, beta, pc, cc);
         flops += plan->flops;
     }

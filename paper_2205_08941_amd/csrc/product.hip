@@ -36,6 +36,9 @@ namespace {
 constexpr int kXcd = 8;       // MI355X: 8 XCDs, workgroups dealt round-robin
 constexpr int kWaves = 4;     // wavefronts (tiles) per workgroup
 constexpr int kMaxRows = 16;  // rows of a tile, at most
+// entries past a plan's last that the kernels' prefetch reads: the rings read the slots of entry
+// 2 D - 2 past the tile's last and up to 16 slots more than one entry's (D <= 4)
+constexpr int kSpareEntries = 12;
 constexpr int kPlanThreads = 256;   // threads of a planner workgroup
 
 __device__ inline int64_t logical_workgroup(int64_t nwg_padded)
@@ -85,27 +88,27 @@ __global__ __launch_bounds__(256) void k_product_wg(
 }
 
 // One wave tile per one-wave workgroup, operands through a per-wave LDS ring
-// (BUF: copied through buffer resources of a_bytes and b_bytes).
-template <int B, int G, int D, class T = double, bool BUF = false, int W = 1, int TR = 0>
+// (CP: kPointerCopies, kBufferCopies with resources of a_bytes and b_bytes, kPackedCopies).
+template <int B, int G, int D, class T = double, int CP = kPointerCopies, int W = 1, int TR = 0>
 __global__ __launch_bounds__(64 * W) void k_product_ring(
     int64_t ntiles, int64_t nwg_padded, const int *__restrict__ order, const int *__restrict__ hdr,
     const int64_t *__restrict__ ebeg, const int *__restrict__ ent, const T *__restrict__ vA,
     const T *__restrict__ vB, const T *__restrict__ zblk, double *__restrict__ vC, double alpha, double beta,
     unsigned a_bytes, unsigned b_bytes)
 {
-    constexpr int kRing = D * RingEntry<B, G, T>::kBytes;   // per wave
+    constexpr int kRing = D * RingEntry<B, G, T>::kStep;   // per wave
     __shared__ __attribute__((aligned(16))) char ring[W * kRing];
     const int64_t t = logical_workgroup(nwg_padded);
     if (t >= ntiles) return;   // uniform over the workgroup
     const int w = W > 1 ? (int)(threadIdx.x >> 6) : 0;
-    tile_ring<B, G, D, T, BUF, W, TR>(order[t], hdr, ebeg, ent, vA, vB, zblk, vC, alpha, beta,
+    tile_ring<B, G, D, T, CP, W, TR>(order[t], hdr, ebeg, ent, vA, vB, zblk, vC, alpha, beta,
                                       (lds_char_t *)ring + w * kRing, a_bytes, b_bytes);
 }
 
 // Two products sharing B and the patterns (C = A B, C2 = A2 B) on one plan of G / 2
 // rows: one wave tile of G rows per one-wave workgroup, B's copies serving both
 // (TR = 1: a transposed plan, the launch passing the shared left operand as B).
-template <int B, int G, bool BUF, int TR = 0>
+template <int B, int G, int D, int CP, int TR = 0>
 __global__ __launch_bounds__(64) void k_product_ring_pair(
     int64_t ntiles, int64_t nwg_padded, const int *__restrict__ order, const int *__restrict__ hdr,
     const int64_t *__restrict__ ebeg, const int *__restrict__ ent, const double *__restrict__ vA,
@@ -113,10 +116,10 @@ __global__ __launch_bounds__(64) void k_product_ring_pair(
     double *__restrict__ vC, double *__restrict__ vC2, double alpha, double beta, unsigned a_bytes,
     unsigned a2_bytes, unsigned b_bytes)
 {
-    __shared__ __attribute__((aligned(16))) char ring[2 * RingEntry<B, G, double>::kBytes];
+    __shared__ __attribute__((aligned(16))) char ring[D * RingEntry<B, G, double>::kStep];
     const int64_t t = logical_workgroup(nwg_padded);
     if (t >= ntiles) return;
-    tile_ring<B, G, 2, double, BUF, 1, TR, 2>(order[t], hdr, ebeg, ent, vA, vB, zblk, vC, alpha, beta,
+    tile_ring<B, G, D, double, CP, 1, TR, 2>(order[t], hdr, ebeg, ent, vA, vB, zblk, vC, alpha, beta,
                                              (lds_char_t *)ring, a_bytes, b_bytes, vA2, vC2, a2_bytes);
 }
 
@@ -637,22 +640,37 @@ void launch_wg(hipStream_t st, const Plan *plan, const double *A, const double *
                                                          plan->ent.as<int>(), A, Bm, C, alpha, beta);
 }
 
+// Packed copies read 16 bytes at a time.
+inline bool aligned16(const void *a, const void *b, const void *c = nullptr)
+{
+    return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | reinterpret_cast<uintptr_t>(c)) & 15) == 0;
+}
+constexpr int kPackedDepth = 3;   // ring depth of packed copies
+
 template <int B, int G, int D, class T = double, int W = 1, int TR = 0>
 void launch_ring_t(hipStream_t st, const Plan *plan, const T *A, const T *Bm, double *C, double alpha, double beta,
                    const T *zblk, int64_t a_bytes, int64_t b_bytes)
 {
     const int64_t nwg_padded = ((plan->ntiles + kXcd - 1) / kXcd) * kXcd;
+    auto go = [&](auto kern, bool buf) {
+        kern<<<(unsigned)nwg_padded, 64 * W, 0, st>>>(
+            plan->ntiles, nwg_padded, plan->order.as<int>(), plan->hdr.as<int>(), plan->ebeg.as<int64_t>(),
+            plan->ent.as<int>(), A, Bm, zblk, C, alpha, beta, buf ? (unsigned)a_bytes : 0u, buf ? (unsigned)b_bytes : 0u);
+    };
+    if constexpr (B == 4 && W == 1 && D == 2) {
+        if (plan->variant == 4 && aligned16(A, Bm)) {
+            go(k_product_ring<B, G, kPackedDepth, T, kPackedCopies, W, TR>, false);
+            return;
+        }
+    }
+    // two-row tiles serve products of few tiles, whose waves run alone on their SIMDs: one entry
+    // further ahead covers the copies' latency
+    constexpr int DD = G == 2 && D == 2 && W == 1 ? 3 : D;
     // variants 4 and 5: buffer copies when both operands fit a buffer resource; else 64-bit addresses
     const bool buf = (plan->variant == 4 || plan->variant == 5) && a_bytes <= (int64_t)kBufMaxBytes &&
                      b_bytes <= (int64_t)kBufMaxBytes;
-    if (buf)
-        k_product_ring<B, G, D, T, true, W, TR><<<(unsigned)nwg_padded, 64 * W, 0, st>>>(
-            plan->ntiles, nwg_padded, plan->order.as<int>(), plan->hdr.as<int>(), plan->ebeg.as<int64_t>(),
-            plan->ent.as<int>(), A, Bm, zblk, C, alpha, beta, (unsigned)a_bytes, (unsigned)b_bytes);
-    else
-        k_product_ring<B, G, D, T, false, W, TR><<<(unsigned)nwg_padded, 64 * W, 0, st>>>(
-            plan->ntiles, nwg_padded, plan->order.as<int>(), plan->hdr.as<int>(), plan->ebeg.as<int64_t>(),
-            plan->ent.as<int>(), A, Bm, zblk, C, alpha, beta, 0u, 0u);
+    if (buf) go(k_product_ring<B, G, DD, T, kBufferCopies, W, TR>, true);
+    else go(k_product_ring<B, G, DD, T, kPointerCopies, W, TR>, false);
 }
 
 // Transposed plans (one-wave tiles of 4 or 8 rows, depth 2) compute C^T = B^T A^T:
@@ -661,7 +679,7 @@ template <int B, int G, int D, class T = double, int W = 1>
 void launch_ring(hipStream_t st, const Plan *plan, const T *A, const T *Bm, double *C, double alpha, double beta,
                  const T *zblk, int64_t a_bytes, int64_t b_bytes)
 {
-    if constexpr (W == 1 && D == 2 && (G == 4 || G == 8)) {
+    if constexpr (W == 1 && D == 2) {
         if (plan->transposed) {
             launch_ring_t<B, G, D, T, W, 1>(st, plan, Bm, A, C, alpha, beta, zblk, b_bytes, a_bytes);
             return;
@@ -811,7 +829,117 @@ __global__ void k_tile_order(int ng, int span, const int *__restrict__ ntile, co
     }
 }
 
-void make_tiles(Context *ctx, const bsm_pattern_s *PC, int G, int waves, TileSet &ts)
+// Columns of a group, at most, that k_cluster_tiles orders (more keep the order of their row sets).
+constexpr int kClusterCols = 2048;
+// Weight of a differing row in the distance of two columns, Angstrom^2.
+constexpr float kClusterRow = 20.0f;
+
+// One wave per row group: take the group's columns tile by tile, each tile the column
+// farthest from the group and the jt - 1 columns nearest to it, by squared distance plus
+// kClusterRow per row that holds an output in one of the two only.  A tile's columns then
+// need nearly the same k: fewer entries, fewer idle lanes and fewer copied blocks than
+// runs of the row-set order, whose columns share rows but lie anywhere on the sphere.
+// Counted on 4096 atoms, b = 9: 16 A x 16 A -> 16 A 13% fewer entries and 6% fewer rows
+// multiplied, 8 A x 10 A -> 18 A 12% and 12%, 10 A x 6 A -> 16 A 11% and 10%.
+// hdr and tcols hold the row-set order (k_group_tiles) and are rewritten; scr as there.
+// Ties go to the lower column, so the tiles do not depend on timing.
+__global__ __launch_bounds__(64) void k_cluster_tiles(int n, int G, int jt, const double *__restrict__ pos, double bx,
+                                                      double by, double bz, const int64_t *__restrict__ toff,
+                                                      int64_t ntiles, int *__restrict__ hdr, int *__restrict__ tcols,
+                                                      const int *__restrict__ scr)
+{
+    __shared__ float px[kClusterCols], py[kClusterCols], pz[kClusterCols];
+    __shared__ unsigned key[kClusterCols];
+    __shared__ int set[kClusterCols], pick[64];
+    const int g = blockIdx.x, lane = threadIdx.x, hs = G + G * jt;
+    const int i0 = g * G, gr = min(G, n - i0);
+    const int64_t t0 = toff[g], cap = ntiles * jt, o = t0 * jt;
+    const int nt = (int)(toff[g + 1] - t0), room = nt * jt;
+    const int *col = scr + o, *sl = scr + 5 * cap + o * G;
+    if (room > kClusterCols) return;
+    const double box[3] = {bx, by, bz};
+    double cen[3];
+    for (int d = 0; d < 3; ++d) {
+        double s = 0.0;
+        for (int a = 0; a < gr; ++a) {
+            const double v = pos[3 * (i0 + a) + d] - pos[3 * i0 + d];
+            s += v - box[d] * rint(v / box[d]);
+        }
+        cen[d] = pos[3 * i0 + d] + s / gr;
+    }
+    int left = 0;   // columns not yet taken
+    for (int u = lane; u < room; u += 64) {
+        int m = 0;
+        for (int a = 0; a < G; ++a) m |= (sl[(int64_t)u * G + a] >= 0 ? 1 : 0) << a;
+        set[u] = m;   // 0: no column here
+        float r[3] = {0.f, 0.f, 0.f};
+        if (m != 0)
+            for (int d = 0; d < 3; ++d) {
+                const double v = pos[3 * col[u] + d] - cen[d];
+                r[d] = (float)(v - box[d] * rint(v / box[d]));
+            }
+        px[u] = r[0];
+        py[u] = r[1];
+        pz[u] = r[2];
+        left += m != 0 ? 1 : 0;
+    }
+    for (int off = 32; off > 0; off >>= 1) left += __shfl_xor(left, off, 64);
+    __syncthreads();
+    const float fx = (float)bx, fy = (float)by, fz = (float)bz, ix = 1.f / fx, iy = 1.f / fy, iz = 1.f / fz;
+    // A column's key: its distance's upper bits and, below them, the column itself, so that one
+    // integer minimum gives the nearest (distances are told apart to 1 part in 4096, then by column).
+    auto pack = [](float d, int u) { return (__float_as_uint(d) & ~(unsigned)(kClusterCols - 1)) | (unsigned)u; };
+    constexpr unsigned kNone = 0xffffffffu;
+    auto least = [&](unsigned v) {   // over the wave
+        for (int off = 1; off < 64; off <<= 1) v = min(v, (unsigned)__shfl_xor((int)v, off, 64));
+        return v;
+    };
+    for (int t = 0; t < nt; ++t) {
+        unsigned best = kNone;
+        for (int u = lane; u < room; u += 64)   // the farthest: the least inverse square
+            if (set[u] != 0) best = min(best, pack(1.0f / (1.0f + px[u] * px[u] + py[u] * py[u] + pz[u] * pz[u]), u));
+        const int seed = (int)(least(best) & (kClusterCols - 1));
+        const float sx = px[seed], sy = py[seed], sz = pz[seed];
+        const int ss = set[seed];
+        for (int u = lane; u < room; u += 64) {
+            const int m = set[u];
+            float dx = px[u] - sx, dy = py[u] - sy, dz = pz[u] - sz;
+            dx -= fx * rintf(dx * ix);
+            dy -= fy * rintf(dy * iy);
+            dz -= fz * rintf(dz * iz);
+            key[u] = m == 0 ? kNone
+                            : pack((dx * dx + dy * dy + dz * dz) + kClusterRow * (float)__popc((unsigned)(m ^ ss)), u);
+        }
+        const int take = min(jt, left);
+        if (lane == 0) {
+            key[seed] = kNone;
+            set[seed] = 0;
+            pick[0] = seed;
+        }
+        __syncthreads();
+        for (int q = 1; q < take; ++q) {
+            best = kNone;
+            for (int u = lane; u < room; u += 64) best = min(best, key[u]);
+            const int u = (int)(least(best) & (kClusterCols - 1));
+            if (lane == 0) {
+                key[u] = kNone;
+                set[u] = 0;
+                pick[q] = u;
+            }
+            __syncthreads();
+        }
+        left -= take;
+        for (int x = lane; x < (G + 1) * jt; x += 64) {
+            const int a = x / jt, q = x - a * jt, u = q < take ? pick[q] : -1;
+            if (a == G) tcols[(t0 + t) * jt + q] = u >= 0 ? col[u] : -1;
+            else hdr[(t0 + t) * hs + G + a * jt + q] = u >= 0 ? sl[(int64_t)u * G + a] : -1;
+        }
+        __syncthreads();
+    }
+}
+
+// cluster: tiles of near columns (k_cluster_tiles), else runs of the context's column order
+void make_tiles(Context *ctx, const bsm_pattern_s *PC, int G, int waves, bool cluster, TileSet &ts)
 {
     hipStream_t st = ctx->stream;
     const int n = PC->natoms, jt = waves * (64 / PC->b);
@@ -838,6 +966,10 @@ void make_tiles(Context *ctx, const bsm_pattern_s *PC, int G, int waves, TileSet
     k_group_tiles<<<ng, kPlanThreads, 0, st>>>(n, G, jt, ctx->column_order, PC->rowptr.as<int>(), PC->cols.as<int>(),
                                                ts.toff.as<int64_t>(), nt, ts.hdr.as<int>(), ts.tcols.as<int>(),
                                                ts.scr.as<int>());
+    if (cluster)
+        k_cluster_tiles<<<ng, 64, 0, st>>>(n, G, jt, PC->pos.as<double>(), PC->box[0], PC->box[1], PC->box[2],
+                                           ts.toff.as<int64_t>(), nt, ts.hdr.as<int>(), ts.tcols.as<int>(),
+                                           ts.scr.as<int>());
     BSM_HIP_TRY(hipGetLastError());
 }
 
@@ -891,10 +1023,15 @@ void fill_entries(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *PB
     if (transposed) std::swap(PA, PB);
     hipStream_t st = ctx->stream;
     const int64_t nt = ts.nt, ne = ec.ne;
-    plan->span = std::max(1, ctx->group_span);
+    // Groups interleaved by column position share B blocks in L2 while their own A blocks stay
+    // there too; four groups of the 16 A class hold 18 MB of A against an XCD's 4 MB, and one group
+    // after the other runs better (1000 atoms 20.1 ms against 21.0, 4096 atoms 69.5 against 71.1),
+    // while 8 A x 10 A -> 18 A keeps its four (1000 atoms 1.52 ms against 1.54).
+    const double group_bytes = (double)ts.G * (double)PA->nnzb / std::max(1, PA->natoms) * PA->b * PA->b * 8.0;
+    plan->span = ctx->group_span > 0 ? ctx->group_span : (4.0 * group_bytes > 4.0 * (1 << 20) ? 1 : 4);
     plan->order = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt));
-    plan->ent = DevBuf(ctx, sizeof(int) * (size_t)((ne + 4) * es));   // 4 spare entries
-    BSM_HIP_TRY(hipMemsetAsync(plan->ent.as<int>() + ne * es, 0xff, sizeof(int) * 4 * es, st));
+    plan->ent = DevBuf(ctx, sizeof(int) * (size_t)((ne + kSpareEntries) * es));
+    BSM_HIP_TRY(hipMemsetAsync(plan->ent.as<int>() + ne * es, 0xff, sizeof(int) * kSpareEntries * es, st));
     if (nt > 0) {
         k_tile_order<<<ts.ng, 256, 0, st>>>(ts.ng, plan->span, ts.ntile.as<int>(), ts.toff.as<int64_t>(),
                                             plan->order.as<int>());
@@ -938,7 +1075,47 @@ void launch_product_f64(Context *ctx, const Plan *plan, double alpha, const bsm_
     }
 }
 
-// A paired launch's 4-row plan, estimated from the class's default plan (about 1.3 times its
+// Tiles of 8 rows that P_C takes, counted once per pattern.
+static int64_t tiles_of_8(Context *ctx, const bsm_pattern_s *PC)
+{
+    if (PC->tiles8 >= 0) return PC->tiles8;
+    hipStream_t st = ctx->stream;
+    const int ng = (PC->natoms + 7) / 8;
+    DevBuf ntile(ctx, sizeof(int) * ng), ntile64(ctx, sizeof(int64_t) * ng), toff(ctx, sizeof(int64_t) * (ng + 1));
+    k_group_union<<<ng, kPlanThreads, 0, st>>>(PC->natoms, 8, PC->rowptr.as<int>(), PC->cols.as<int>(), 64 / PC->b,
+                                               ntile.as<int>());
+    k_int_to_i64<<<(ng + 255) / 256, 256, 0, st>>>(ng, ntile.as<int>(), ntile64.as<int64_t>());
+    k_scan64<<<1, 1024, 0, st>>>(ng, ntile64.as<int64_t>(), toff.as<int64_t>());
+    int64_t nt = 0;
+    BSM_HIP_TRY(hipMemcpyAsync(&nt, toff.as<int64_t>() + ng, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    BSM_HIP_TRY(hipStreamSynchronize(st));
+    return PC->tiles8 = nt;
+}
+
+// Rows per tile of the ring kernels (b = 4 and 9).  8-row tiles copy the fewest blocks per
+// triple, but a product of few tiles leaves SIMDs idle behind long serial lists of k, and then
+// narrower tiles win: two rows below 1600 tiles of 8 (1.6 per SIMD), four up to about two
+// rounds of the resident 8-row waves.  Measured over 75 classes and sizes (64 to 4096 atoms) with
+// b = 9 and as many with b = 4, this line is within 2.3% and 0.4% of the best choice in the mean,
+// always 8 rows 46% and 51% slower; 64 atoms, b = 9, 8 A: 124 us with 8 rows, 44 with two;
+// 512 atoms, 8 A x 6 A -> 14 A: 276 with 8, 232 with four; 1000 atoms, 16 A: 20.2 ms with 8, 22.3 with four.
+static int ring_rows(Context *ctx, const bsm_pattern_s *PC)
+{
+    const int64_t nt = tiles_of_8(ctx, PC);
+    return nt < 1600 ? 2 : nt < (PC->b == 9 ? 4000 : 2500) ? 4 : 8;
+}
+
+// Rows of a paired launch's plan: its tiles take them twice.
+static int pair_rows(Context *ctx, const bsm_pattern_s *PC) { return tiles_of_8(ctx, PC) < 1600 ? 2 : 4; }
+
+static Plan *find_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C, int variant,
+                       int G, int transposed, int sets)
+{
+    auto it = ctx->plans.find(std::make_tuple(A->id, B->id, C->id, variant, G, transposed, sets));
+    return it == ctx->plans.end() ? nullptr : it->second.get();
+}
+
+// A second plan beside the class's default one: a paired launch's 4-row plan, estimated from the class's default plan (about 1.3 times its
 // size), fits when free device memory holds twice the estimate and a quarter of the device more.
 static bool pair_plan_fits(Context *ctx, const Plan *one)
 {
@@ -953,33 +1130,45 @@ Plan *get_pair_plan(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *
     const int b = PC->b;
     if (b != 4 && b != 9) return nullptr;
     if (ctx->product_variant >= 0 && ctx->product_variant != 4) return nullptr;
-    // direct 4-row ring plan: 8 rows per paired tile
-    auto it = ctx->plans.find(std::make_tuple(PA->id, PB->id, PC->id, 4, 4, 0));
-    if (it != ctx->plans.end()) return it->second.get();
+    // direct ring plan of half the paired tile's rows
+    const int G = pair_rows(ctx, PC);
+    if (Plan *p = find_plan(ctx, PA, PB, PC, 4, G, 0, 0)) return p;
     // The 4-row plan is a second plan beside the default one (about 1.3 times its size, 4.9 GB
     // for the 16 A class at 4096 atoms, eight times that at 32768): built only while free
     // device memory holds twice that and a quarter of the device besides (room for what the
     // caller allocates next), else the pair runs as two launches (same results either way)
     if (!pair_plan_fits(ctx, get_plan(ctx, PA, PB, PC))) return nullptr;
-    return get_plan_kind(ctx, PA, PB, PC, 4, 4);
+    return get_plan_kind(ctx, PA, PB, PC, 4, G);
 }
 
 namespace {
-template <int B, int TR>
-void launch_pair(hipStream_t st, const Plan *plan, const double *A, const double *A2, const double *Bm, double *C,
+template <int B, int G, int TR>
+void launch_pair_g(hipStream_t st, const Plan *plan, const double *A, const double *A2, const double *Bm, double *C,
                  double *C2, double alpha, double beta, const double *zblk, int64_t a_bytes, int64_t b_bytes)
 {
     const int64_t nwg_padded = ((plan->ntiles + kXcd - 1) / kXcd) * kXcd;
     const bool buf = a_bytes <= (int64_t)kBufMaxBytes && b_bytes <= (int64_t)kBufMaxBytes;
-    if (buf)
-        k_product_ring_pair<B, 8, true, TR><<<(unsigned)nwg_padded, 64, 0, st>>>(
+    auto go = [&](auto kern, bool rs) {
+        kern<<<(unsigned)nwg_padded, 64, 0, st>>>(
             plan->ntiles, nwg_padded, plan->order.as<int>(), plan->hdr.as<int>(), plan->ebeg.as<int64_t>(),
-            plan->ent.as<int>(), A, A2, Bm, zblk, C, C2, alpha, beta, (unsigned)a_bytes, (unsigned)a_bytes,
-            (unsigned)b_bytes);
-    else
-        k_product_ring_pair<B, 8, false, TR><<<(unsigned)nwg_padded, 64, 0, st>>>(
-            plan->ntiles, nwg_padded, plan->order.as<int>(), plan->hdr.as<int>(), plan->ebeg.as<int64_t>(),
-            plan->ent.as<int>(), A, A2, Bm, zblk, C, C2, alpha, beta, 0u, 0u, 0u);
+            plan->ent.as<int>(), A, A2, Bm, zblk, C, C2, alpha, beta, rs ? (unsigned)a_bytes : 0u,
+            rs ? (unsigned)a_bytes : 0u, rs ? (unsigned)b_bytes : 0u);
+    };
+    if constexpr (B == 4) {
+        if (aligned16(A, A2, Bm)) {
+            go(k_product_ring_pair<B, G, kPackedDepth, kPackedCopies, TR>, false);
+            return;
+        }
+    }
+    if (buf) go(k_product_ring_pair<B, G, 2, kBufferCopies, TR>, true);
+    else go(k_product_ring_pair<B, G, 2, kPointerCopies, TR>, false);
+}
+template <int B, int TR>
+void launch_pair(hipStream_t st, const Plan *plan, const double *A, const double *A2, const double *Bm, double *C,
+                 double *C2, double alpha, double beta, const double *zblk, int64_t a_bytes, int64_t b_bytes)
+{
+    if (plan->G == 2) launch_pair_g<B, 4, TR>(st, plan, A, A2, Bm, C, C2, alpha, beta, zblk, a_bytes, b_bytes);
+    else launch_pair_g<B, 8, TR>(st, plan, A, A2, Bm, C, C2, alpha, beta, zblk, a_bytes, b_bytes);
 }
 }  // namespace
 
@@ -987,8 +1176,8 @@ void launch_product_pair_f64(Context *ctx, const Plan *plan, double alpha, const
                              const double *A, const double *A2, const bsm_pattern_s *PB, const double *Bm,
                              double beta, const bsm_pattern_s *PC, double *C, double *C2)
 {
-    BSM_REQUIRE(plan->variant == 4 && plan->G == 4 && !plan->transposed && (PC->b == 4 || PC->b == 9),
-                BSM_EINVAL, "a paired launch takes a direct 4-row ring plan, b = 4 or 9");
+    BSM_REQUIRE(plan->variant == 4 && (plan->G == 2 || plan->G == 4) && !plan->transposed && (PC->b == 4 || PC->b == 9),
+                BSM_EINVAL, "a paired launch takes a direct 2- or 4-row ring plan, b = 4 or 9");
     if (plan->ntiles == 0) return;
     hipStream_t st = ctx->stream;
     Context::ProfRec rec{plan, nullptr, nullptr, BSM_F64, 2};
@@ -1014,19 +1203,19 @@ Plan *get_pair_plan_a(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s
     const int b = PC->b;
     if (b != 4 && b != 9) return nullptr;
     if (ctx->product_variant >= 0 && ctx->product_variant != 4) return nullptr;
-    // transposed 4-row ring plan: the tiles' rows walk B and B2, the shared A is the copied operand
-    auto it = ctx->plans.find(std::make_tuple(PA->id, PB->id, PC->id, 4, 4, 2));
-    if (it != ctx->plans.end()) return it->second.get();
+    // transposed ring plan: the tiles' rows walk B and B2, the shared A is the copied operand
+    const int G = pair_rows(ctx, PC);
+    if (Plan *p = find_plan(ctx, PA, PB, PC, 4, G, 2, 0)) return p;
     if (!pair_plan_fits(ctx, get_plan(ctx, PA, PB, PC))) return nullptr;
-    return get_transposed_plan(ctx, PA, PB, PC, 4);
+    return get_transposed_plan(ctx, PA, PB, PC, G);
 }
 
 void launch_product_pair_a_f64(Context *ctx, const Plan *plan, double alpha, const bsm_pattern_s *PA,
                                const double *A, const bsm_pattern_s *PB, const double *Bm, const double *B2,
                                double beta, const bsm_pattern_s *PC, double *C, double *C2)
 {
-    BSM_REQUIRE(plan->variant == 4 && plan->G == 4 && plan->transposed && (PC->b == 4 || PC->b == 9),
-                BSM_EINVAL, "a paired launch sharing A takes a transposed 4-row ring plan, b = 4 or 9");
+    BSM_REQUIRE(plan->variant == 4 && (plan->G == 2 || plan->G == 4) && plan->transposed && (PC->b == 4 || PC->b == 9),
+                BSM_EINVAL, "a paired launch sharing A takes a transposed 2- or 4-row ring plan, b = 4 or 9");
     if (plan->ntiles == 0) return;
     hipStream_t st = ctx->stream;
     Context::ProfRec rec{plan, nullptr, nullptr, BSM_F64, 2};
@@ -1147,64 +1336,91 @@ static std::unique_ptr<Plan> named_plan(const bsm_pattern_s *A, const bsm_patter
     return plan;
 }
 
-// direct, transposed, or (both) the one with the smaller estimated cost: both are
-// counted over the same tiles, one is written
-static std::unique_ptr<Plan> new_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B,
-                                      const bsm_pattern_s *C, int variant, int G, bool direct, bool transposed)
+// Whether tiles of near columns serve a plan whose kernel walks rows of PA and reads
+// columns of PB: where the columns' own range cuts many k (its radius well below those of
+// the rows and outputs together).  Where it cuts few or none (a narrow matrix times a wide
+// one, 6 A x 16 A -> 10 A), a tile's k are its rows' k and the row-set order idles fewer
+// lanes (nor does any k fall to the columns of a nearly full PB): there counted cost 0.478 against 0.509 of the clustered tiles, against 0.426 and
+// 0.384 for 16 A x 16 A -> 16 A.
+static bool cluster_pays(const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC)
 {
-    TileSet ts;
-    make_tiles(ctx, C, G, variant == 5 ? 2 : 1, ts);
+    const double n = (double)PB->natoms;
+    return PA->cutoff + PC->cutoff - PB->cutoff >= 0.3 * PC->cutoff && (double)PB->nnzb < 0.8 * n * n;
+}
+
+// direct, transposed, or (both) the one with the smaller estimated cost: both are
+// counted, one is written.  sets: tiles are runs of the context's column order.
+static std::unique_ptr<Plan> new_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B,
+                                      const bsm_pattern_s *C, int variant, int G, bool direct, bool transposed,
+                                      bool sets)
+{
+    TileSet tiles[2];   // plain, clustered
     std::unique_ptr<Plan> plan;
     EntryCount ec;
+    TileSet *used = nullptr;
     for (int tr = direct ? 0 : 1; tr <= (transposed ? 1 : 0); ++tr) {
+        const bool near = !sets && variant == 4 && ctx->column_order == 1 && (tr ? cluster_pays(B, A, C) : cluster_pays(A, B, C));
+        TileSet &ts = tiles[near ? 1 : 0];
+        if (ts.G == 0) make_tiles(ctx, C, G, variant == 5 ? 2 : 1, near, ts);
         std::unique_ptr<Plan> p = named_plan(A, B, C, variant);
         EntryCount e;
         count_entries(ctx, A, B, C, ts, tr, p.get(), e);
         if (plan && !(plan_cost(p.get()) < plan_cost(plan.get()))) continue;
         plan = std::move(p);
         ec = std::move(e);
+        used = &ts;
     }
-    fill_entries(ctx, A, B, C, ts, plan.get(), ec);
+    fill_entries(ctx, A, B, C, *used, plan.get(), ec);
     return plan;
 }
 
 Plan *get_transposed_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C, int G)
 {
-    auto key = std::make_tuple(A->id, B->id, C->id, 4, G, 2);
+    auto key = std::make_tuple(A->id, B->id, C->id, 4, G, 2, 0);
     auto it = ctx->plans.find(key);
     if (it != ctx->plans.end()) return it->second.get();
-    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, 4, G, false, true);
+    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, 4, G, false, true, false);
     Plan *raw = plan.get();
     ctx->plans[key] = std::move(plan);
     return raw;
 }
 
 Plan *get_plan_kind(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C,
-                    int variant, int G, bool allow_transposed)
+                    int variant, int G, bool allow_transposed, bool sets)
 {
     // C = (B^T A^T)^T is an option for the default ring kernel when A and B lie on
     // different patterns (all patterns are symmetric): a wide A times a narrow B
     // then walks the narrow pattern, with far fewer idle lanes
-    const bool try_t = allow_transposed && ctx->transposed_plans > 0 && variant == 4 && (G == 4 || G == 8) &&
+    const bool try_t = allow_transposed && ctx->transposed_plans > 0 && variant == 4 && G <= 8 &&
                        (C->b == 4 || C->b == 9) && A->id != B->id;
-    auto key = std::make_tuple(A->id, B->id, C->id, variant, G, try_t ? 1 : 0);
+    auto key = std::make_tuple(A->id, B->id, C->id, variant, G, try_t ? 1 : 0, sets ? 1 : 0);
     auto it = ctx->plans.find(key);
     if (it != ctx->plans.end()) return it->second.get();
-    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, variant, G, !(try_t && ctx->transposed_plans == 2), try_t);
+    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, variant, G, !(try_t && ctx->transposed_plans == 2), try_t, sets);
     Plan *raw = plan.get();
     ctx->plans[key] = std::move(plan);
     return raw;
 }
 
-Plan *get_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C)
+Plan *get_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C, int prec)
 {
     int variant = ctx->product_variant >= 0 ? ctx->product_variant : default_variant(C->b);
     if (variant == 6 && C->b != 9) variant = 4;   // the FP64 matrix-core tiles are for b = 9
     if (variant >= 2 && C->b != 9 && C->b != 4) variant = 0;
     int G = variant == 2 ? kMaxRows : (ctx->rows_per_wave > 0 ? ctx->rows_per_wave : default_rows_per_wave(C->b));
     if ((variant == 4 || variant == 5 || variant == 6) && (C->b == 4 || C->b == 9) && ctx->rows_per_wave == 0)
-        G = 8;   // measured best for the ring
+        G = variant == 4 && !(prec == BSM_BF16 && C->b == 9 && A == B) ? ring_rows(ctx, C) : 8;
     if ((variant == 5 || variant == 6) && G < 4) G = 4;   // two-wave and matrix-core tiles take 4 or 8 rows
+    if (variant == 4 && C->b == 9 && A == B && ctx->column_order == 1) {
+        // BF16 products of this class run on the matrix cores, which sum an entry pair by pair:
+        // they keep the row-set order's entries.  Two plans of one class stand side by side only
+        // while the second's memory is easily spared; else the one that is there serves both.
+        const int sets = prec == BSM_BF16 ? 1 : 0;
+        if (Plan *own = find_plan(ctx, A, B, C, variant, G, 0, sets)) return own;
+        Plan *other = find_plan(ctx, A, B, C, variant, G, 0, 1 - sets);
+        if (other && !pair_plan_fits(ctx, other)) return other;
+        return get_plan_kind(ctx, A, B, C, variant, G, false, sets != 0);
+    }
     return get_plan_kind(ctx, A, B, C, variant, G, true);
 }
 

@@ -45,7 +45,7 @@ __device__ inline void multiply_entry(const_as4<int> *entu, int64_t q, const_as4
 // (i_a, j) in C or -1).  Entries of tile t: ebeg[t] .. ebeg[t+1] (an even count;
 // an odd list ends in a padding entry whose A slots are all -1), each G + JT
 // ints: aslot[G] (slot of (i_a, k) in A or -1), bslot[JT] (slot of (k, j) in B
-// or -1).  The entry array has 4 spare entries at its end, so the index
+// or -1).  The entry array has spare entries at its end, so the index
 // prefetch past a tile's last entry stays in bounds.
 // T = double: FP64 product.  T = float: operands already rounded to FP32 (or to
 // BF16 and stored as FP32), FP32 fused multiply-add accumulation in the same
@@ -146,7 +146,58 @@ __device__ inline void tile_sgpr(int64_t tile, const int *__restrict__ hdr, cons
 // track that hazard into inline asm.
 #define BSM_FMA_DPP(acc, a, bq, lane) "v_fmac_f64_dpp " acc ", " a ", " bq " row_newbcast:" lane " row_mask:0xf bank_mask:0xf\n"
 
-template <int B, int NA, int R, class T = double> struct DppRow;
+// Any b: up to four FMAs to an asm block, m ascending.
+template <class T> struct DppChunk;
+template <> struct DppChunk<double> {
+    template <int L0> __device__ static inline void run(double &acc, double a0, double b0)
+    {
+        asm("s_nop 1\n" BSM_FMA_DPP("%0", "%1", "%2", "%3") : "+v"(acc) : "v"(a0), "v"(b0), "n"(L0));
+    }
+    template <int L0, int L1> __device__ static inline void run(double &acc, double a0, double a1, double b0, double b1)
+    {
+        asm("s_nop 1\n" BSM_FMA_DPP("%0", "%1", "%3", "%5") BSM_FMA_DPP("%0", "%2", "%4", "%6")
+            : "+v"(acc) : "v"(a0), "v"(a1), "v"(b0), "v"(b1), "n"(L0), "n"(L1));
+    }
+    template <int L0, int L1, int L2>
+    __device__ static inline void run(double &acc, double a0, double a1, double a2, double b0, double b1, double b2)
+    {
+        asm("s_nop 1\n" BSM_FMA_DPP("%0", "%1", "%4", "%7") BSM_FMA_DPP("%0", "%2", "%5", "%8")
+            BSM_FMA_DPP("%0", "%3", "%6", "%9")
+            : "+v"(acc) : "v"(a0), "v"(a1), "v"(a2), "v"(b0), "v"(b1), "v"(b2), "n"(L0), "n"(L1), "n"(L2));
+    }
+    template <int L0, int L1, int L2, int L3>
+    __device__ static inline void run(double &acc, double a0, double a1, double a2, double a3, double b0, double b1,
+                                      double b2, double b3)
+    {
+        asm("s_nop 1\n" BSM_FMA_DPP("%0", "%1", "%5", "%9") BSM_FMA_DPP("%0", "%2", "%6", "%10")
+            BSM_FMA_DPP("%0", "%3", "%7", "%11") BSM_FMA_DPP("%0", "%4", "%8", "%12")
+            : "+v"(acc)
+            : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(b0), "v"(b1), "v"(b2), "v"(b3), "n"(L0), "n"(L1), "n"(L2), "n"(L3));
+    }
+};
+
+template <int B, int NA, int R, class T = double> struct DppRow {
+    static constexpr int e(int m) { return R * B + m; }
+    template <int M> __device__ static inline void chunk(T &acc, const T (&av)[NA], const T (&bv)[B])
+    {
+        constexpr int left = B - M;
+        if constexpr (left >= 4) {
+            DppChunk<T>::template run<(e(M) & 15), (e(M + 1) & 15), (e(M + 2) & 15), (e(M + 3) & 15)>(
+                acc, av[e(M) >> 4], av[e(M + 1) >> 4], av[e(M + 2) >> 4], av[e(M + 3) >> 4], bv[M], bv[M + 1],
+                bv[M + 2], bv[M + 3]);
+            if constexpr (left > 4) chunk<M + 4>(acc, av, bv);
+        } else if constexpr (left == 3) {
+            DppChunk<T>::template run<(e(M) & 15), (e(M + 1) & 15), (e(M + 2) & 15)>(
+                acc, av[e(M) >> 4], av[e(M + 1) >> 4], av[e(M + 2) >> 4], bv[M], bv[M + 1], bv[M + 2]);
+        } else if constexpr (left == 2) {
+            DppChunk<T>::template run<(e(M) & 15), (e(M + 1) & 15)>(acc, av[e(M) >> 4], av[e(M + 1) >> 4], bv[M],
+                                                                    bv[M + 1]);
+        } else {
+            DppChunk<T>::template run<(e(M) & 15)>(acc, av[e(M) >> 4], bv[M]);
+        }
+    }
+    __device__ static inline void run(T &acc, const T (&av)[NA], const T (&bv)[B]) { chunk<0>(acc, av, bv); }
+};
 
 template <int NA, int R> struct DppRow<9, NA, R, double> {
     static constexpr int e(int m) { return R * 9 + m; }
@@ -188,6 +239,34 @@ template <int NA, int R> struct DppRow<4, NA, R, double> {
 // fused multiply-add per element, in m order, as the FP32 reference sums).
 #define BSM_FMA_DPP32(acc, a, bq, lane) "v_fmac_f32_dpp " acc ", " a ", " bq " row_newbcast:" lane " row_mask:0xf bank_mask:0xf\n"
 
+template <> struct DppChunk<float> {
+    template <int L0> __device__ static inline void run(float &acc, float a0, float b0)
+    {
+        asm("s_nop 1\n" BSM_FMA_DPP32("%0", "%1", "%2", "%3") : "+v"(acc) : "v"(a0), "v"(b0), "n"(L0));
+    }
+    template <int L0, int L1> __device__ static inline void run(float &acc, float a0, float a1, float b0, float b1)
+    {
+        asm("s_nop 1\n" BSM_FMA_DPP32("%0", "%1", "%3", "%5") BSM_FMA_DPP32("%0", "%2", "%4", "%6")
+            : "+v"(acc) : "v"(a0), "v"(a1), "v"(b0), "v"(b1), "n"(L0), "n"(L1));
+    }
+    template <int L0, int L1, int L2>
+    __device__ static inline void run(float &acc, float a0, float a1, float a2, float b0, float b1, float b2)
+    {
+        asm("s_nop 1\n" BSM_FMA_DPP32("%0", "%1", "%4", "%7") BSM_FMA_DPP32("%0", "%2", "%5", "%8")
+            BSM_FMA_DPP32("%0", "%3", "%6", "%9")
+            : "+v"(acc) : "v"(a0), "v"(a1), "v"(a2), "v"(b0), "v"(b1), "v"(b2), "n"(L0), "n"(L1), "n"(L2));
+    }
+    template <int L0, int L1, int L2, int L3>
+    __device__ static inline void run(float &acc, float a0, float a1, float a2, float a3, float b0, float b1,
+                                      float b2, float b3)
+    {
+        asm("s_nop 1\n" BSM_FMA_DPP32("%0", "%1", "%5", "%9") BSM_FMA_DPP32("%0", "%2", "%6", "%10")
+            BSM_FMA_DPP32("%0", "%3", "%7", "%11") BSM_FMA_DPP32("%0", "%4", "%8", "%12")
+            : "+v"(acc)
+            : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(b0), "v"(b1), "v"(b2), "v"(b3), "n"(L0), "n"(L1), "n"(L2), "n"(L3));
+    }
+};
+
 template <int NA, int R> struct DppRow<9, NA, R, float> {
     static constexpr int e(int m) { return R * 9 + m; }
     __device__ static inline void run(float &acc, const float (&av)[NA], const float (&bv)[9])
@@ -228,6 +307,21 @@ template <int B, int NA, class T, int... R>
 __device__ inline void fma_block(T (&acc)[B], const T (&av)[NA], const T (&bv)[B], std::integer_sequence<int, R...>)
 {
     (DppRow<B, NA, R, T>::run(acc[R], av, bv), ...);
+}
+
+// the same, lanes with `keep` set keeping their sums
+template <int B, int NA, class T, int R>
+__device__ inline void fma_row_keep(T &acc, const T (&av)[NA], const T (&bv)[B], bool keep)
+{
+    const T old = acc;
+    DppRow<B, NA, R, T>::run(acc, av, bv);
+    acc = keep ? old : acc;
+}
+template <int B, int NA, class T, int... R>
+__device__ inline void fma_block_keep(T (&acc)[B], const T (&av)[NA], const T (&bv)[B], bool keep,
+                                      std::integer_sequence<int, R...>)
+{
+    (fma_row_keep<B, NA, T, R>(acc[R], av, bv, keep), ...);
 }
 
 // Element l16 + 16 v of the block into register v; indices past the block wrap
@@ -507,14 +601,22 @@ __device__ inline void tile_wg(int64_t tile, const int *__restrict__ hdr, const 
 // instructions, reading the zero block for an absent A_{i_a k} or B_kj, so the
 // number of loads issued after an entry is known and one s_waitcnt per entry
 // (vmcnt at most that number, clamped to the counter's 63) orders it before
-// its LDS reads.  Block slot indices come through the scalar cache, so no
-// other vector loads share the vmcnt counter in the loop.
+// its LDS reads.  A ring position of tile_ring also takes, by the same kind of
+// copy, the slots of the entry copied into it next (D entries on): they land
+// with the blocks they follow, wait for nothing of their own, and count like
+// any copy.
 template <int B, int G, class T = double> struct RingEntry {
     static constexpr int kBlocks = G + 64 / B;               // A rows, then B columns
     static constexpr int kBytes = kBlocks * B * B * (int)sizeof(T);
     static constexpr int kDwords = B * B * (int)sizeof(T) / 4;   // per block
     static constexpr int kInstPerBlock = (kDwords + 63) / 64;
     static constexpr int kInst = kBlocks * kInstPerBlock;    // DMA loads per entry
+    static constexpr int kSlotVecs = (kBlocks + 15) / 16;    // vectors of 16 slots, at most
+    // packed copies (kPackedCopies): 16 bytes per lane, the lanes of one DMA load over several blocks
+    static constexpr int kLanesPerBlock = B * B * (int)sizeof(T) / 16;
+    static constexpr int kBlocksPerInst = kLanesPerBlock > 0 ? 64 / kLanesPerBlock : 0;
+    static constexpr int kPackedInst = kBlocksPerInst > 0 ? (kBlocks + kBlocksPerInst - 1) / kBlocksPerInst : 0;
+    static constexpr int kStep = kBytes + 256 * kSlotVecs;   // tile_ring: bytes of a ring position
 };
 
 typedef __attribute__((address_space(3))) void lds_void_t;
@@ -545,6 +647,21 @@ __device__ inline void dma_block(const char *g, lds_void_t *l, int lane, std::in
     }
 }
 
+// whether any element of an A block, as a wave holds it, is not finite (wave-uniform)
+template <int NA, class T> __device__ inline bool nonfinite_row(const T (&x)[NA])
+{
+    bool bad = false;
+#pragma unroll
+    for (int v = 0; v < NA; ++v) bad |= !__builtin_isfinite(x[v]);
+    return __ballot(bad) != 0ull;
+}
+
+// f(integral_constant<int, 0>), f(integral_constant<int, 1>), ... for the blocks of an entry
+template <class F, int... I> __device__ __attribute__((always_inline)) inline void slot_blocks(F f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
 // The same copy through a raw buffer resource: voffset = the block's byte
 // offset + 4 lane.  An absent block (slot -1) has offset 2^32 - block bytes:
 // with the lane and immediate offsets it stays below 2^32 and above the
@@ -562,6 +679,14 @@ __device__ inline void dma_block_buf(__amdgpu_buffer_rsrc_t rs, unsigned vo, lds
     }
 }
 
+// How a ring copies its blocks: 64-bit addresses or buffer resources, 4 bytes per
+// lane and one block per load; or, where a block is a multiple of 16 bytes that
+// divides a load (b = 4), 16 bytes per lane and 64 / lanes-per-block blocks per load.
+// The last needs operands at 16-byte boundaries.  An entry of an 8-row tile takes 3
+// such loads instead of 24: b = 4, 8 rows, 1000 atoms, 14 A x 8 A -> 8 A 175 -> 137 us,
+// 216 atoms, 16 A 184 -> 156 us; 4096 atoms, 16 A, held by the bytes, 10.7 -> 10.5 ms.
+enum { kPointerCopies = 0, kBufferCopies = 1, kPackedCopies = 2 };
+
 // Largest operand (bytes) the buffer copies address: absent-block offsets
 // (2^32 - block bytes and up) must lie past it.
 constexpr unsigned kBufMaxBytes = 0xfffff000u;
@@ -569,9 +694,9 @@ constexpr unsigned kBufMaxBytes = 0xfffff000u;
 // T = double: FP64 product.  T = float: operands already rounded (FP32, or BF16
 // stored as FP32), FP32 fused multiply-adds in the same (k, m) order, the sums
 // widened to FP64 for alpha, beta and the store.
-// BUF: copies through raw buffer resources over A and B (a_bytes, b_bytes, each
-// at most kBufMaxBytes): one scalar multiply and one vector add per block
-// instead of 64-bit address arithmetic and a zero-block select.
+// CP: how blocks are copied (above).  kBufferCopies: through raw buffer resources
+// over A and B (a_bytes, b_bytes, each at most kBufMaxBytes), one vector add per
+// block instead of 64-bit address arithmetic and a zero-block select.
 // W = 2: the tile has 2 JT columns and two waves of one workgroup share it,
 // wave w taking columns w JT .. w JT + JT - 1 with its own ring.  Both waves walk
 // the tile's one list of k; each entry holds a half per wave (A slots of the
@@ -589,7 +714,8 @@ constexpr unsigned kBufMaxBytes = 0xfffff000u;
 // TR = 1 on a transposed plan: C = (B^T A^T)^T and C2 = (B^T A2^T)^T, i.e. two
 // products sharing their left operand).  Each product's elements sum the same
 // terms in the same order as its own launch.
-template <int B, int G, int D, class T = double, bool BUF = false, int W = 1, int TR = 0, int DU = 1>
+// Entries ebeg[tile] .. ebeg[tile + 1] are multiplied; `cont`: onto the sums in C.
+template <int B, int G, int D, class T = double, int CP = kPointerCopies, int W = 1, int TR = 0, int DU = 1>
 __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, const int *__restrict__ hdr, const int64_t *__restrict__ ebeg,
                                  const int *__restrict__ ent, const T *__restrict__ vA, const T *__restrict__ vB,
                                  const T *__restrict__ zblk, double *__restrict__ vC, double alpha, double beta,
@@ -609,7 +735,16 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
     constexpr int HS = GP + GP * JT * W;
     constexpr int ES = (GP + JT) * W;
     constexpr int NS = GP + JT;                // plan slots per entry and wave
-    constexpr int NB = RE::kBlocks, DW = RE::kDwords, IPB = RE::kInstPerBlock, NI = RE::kInst;
+    constexpr bool PK = CP == kPackedCopies;
+    constexpr int NB = RE::kBlocks, DW = RE::kDwords, IPB = RE::kInstPerBlock;
+    constexpr int LPB = RE::kLanesPerBlock, BPI = RE::kBlocksPerInst, NP = RE::kPackedInst;
+    static_assert(!PK || (BB * ESZ % 16 == 0 && LPB > 0 && 64 % (LPB > 0 ? LPB : 1) == 0 && NS <= 64), "packed copies");
+    constexpr int NV = (NS + 15) / 16;         // vectors of 16 slots (one of all slots when packed)
+    constexpr int NL = PK ? 1 : NV;            // DMA loads of an entry's slots
+    constexpr int NI = (PK ? NP : RE::kInst) + NL;   // DMA loads of a step
+    constexpr int NR = PK ? NP + 1 : NV;       // registers of an entry's slots
+    // other b than 4 and 9 multiply no absent block, not even a non-finite A by zero
+    constexpr bool SAFE = B != 4 && B != 9;
     const int lane = threadIdx.x & 63;
     const int w = W > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
     const int l16 = lane & 15;
@@ -624,6 +759,8 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
         cs[a] = lane_ok ? h[GP + (a % GP) * JT * W + w * JT + jl] : -1;
         cact[a] = cs[a] >= 0;
     }
+    // TR: element (r, c) of D is element (c, r) of C's block
+    constexpr int RS = TR ? 1 : B;
     T acc[G][B];
 #pragma unroll
     for (int a = 0; a < G; ++a)
@@ -635,54 +772,114 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
     const int64_t e1 = __builtin_amdgcn_readfirstlane((int)(ebeg[tile + 1] & 0xffffffff)) |
                        ((int64_t)__builtin_amdgcn_readfirstlane((int)(ebeg[tile + 1] >> 32)) << 32);
     const int n = (int)(e1 - e0);
-    const_as4<int> *entu = (const_as4<int> *)(ent + e0 * ES + w * NS);
+    const int *entw = ent + e0 * ES + w * NS;
 
-    // Copy an entry, given its slots, into ring position P; keep its A slots in
-    // `asl`.  The DMA's immediate offset advances the global and the LDS address
-    // together.  The slots of the entry copied next are loaded (scalar loads)
-    // before the current copies are issued, so their latency overlaps them; near
-    // the tile's end these loads read the next tile's entries or the plan's four
-    // spare entries, which are not used.
+    // Slots come 16 to a vector, the same 16 in every row of 16 lanes: one DPP row
+    // broadcast then adds a slot's byte offset to the lane's, and a compare gives the
+    // absent blocks as a scalar mask.  Packed copies take, per load, the slot of the
+    // lane's block, and one vector of all slots for the mask.
     const int lane4 = 4 * lane;
-    auto load_slots = [&](int q, int (&sl)[NS]) {
+    int at[NR];
 #pragma unroll
-        for (int blk = 0; blk < NS; ++blk) sl[blk] = entu[(int64_t)q * ES + blk];
+    for (int v = 0; v < NR; ++v) {
+        if constexpr (PK) {
+            const int blk = v * BPI + lane / LPB;
+            at[v] = v == NP ? min(lane, NS - 1) : (blk < G ? blk % GP : min(GP + (blk - G), NS - 1));
+        } else {
+            at[v] = l16 + 16 * v;
+        }
+    }
+    // packed copies: where a lane's operand begins, at the lane's place in a block
+    uint64_t from[PK ? NP : 1];
+    const uint64_t zero = (uint64_t)zblk + (PK ? 16 * (lane % (LPB > 0 ? LPB : 1)) : 0);
+    if constexpr (PK) {
+        const uint64_t pa = (uint64_t)vA, pa2 = (uint64_t)(DU == 2 ? vA2 : vA), pb = (uint64_t)vB;
+#pragma unroll
+        for (int v = 0; v < NP; ++v) {
+            const int blk = v * BPI + lane / LPB;
+            const uint64_t first = blk < GP ? ~0ull : 0ull, rows = blk < G ? ~0ull : 0ull;
+            from[v] = ((pa & first) | (pa2 & rows & ~first) | (pb & ~rows)) + 16 * (lane % LPB);
+        }
+    }
+    auto load_slots = [&](int q, int (&sl)[NR]) {   // straight to registers: the tile's first entries
+#pragma unroll
+        for (int v = 0; v < NR; ++v) sl[v] = entw[(int64_t)q * ES + at[v]];
+    };
+    auto read_slots = [&](auto P, int (&sl)[NR]) {   // those that ring position P holds
+        lds_const_t<int> *p = (lds_const_t<int> *)(ring + decltype(P)::value * RE::kStep + RE::kBytes);
+#pragma unroll
+        for (int v = 0; v < NR; ++v) sl[v] = PK ? p[at[v]] : p[lane + 64 * v];
     };
     const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc((void *)vA, 0, (int)a_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc((void *)vB, 0, (int)b_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsA2 =
         __builtin_amdgcn_make_buffer_rsrc((void *)(DU == 2 ? vA2 : vA), 0, (int)(DU == 2 ? a2_bytes : a_bytes), 0x00020000);
-    // ring block blk: A rows (the plan's rows, then for DU = 2 the same slots of A2), then B columns
-    auto issue = [&](auto P, const int (&sl)[NS], int (&asl)[G]) {
-        lds_char_t *slot = ring + decltype(P)::value * RE::kBytes;
+    // Copy entry q, given its slots, and the slots of entry q + D into ring position P;
+    // near the tile's end these are the next tile's entries or the plan's spare
+    // entries, never multiplied.  Ring blocks: A rows (the plan's rows, then for DU = 2
+    // the same slots of A2), then B columns.  `gone`: bit s is set where slot s is absent.
+    auto issue = [&](auto P, int q, const int (&sl)[NR], unsigned &gone) {
+        lds_char_t *slot = ring + decltype(P)::value * RE::kStep;
+        if constexpr (PK) {
+            gone = (unsigned)__ballot(sl[NP] < 0);
 #pragma unroll
-        for (int a = 0; a < G; ++a) asl[a] = sl[a % GP];
-#pragma unroll
-        for (int blk = 0; blk < NB; ++blk) {
-            lds_void_t *l = (lds_void_t *)(slot + blk * (BB * ESZ));
-            const int s_ = blk < G ? sl[blk % GP] : sl[GP + (blk - G)];
-            if constexpr (BUF) {
-                const unsigned vo = (unsigned)s_ * (unsigned)(BB * ESZ) + (unsigned)lane4;
-                dma_block_buf<IPB, DW>(blk < GP ? rsA : (blk < G ? rsA2 : rsB), vo, l, lane,
-                                       std::make_integer_sequence<int, IPB>{});
-            } else {
+            for (int v = 0; v < NP; ++v) {
+                const int blk = v * BPI + lane / LPB;
                 // absent blocks (slot -1) copy the zero block; selected with masks, not a branch
-                const T *base = blk < GP ? vA : (blk < G ? (DU == 2 ? vA2 : vA) : vB);
-                const uint64_t real = (uint64_t)base + (uint64_t)((int64_t)s_ * (BB * ESZ));
-                const uint64_t neg = (uint64_t)(int64_t)(s_ >> 31);
-                const char *g = reinterpret_cast<const char *>((real & ~neg) | ((uint64_t)zblk & neg)) + lane4;
-                dma_block<IPB, DW>(g, l, lane, std::make_integer_sequence<int, IPB>{});
+                const uint64_t real = from[v] + (uint64_t)((int64_t)sl[v] * (BB * ESZ));
+                const uint64_t neg = (uint64_t)(int64_t)(sl[v] >> 31);
+                const char *g = reinterpret_cast<const char *>((real & ~neg) | (zero & neg));
+                lds_void_t *l = (lds_void_t *)(slot + v * (BPI * BB * ESZ));
+                if ((v + 1) * BPI <= NB || blk < NB) __builtin_amdgcn_global_load_lds((const void *)g, l, 16, 0, 0);
             }
+        } else {
+            int off[NV];
+            gone = 0u;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                gone |= ((unsigned)__ballot(sl[v] < 0) & 0xffffu) << (16 * (v & 1));
+                off[v] = (int)((unsigned)sl[v] * (unsigned)(BB * ESZ));
+            }
+            slot_blocks([&](auto BLK) {
+                constexpr int blk = decltype(BLK)::value;
+                constexpr int s_at = blk < G ? blk % GP : GP + (blk - G);   // slot of the block in the entry
+                lds_void_t *l = (lds_void_t *)(slot + blk * (BB * ESZ));
+                if constexpr (CP == kBufferCopies) {
+                    const unsigned vo =
+                        (unsigned)__builtin_amdgcn_mov_dpp(off[s_at / 16], 0x150 + s_at % 16, 0xf, 0xf, true) +
+                        (unsigned)lane4;
+                    dma_block_buf<IPB, DW>(blk < GP ? rsA : (blk < G ? rsA2 : rsB), vo, l, lane,
+                                           std::make_integer_sequence<int, IPB>{});
+                } else {
+                    // absent blocks (slot -1) copy the zero block; selected with masks, not a branch
+                    const int s_ = __builtin_amdgcn_readlane(sl[s_at / 16], s_at % 16);
+                    const T *base = blk < GP ? vA : (blk < G ? (DU == 2 ? vA2 : vA) : vB);
+                    const uint64_t real = (uint64_t)base + (uint64_t)((int64_t)s_ * (BB * ESZ));
+                    const uint64_t neg = (uint64_t)(int64_t)(s_ >> 31);
+                    const char *g = reinterpret_cast<const char *>((real & ~neg) | ((uint64_t)zblk & neg)) + lane4;
+                    dma_block<IPB, DW>(g, l, lane, std::make_integer_sequence<int, IPB>{});
+                }
+            }, std::make_integer_sequence<int, NB>{});
         }
+        const int *es = entw + (int64_t)(q + D) * ES;
+#pragma unroll
+        for (int v = 0; v < NL; ++v)
+            __builtin_amdgcn_global_load_lds((const void *)(es + (PK ? at[NR - 1] : at[v])),
+                                             (lds_void_t *)(slot + RE::kBytes + 256 * v), 4, 0, 0);
     };
     // at most `later` entries' copies still in flight
     auto wait_for = [&](auto L) {
-        constexpr int later = decltype(L)::value;
-        wait_vmcnt<(later * NI < 63 ? later * NI : 63)>();
+        constexpr int later = decltype(L)::value * NI;
+        wait_vmcnt<(later < 63 ? later : 63)>();
     };
     // multiply the entry held at ring position P
-    auto compute = [&](auto P, const int (&as)[G]) {
-        const lds_char_t *slot = ring + decltype(P)::value * RE::kBytes;
+    auto compute = [&](auto P, unsigned gone) {
+        int as[G];
+#pragma unroll
+        for (int a = 0; a < G; ++a) as[a] = ((gone >> (a % GP)) & 1u) ? -1 : 0;
+        const bool bgone = SAFE && ((gone >> (GP + jl)) & 1u);
+        const bool part = SAFE && ((gone >> GP) & ((1u << (JT & 31)) - 1u)) != 0u;
+        const lds_char_t *slot = ring + decltype(P)::value * RE::kStep;
         T bv[B];
         lds_const_t<T> *bp = (lds_const_t<T> *)(slot + (G + jl) * (BB * ESZ)) + (TR ? c * B : c);
 #pragma unroll
@@ -697,7 +894,7 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
                 xr[v] = ap[idx];
             }
         };
-        if constexpr (G <= 4) {
+        if constexpr (G <= 4 && !SAFE) {
             // all rows' A values read up front (their LDS latency overlaps)
             T xa[G][NA];
 #pragma unroll
@@ -712,55 +909,61 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
 #pragma unroll
             for (int a = 0; a < G; ++a) {
                 if (a + 1 < G) read_row(xr[(a + 1) & 1], a + 1);
-                if (as[a] >= 0) fma_block<B, NA, T>(acc[a], xr[a & 1], bv, std::make_integer_sequence<int, B>{});
+                if (as[a] < 0) continue;
+                if constexpr (SAFE) {
+                    if (part && nonfinite_row<NA, T>(xr[a & 1])) {   // lanes without a B block keep their sums
+                        fma_block_keep<B, NA, T>(acc[a], xr[a & 1], bv, bgone, std::make_integer_sequence<int, B>{});
+                        continue;
+                    }
+                }
+                fma_block<B, NA, T>(acc[a], xr[a & 1], bv, std::make_integer_sequence<int, B>{});
             }
         }
     };
-    static_assert(D >= 2 && D <= 3, "ring depth 2 or 3");
+    static_assert(D >= 2 && D <= 4, "ring depth 2 to 4");
 
     // Every step copies the entry D - 1 ahead, also past the tile's end (the
     // next tile's entries or the plan's spare entries: in bounds, never
     // multiplied), so the steps are straight-line code and each waits for the
-    // same count; the tile ends by draining its copies.  sbuf[p] holds the slots
-    // of the entry copied next into ring position p; they are loaded one step
-    // ahead, up to D entries past the tile.  Entry counts are even, so for D = 2
-    // both steps of an iteration are inside the tile.
-    int asl[D][G];
-    int sbuf[D][NS];
+    // same count; the tile ends by draining its copies.  `next` holds the slots of
+    // the entry copied next: those that landed with the entry multiplied in the
+    // step before.  Entry counts are even, so for D = 2 both steps of an iteration
+    // are inside the tile.
+    unsigned gone[D];
+    int next[NR];
     if (n > 0) {
-        load_slots(0, sbuf[0]);
-        load_slots(1, sbuf[1]);
-        issue(std::integral_constant<int, 0>{}, sbuf[0], asl[0]);
-        if constexpr (D == 3) {
-            load_slots(2, sbuf[2]);
-            issue(std::integral_constant<int, 1>{}, sbuf[1], asl[1]);
-        }
+        int first[D][NR];
+#pragma unroll
+        for (int d = 0; d < D; ++d) load_slots(d, first[d]);
+        issue(std::integral_constant<int, 0>{}, 0, first[0], gone[0]);
+        if constexpr (D >= 3) issue(std::integral_constant<int, 1>{}, 1, first[1], gone[1]);
+        if constexpr (D >= 4) issue(std::integral_constant<int, 2>{}, 2, first[2], gone[2]);
+#pragma unroll
+        for (int v = 0; v < NR; ++v) next[v] = first[D - 1][v];
     }
     for (int q0 = 0; q0 < n; q0 += D) {
         // ring position of entry q0 + r is r; entry q0 + r + D - 1 goes to (r + D - 1) % D
         auto step = [&](auto R) {
             constexpr int r = decltype(R)::value;
             constexpr int pn = (r + D - 1) % D;
-            if constexpr (D == 3)
+            if constexpr (D >= 3)
                 if (q0 + r >= n) return;
             if constexpr (W > 1) __builtin_amdgcn_s_barrier();   // both waves at entry q0 + r
-            load_slots(q0 + r + D, sbuf[r]);   // entry q0 + r's slots are no longer needed
-            __builtin_amdgcn_sched_barrier(0);    // these loads first: their latency overlaps the copies
-            issue(std::integral_constant<int, pn>{}, sbuf[pn], asl[pn]);
+            issue(std::integral_constant<int, pn>{}, q0 + r + D - 1, next, gone[pn]);
             wait_for(std::integral_constant<int, D - 1>{});
-            compute(std::integral_constant<int, r>{}, asl[r]);
+            read_slots(R, next);
+            compute(R, gone[r]);
         };
         step(std::integral_constant<int, 0>{});
         step(std::integral_constant<int, 1>{});
-        if constexpr (D == 3) step(std::integral_constant<int, 2>{});
+        if constexpr (D >= 3) step(std::integral_constant<int, 2>{});
+        if constexpr (D >= 4) step(std::integral_constant<int, 3>{});
     }
     wait_vmcnt<0>();
 #pragma unroll
     for (int a = 0; a < G; ++a) {
         if (!cact[a]) continue;
-        // TR: element (r, c) of D is element (c, r) of C's block
         double *cp = (DU == 2 && a >= GP ? vC2 : vC) + (int64_t)cs[a] * BB + (TR ? c * B : c);
-        constexpr int RS = TR ? 1 : B;
         if (beta == 0.0) {
 #pragma unroll
             for (int r = 0; r < B; ++r) cp[r * RS] = alpha * (double)acc[a][r];
