@@ -10,11 +10,35 @@ constexpr int kT = 256;
 
 inline unsigned grid1(int64_t n) { return (unsigned)std::max<int64_t>(1, (n + kT - 1) / kT); }
 
-__global__ void k_axpby(int64_t n, double a, const double *__restrict__ x, double b, double *__restrict__ y)
+__global__ void k_axpby(int64_t n, double a, const double *x, double b, double *y)
 {
     int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (e >= n) return;
-    y[e] = (b == 0.0) ? a * x[e] : a * x[e] + b * y[e];
+    y[e] = (b == 0.0) ? a * x[e] : fma(b, y[e], a * x[e]);
+}
+
+// The same for 16-byte aligned arrays of an even count: kUnroll pairs per thread, all loads
+// before the stores (each element is the fma above, written out so that both give the same bits).
+constexpr int kUnroll = 4;
+__global__ __launch_bounds__(kT) void k_axpby2(int64_t n2, double a, const double2 *x, double b, double2 *y)
+{
+    const int64_t e0 = (int64_t)blockIdx.x * (kT * kUnroll) + threadIdx.x;
+    double2 xv[kUnroll], yv[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t e = e0 + u * kT;
+        if (e >= n2) continue;
+        xv[u] = x[e];
+        if (b != 0.0) yv[u] = y[e];
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t e = e0 + u * kT;
+        if (e >= n2) continue;
+        double2 v = make_double2(a * xv[u].x, a * xv[u].y);
+        if (b != 0.0) v = make_double2(fma(b, yv[u].x, v.x), fma(b, yv[u].y, v.y));
+        y[e] = v;
+    }
 }
 
 // z <- a x + b y + c z, one element per thread (x or y may be z).  Each element
@@ -29,45 +53,72 @@ __global__ void k_axpbypcz(int64_t n, double a, const double *x, double b, const
     z[e] = (c == 0.0) ? v : fma(c, z[e], v);
 }
 
-// The same for an even count of 16-byte aligned elements, two per thread
-// (16-byte loads and stores).
-__global__ void k_axpbypcz2(int64_t n2, double a, const double2 *x, double b, const double2 *y, double c,
-                            double2 *z)
+// The same for an even count of 16-byte aligned elements, kUnroll pairs per thread.
+__global__ __launch_bounds__(kT) void k_axpbypcz2(int64_t n2, double a, const double2 *x, double b, const double2 *y,
+                                                  double c, double2 *z)
 {
-    int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (e >= n2) return;
-    const double2 xv = x[e], yv = y[e];
-    double2 v = make_double2(fma(a, xv.x, b * yv.x), fma(a, xv.y, b * yv.y));
-    if (c != 0.0) {
-        const double2 zv = z[e];
-        v = make_double2(fma(c, zv.x, v.x), fma(c, zv.y, v.y));
+    const int64_t e0 = (int64_t)blockIdx.x * (kT * kUnroll) + threadIdx.x;
+    double2 xv[kUnroll], yv[kUnroll], zv[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t e = e0 + u * kT;
+        if (e >= n2) continue;
+        xv[u] = x[e];
+        yv[u] = y[e];
+        if (c != 0.0) zv[u] = z[e];
     }
-    z[e] = v;
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t e = e0 + u * kT;
+        if (e >= n2) continue;
+        double2 v = make_double2(fma(a, xv[u].x, b * yv[u].x), fma(a, xv[u].y, b * yv[u].y));
+        if (c != 0.0) v = make_double2(fma(c, zv[u].x, v.x), fma(c, zv[u].y, v.y));
+        z[e] = v;
+    }
 }
 
 // In place (M_ij, M_ji) <- ((M_ij + M_ji^T)/2, its transpose).  The thread of
 // element (p, q) of slot s with s < t (or s == t and p <= q) writes both partners.
-__global__ void k_symmetrize(int64_t nnz, int b, const int *__restrict__ tmap, double *__restrict__ M)
+// Four elements per thread, all loads before the stores.
+template <int BC>
+__global__ __launch_bounds__(kT) void k_symmetrize(int64_t nnz, int b_arg, const int *__restrict__ tmap, double *M)
 {
-    const int bb = b * b;
-    int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (e >= nnz * bb) return;
-    const int64_t s = e / bb;
-    const int r = (int)(e - s * bb), p = r / b, q = r - p * b;
-    const int64_t t = tmap[s];
-    if (t < s || (t == s && p > q)) return;
-    double *x = M + s * bb + p * b + q;
-    double *y = M + t * bb + q * b + p;
-    const double v = 0.5 * (*x + *y);
-    *x = v;
-    *y = v;
+    const int b = BC > 0 ? BC : b_arg, bb = b * b;
+    const int64_t nel = nnz * bb, e0 = (int64_t)blockIdx.x * (kT * kUnroll) + threadIdx.x;
+    int64_t at[kUnroll];
+    double x[kUnroll], y[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t e = e0 + u * kT;
+        at[u] = -1;
+        if (e >= nel) continue;
+        const int64_t s = e / bb;
+        const int r = (int)(e - s * bb), p = r / b, q = r - p * b;
+        const int64_t t = tmap[s];
+        if (t < s || (t == s && p > q)) continue;
+        at[u] = t * bb + q * b + p;
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+        if (at[u] >= 0) {
+            x[u] = M[e0 + u * kT];
+            y[u] = M[at[u]];
+        }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+        if (at[u] >= 0) {
+            const double v = 0.5 * (x[u] + y[u]);
+            M[e0 + u * kT] = v;
+            M[at[u]] = v;
+        }
 }
 
 // out[s] <- alpha (M[s] + M[t]^T) + beta out[s]
-__global__ void k_add_transpose(int64_t nnz, int b, const int *__restrict__ tmap, double alpha,
+template <int BC>
+__global__ void k_add_transpose(int64_t nnz, int b_arg, const int *__restrict__ tmap, double alpha,
                                 const double *__restrict__ M, double beta, double *__restrict__ out)
 {
-    const int bb = b * b;
+    const int b = BC > 0 ? BC : b_arg, bb = b * b;
     int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (e >= nnz * bb) return;
     const int64_t s = e / bb;
@@ -89,24 +140,29 @@ __device__ inline int find_in_row(const int *__restrict__ rowptr, const int *__r
 }
 
 // One workgroup per chunk of destination slots: look up the source slot, copy or zero.
-__global__ __launch_bounds__(kT) void k_mask_copy(int64_t nnzd, int b, const int *__restrict__ rowsD,
+// Chunks of 64 slots: 256 left the narrow patterns (6 A at 4096 atoms: 680 chunks) too few
+// workgroups to cover the loads.
+constexpr int kMaskSlots = 64;
+template <int BC>
+__global__ __launch_bounds__(kT) void k_mask_copy(int64_t nnzd, int b_arg, const int *__restrict__ rowsD,
                                                   const int *__restrict__ colsD, const int *__restrict__ rpS,
                                                   const int *__restrict__ colsS, const double *__restrict__ src,
                                                   double *__restrict__ dst)
 {
-    __shared__ int ss[kT];
-    const int bb = b * b;
-    const int64_t base = (int64_t)blockIdx.x * kT;
-    const int nsl = (int)min((int64_t)kT, nnzd - base);
+    __shared__ int ss[kMaskSlots];
+    const int b = BC > 0 ? BC : b_arg, bb = b * b;
+    const int64_t base = (int64_t)blockIdx.x * kMaskSlots;
+    const int nsl = (int)min((int64_t)kMaskSlots, nnzd - base);
     if (threadIdx.x < nsl) {
         const int64_t s = base + threadIdx.x;
         ss[threadIdx.x] = find_in_row(rpS, colsS, rowsD[s], colsD[s]);
     }
     __syncthreads();
+#pragma unroll 4
     for (int e = threadIdx.x; e < nsl * bb; e += kT) {
         const int ls = e / bb, r = e - ls * bb;
         const int t = ss[ls];
-        dst[(base + ls) * bb + r] = (t >= 0) ? src[(int64_t)t * bb + r] : 0.0;
+        dst[base * bb + e] = (t >= 0) ? src[(int64_t)t * bb + r] : 0.0;
     }
 }
 
@@ -146,10 +202,21 @@ __global__ __launch_bounds__(kT) void k_fill_blocks(int64_t count, int b, const 
 
 }  // namespace
 
+// whether n elements of the arrays can be read in 16-byte pairs
+static bool pairs_of_16(int64_t n, const double *x, const double *y, const double *z)
+{
+    return n % 2 == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y) |
+                           reinterpret_cast<uintptr_t>(z)) % 16 == 0);
+}
+
 void axpby(Context *ctx, int64_t n, double alpha, const double *x, double beta, double *y)
 {
     if (n <= 0) return;
-    k_axpby<<<grid1(n), kT, 0, ctx->stream>>>(n, alpha, x, beta, y);
+    if (pairs_of_16(n, x, y, y))
+        k_axpby2<<<grid1((n / 2 + kUnroll - 1) / kUnroll), kT, 0, ctx->stream>>>(
+            n / 2, alpha, reinterpret_cast<const double2 *>(x), beta, reinterpret_cast<double2 *>(y));
+    else
+        k_axpby<<<grid1(n), kT, 0, ctx->stream>>>(n, alpha, x, beta, y);
     BSM_HIP_TRY(hipGetLastError());
 }
 
@@ -157,10 +224,9 @@ void axpbypcz(Context *ctx, int64_t n, double a, const double *x, double b, cons
               double *z)
 {
     if (n <= 0) return;
-    const bool paired = (n % 2 == 0) && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y) |
-                                          reinterpret_cast<uintptr_t>(z)) % 16 == 0);
+    const bool paired = pairs_of_16(n, x, y, z);
     if (paired)
-        k_axpbypcz2<<<grid1(n / 2), kT, 0, ctx->stream>>>(n / 2, a, reinterpret_cast<const double2 *>(x), b,
+        k_axpbypcz2<<<grid1((n / 2 + kUnroll - 1) / kUnroll), kT, 0, ctx->stream>>>(n / 2, a, reinterpret_cast<const double2 *>(x), b,
                                                           reinterpret_cast<const double2 *>(y), c,
                                                           reinterpret_cast<double2 *>(z));
     else
@@ -172,7 +238,10 @@ void symmetrize(Context *ctx, const bsm_pattern_s *P, double *M)
 {
     const int64_t n = nelems(P);
     if (n <= 0) return;
-    k_symmetrize<<<grid1(n), kT, 0, ctx->stream>>>(P->nnzb, P->b, P->tmap.as<int>(), M);
+    auto go = [&](auto kern) {
+        kern<<<grid1((n + kUnroll - 1) / kUnroll), kT, 0, ctx->stream>>>(P->nnzb, P->b, P->tmap.as<int>(), M);
+    };
+    P->b == 9 ? go(k_symmetrize<9>) : P->b == 4 ? go(k_symmetrize<4>) : go(k_symmetrize<0>);
     BSM_HIP_TRY(hipGetLastError());
 }
 
@@ -180,16 +249,22 @@ void add_transpose(Context *ctx, const bsm_pattern_s *P, double alpha, const dou
 {
     const int64_t n = nelems(P);
     if (n <= 0) return;
-    k_add_transpose<<<grid1(n), kT, 0, ctx->stream>>>(P->nnzb, P->b, P->tmap.as<int>(), alpha, M, beta, out);
+    auto go = [&](auto kern) {
+        kern<<<grid1(n), kT, 0, ctx->stream>>>(P->nnzb, P->b, P->tmap.as<int>(), alpha, M, beta, out);
+    };
+    P->b == 9 ? go(k_add_transpose<9>) : P->b == 4 ? go(k_add_transpose<4>) : go(k_add_transpose<0>);
     BSM_HIP_TRY(hipGetLastError());
 }
 
 void mask_copy(Context *ctx, const bsm_pattern_s *Ps, const double *src, const bsm_pattern_s *Pd, double *dst)
 {
     if (Pd->nnzb <= 0) return;
-    k_mask_copy<<<(unsigned)((Pd->nnzb + kT - 1) / kT), kT, 0, ctx->stream>>>(
-        Pd->nnzb, Pd->b, Pd->rowidx.as<int>(), Pd->cols.as<int>(), Ps->rowptr.as<int>(), Ps->cols.as<int>(), src,
-        dst);
+    auto go = [&](auto kern) {
+        kern<<<(unsigned)((Pd->nnzb + kMaskSlots - 1) / kMaskSlots), kT, 0, ctx->stream>>>(
+            Pd->nnzb, Pd->b, Pd->rowidx.as<int>(), Pd->cols.as<int>(), Ps->rowptr.as<int>(), Ps->cols.as<int>(), src,
+            dst);
+    };
+    Pd->b == 9 ? go(k_mask_copy<9>) : Pd->b == 4 ? go(k_mask_copy<4>) : go(k_mask_copy<0>);
     BSM_HIP_TRY(hipGetLastError());
 }
 

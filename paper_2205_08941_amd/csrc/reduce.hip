@@ -79,6 +79,7 @@ __global__ __launch_bounds__(kThreads) void k_trace_products(
         }
         __syncthreads();
         const int nel = nsl * bb;
+#pragma unroll 4
         for (int e = threadIdx.x; e < nel; e += kThreads) {
             const int ls = e / bb, r = e - ls * bb;
             const int p = r / b, q = r - p * b;
@@ -153,6 +154,7 @@ __global__ __launch_bounds__(kThreads) void k_dots(int count, int64_t nel, Ptrs 
     for (int n = 0; n < CNT; ++n) acc[n] = 0.0;
     const int64_t per = (nel + gridDim.x - 1) / gridDim.x;
     const int64_t lo = per * blockIdx.x, hi = min(nel, lo + per);
+#pragma unroll CNT == 1 ? 8 : 4
     for (int64_t e = lo + threadIdx.x; e < hi; e += kThreads) {
 #pragma unroll
         for (int n = 0; n < CNT; ++n)
@@ -177,69 +179,97 @@ __global__ __launch_bounds__(kThreads) void k_trace_single(int n, int b, const i
     block_reduce_store<1>(acc, 1, partials);
 }
 
-// ||M - I||_F^2 summed elementwise (the identity sits on the diagonal slots).
-__global__ __launch_bounds__(kThreads) void k_dist_identity(int64_t nnz, int b, const int *__restrict__ rows,
+// ||M - I||_F^2 summed elementwise (the identity sits on the diagonal slots).  BC: the block
+// size (0: b), I: the element index type, 32 bits where they reach: a 64-bit division by a
+// runtime block size and two dependent loads per element held the stream (1000 atoms, P14, 385 MB:
+// 200 -> 87 us).
+template <int BC, class I>
+__global__ __launch_bounds__(kThreads) void k_dist_identity(int64_t nnz, int b_arg, const int *__restrict__ rows,
                                                             const int *__restrict__ cols,
                                                             const double *__restrict__ M,
                                                             double *__restrict__ partials)
 {
     double acc[1] = {0.0};
+    const int b = BC > 0 ? BC : b_arg;
     const int bb = b * b;
     const int64_t nel = nnz * bb;
     const int64_t per = (nel + gridDim.x - 1) / gridDim.x;
     const int64_t lo = per * blockIdx.x, hi = min(nel, lo + per);
-    for (int64_t e = lo + threadIdx.x; e < hi; e += kThreads) {
-        const int64_t s = e / bb;
-        const int r = (int)(e - s * bb);
-        const bool one = rows[s] == cols[s] && (r / b) == (r % b);
-        const double v = M[e] - (one ? 1.0 : 0.0);
-        acc[0] = fma(v, v, acc[0]);
+    constexpr int U = 8;   // elements in flight per thread, added in order
+    for (int64_t x0 = lo + threadIdx.x; x0 < hi; x0 += U * kThreads) {
+        double v[U];
+        int ri[U], ci[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const I e = (I)min(x0 + u * kThreads, hi - 1);
+            const I s = e / (I)bb;
+            const int r = (int)(e - s * (I)bb), p = r / b;
+            v[u] = M[e];
+            ri[u] = rows[s];
+            ci[u] = cols[s] + (r == p * b + p ? 0 : 1 << 30);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double d = v[u] - (ri[u] == ci[u] ? 1.0 : 0.0);
+            if (x0 + u * kThreads < hi) acc[0] = fma(d, d, acc[0]);
+        }
     }
     block_reduce_store<1>(acc, 1, partials);
 }
 
-// Partial sums of every slot n added in workgroup order (one workgroup).
-__device__ inline void k_finish_body(int count, int nparts, const double *__restrict__ partials,
-                                     double *__restrict__ out)
+// Partial sums of slot n added in workgroup order, by one workgroup.
+__device__ inline void k_finish_body(int n, int nparts, const double *__restrict__ partials, double *__restrict__ out)
 {
     __shared__ double red[kThreads];
-    for (int n = 0; n < count; ++n) {
-        double v = 0.0;
-        const int per = (nparts + kThreads - 1) / kThreads;
-        const int lo = threadIdx.x * per, hi = min(nparts, lo + per);
-        for (int q = lo; q < hi; ++q) v += partials[(size_t)n * nparts + q];
-        red[threadIdx.x] = v;
-        __syncthreads();
-        for (int off = kThreads / 2; off > 0; off >>= 1) {
-            if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) out[n] = red[0];
+    double v = 0.0;
+    const int per = (nparts + kThreads - 1) / kThreads;
+    const int lo = threadIdx.x * per, hi = min(nparts, lo + per);
+    for (int q = lo; q < hi; ++q) v += partials[(size_t)n * nparts + q];
+    red[threadIdx.x] = v;
+    __syncthreads();
+    for (int off = kThreads / 2; off > 0; off >>= 1) {
+        if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
         __syncthreads();
     }
+    if (threadIdx.x == 0) out[n] = red[0];
 }
 
-__global__ __launch_bounds__(kThreads) void k_finish(int count, int nparts, const double *__restrict__ partials,
+// One workgroup per slot; `out` is the context's pinned host memory, read after the
+// stream is synchronised (no copy in between).
+__global__ __launch_bounds__(kThreads) void k_finish(int nparts, const double *__restrict__ partials,
                                                      double *__restrict__ out)
 {
-    k_finish_body(count, nparts, partials, out);
+    k_finish_body(blockIdx.x, nparts, partials, out);
 }
 
 // Largest absolute row sum (max over scalar rows of sum_j |A_ij|); max is
 // order-independent, so an integer atomicMax on the non-negative bit pattern is exact.
-__global__ void k_row_abs_max(int n, int b, const int *__restrict__ rowptr, const double *__restrict__ A,
-                              unsigned long long *__restrict__ out)
+// One workgroup per atom: all threads bring a run of its blocks to LDS, then thread p < b
+// adds scalar row p in slot and column order.  (One thread per scalar row straight from
+// memory left the chip waiting on its loads: 1000 atoms, P6, 145 -> 34 us.)
+constexpr int kRowStage = 2048;   // doubles of a run
+__global__ __launch_bounds__(kThreads) void k_row_abs_max(int b, const int *__restrict__ rowptr,
+                                                          const double *__restrict__ A,
+                                                          unsigned long long *__restrict__ out)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)n * b) return;
-    const int i = (int)(t / b), p = (int)(t - (int64_t)i * b);
+    __shared__ double run[kRowStage];
+    const int i = blockIdx.x, bb = b * b, per = kRowStage / bb;   // slots of a run
+    const int p = threadIdx.x;
     double s = 0.0;
-    for (int sl = rowptr[i]; sl < rowptr[i + 1]; ++sl) {
-        const double *blk = A + (int64_t)sl * b * b + p * b;
-        for (int q = 0; q < b; ++q) s += fabs(blk[q]);
+    for (int s0 = rowptr[i], s1 = rowptr[i + 1]; s0 < s1; s0 += per) {
+        const int ns = min(per, s1 - s0);
+        const double *src = A + (int64_t)s0 * bb;
+        for (int e = threadIdx.x; e < ns * bb; e += kThreads) run[e] = fabs(src[e]);
+        __syncthreads();
+        if (p < b)
+            for (int sl = 0; sl < ns; ++sl)
+                for (int q = 0; q < b; ++q) s += run[sl * bb + p * b + q];
+        __syncthreads();
     }
-    if (!(s >= 0.0)) s = __builtin_inf();   // NaN row: report as non-finite
-    atomicMax(out, (unsigned long long)__double_as_longlong(s));
+    if (p < b) {
+        if (!(s >= 0.0)) s = __builtin_inf();   // NaN row: report as non-finite
+        atomicMax(out, (unsigned long long)__double_as_longlong(s));
+    }
 }
 
 int grid_for(int64_t work)
@@ -251,10 +281,8 @@ int grid_for(int64_t work)
 void finish(Context *ctx, int count, int nparts, double *out)
 {
     hipStream_t st = ctx->stream;
-    double *dev_out = ctx->red_partials.as<double>() + (size_t)kRedSlots * kRedBlocks;
-    k_finish<<<1, kThreads, 0, st>>>(count, nparts, ctx->red_partials.as<double>(), dev_out);
+    k_finish<<<count, kThreads, 0, st>>>(nparts, ctx->red_partials.as<double>(), ctx->host_scalars);
     BSM_HIP_TRY(hipGetLastError());
-    BSM_HIP_TRY(hipMemcpyAsync(ctx->host_scalars, dev_out, sizeof(double) * count, hipMemcpyDeviceToHost, st));
     BSM_HIP_TRY(hipStreamSynchronize(st));
     for (int n = 0; n < count; ++n) out[n] = ctx->host_scalars[n];
 }
@@ -279,7 +307,7 @@ static double *g_scratch_ptr[kMaxDevices];   // device address of `scratch` per 
 __global__ __launch_bounds__(kThreads) void k_finish_to(int nparts, const double *__restrict__ partials,
                                                         double *__restrict__ out)
 {
-    k_finish_body(1, nparts, partials, out);
+    k_finish_body(0, nparts, partials, out);
 }
 
 void trace_products(Context *ctx, int count, const bsm_pattern_s *PA, const double *const *A,
@@ -427,8 +455,14 @@ double trace_single(Context *ctx, const bsm_pattern_s *P, const double *A)
 double dist_identity_sq(Context *ctx, const bsm_pattern_s *P, const double *A)
 {
     const int grid = grid_for(nelems(P));
-    k_dist_identity<<<grid, kThreads, 0, ctx->stream>>>(P->nnzb, P->b, P->rowidx.as<int>(), P->cols.as<int>(), A,
-                                                        ctx->red_partials.as<double>());
+    auto go = [&](auto kern) {
+        kern<<<grid, kThreads, 0, ctx->stream>>>(P->nnzb, P->b, P->rowidx.as<int>(), P->cols.as<int>(), A,
+                                                 ctx->red_partials.as<double>());
+    };
+    const bool small = nelems(P) < (int64_t)1 << 31;
+    if (P->b == 9) small ? go(k_dist_identity<9, unsigned>) : go(k_dist_identity<9, uint64_t>);
+    else if (P->b == 4) small ? go(k_dist_identity<4, unsigned>) : go(k_dist_identity<4, uint64_t>);
+    else small ? go(k_dist_identity<0, unsigned>) : go(k_dist_identity<0, uint64_t>);
     BSM_HIP_TRY(hipGetLastError());
     double out = 0.0;
     finish(ctx, 1, grid, &out);
@@ -441,8 +475,7 @@ double max_abs_row_sum(Context *ctx, const bsm_pattern_s *P, const double *A)
     unsigned long long *dv = reinterpret_cast<unsigned long long *>(ctx->red_partials.as<double>() +
                                                                     (size_t)kRedSlots * kRedBlocks + kRedSlots);
     BSM_HIP_TRY(hipMemsetAsync(dv, 0, sizeof(unsigned long long), st));
-    const int64_t rows = (int64_t)P->natoms * P->b;
-    k_row_abs_max<<<(unsigned)((rows + 255) / 256), 256, 0, st>>>(P->natoms, P->b, P->rowptr.as<int>(), A, dv);
+    k_row_abs_max<<<P->natoms, kThreads, 0, st>>>(P->b, P->rowptr.as<int>(), A, dv);
     BSM_HIP_TRY(hipGetLastError());
     BSM_HIP_TRY(hipMemcpyAsync(ctx->host_scalars, dv, sizeof(double), hipMemcpyDeviceToHost, st));
     BSM_HIP_TRY(hipStreamSynchronize(st));
