@@ -144,10 +144,12 @@ int bsm_ctx_set_rows_per_wave(bsm_ctx ctx, int rows);
  * FP64 products on the matrix cores (v_mfma_f64_16x16x4_f64, b = 9 only, other b
  * take 4; rows 4 or 8; direct plans; FP32 and BF16 products take 4), a measured
  * alternative that multiplies every block pair of its 16 x 16 tiles; -1 = default
- * (4 for b = 4 and 9, with 8 rows per tile, else 0).
- * Variants 1 to 4 multiply absent (k, j) blocks by zero instead of skipping
- * them, so a non-finite block of A can make other blocks of its output row
- * non-finite.  Clears cached plans (a bsm_batch made before keeps pointers to
+ * (4 for b = 4 and 9; for the other b from 5 to 16, while the operands fit buffer
+ * resources and no rows per wave are set, the rings of 4 in tiles of 2, 4 or 8 rows;
+ * else 0).
+ * Variants 1 to 4 with b = 4 and 9 multiply absent (k, j) blocks by zero instead of
+ * skipping them, so a non-finite block of A can make other blocks of its output row
+ * non-finite; with other b no kernel does.  Clears cached plans (a bsm_batch made before keeps pointers to
  * them: destroy batches first). */
 int bsm_ctx_set_product_variant(bsm_ctx ctx, int variant);
 /* Launch order of product tiles in plans built from now on: tiles of `span`
@@ -171,7 +173,7 @@ int bsm_ctx_set_group_span(bsm_ctx ctx, int span);
 int bsm_ctx_set_column_order(bsm_ctx ctx, int order);
 
 /* Transposed plans for the default product kernel (variant 4, 2, 4 or 8 rows per
- * tile, b = 4 or 9) when A and B lie on different patterns: the product is also
+ * tile, b = 4 or 9, and the other b's rings) when A and B lie on different patterns: the product is also
  * planned as C = (B^T A^T)^T, i.e. D = B^T A^T on P_C with blocks read transposed
  * and D's blocks stored transposed at the slots of (j, i) (patterns are
  * symmetric).  A wide A times a narrow B then walks the narrow pattern, leaving

@@ -23,6 +23,7 @@
 //     of row groups (neighbouring rows share A and B blocks in its L2).
 // No zero fill enters the flop count: 2 b^3 per triple (i, k, j) present.
 #include "bsm_internal.h"
+#include "product_any_b.h"
 #include "tiles.h"
 
 #include <algorithm>
@@ -719,6 +720,12 @@ void launch_b(hipStream_t st, const Plan *plan, const double *A, const double *B
             }
         }
     }
+    if constexpr (B >= 5 && B != 9) {
+        if (plan->variant == 4) {
+            launch_any_b(st, plan, A, Bm, C, alpha, beta, zblk, a_bytes, b_bytes);
+            return;
+        }
+    }
     if constexpr (B == 9 || B == 4) {
         if (plan->variant == 5) {   // LDS rings, tiles shared by two waves
             switch (plan->G) {
@@ -762,6 +769,12 @@ template <int B>
 void launch_b32(hipStream_t st, const Plan *plan, const float *A, const float *Bm, double *C, double alpha,
                 double beta, const float *zblk, int64_t a_bytes, int64_t b_bytes)
 {
+    if constexpr (B >= 5 && B != 9) {
+        if (plan->variant == 4) {
+            launch_any_b(st, plan, A, Bm, C, alpha, beta, zblk, a_bytes, b_bytes);
+            return;
+        }
+    }
     if constexpr (B == 9 || B == 4) {
         if (plan->variant == 5) {   // LDS rings, tiles shared by two waves, FP32 operands
             switch (plan->G) {
@@ -1392,7 +1405,7 @@ Plan *get_plan_kind(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B
     // different patterns (all patterns are symmetric): a wide A times a narrow B
     // then walks the narrow pattern, with far fewer idle lanes
     const bool try_t = allow_transposed && ctx->transposed_plans > 0 && variant == 4 && G <= 8 &&
-                       (C->b == 4 || C->b == 9) && A->id != B->id;
+                       (C->b == 4 || C->b == 9 || any_b_ring(C->b)) && A->id != B->id;
     auto key = std::make_tuple(A->id, B->id, C->id, variant, G, try_t ? 1 : 0, sets ? 1 : 0);
     auto it = ctx->plans.find(key);
     if (it != ctx->plans.end()) return it->second.get();
@@ -1406,7 +1419,13 @@ Plan *get_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, con
 {
     int variant = ctx->product_variant >= 0 ? ctx->product_variant : default_variant(C->b);
     if (variant == 6 && C->b != 9) variant = 4;   // the FP64 matrix-core tiles are for b = 9
-    if (variant >= 2 && C->b != 9 && C->b != 4) variant = 0;
+    // other b: the ring kernels of product_any_b.h by default, their row count and operands they
+    // can address; else the scalar-operand kernel (which any explicit variant from 2 on means too)
+    if (C->b != 9 && C->b != 4) {
+        if (ctx->product_variant < 0 && ctx->rows_per_wave == 0 && any_b_ring(C->b) && fits_buffers(A, B))
+            return get_plan_kind(ctx, A, B, C, 4, any_b_rows(C->b, tiles_of_8(ctx, C) < 1600), true);
+        if (variant >= 2) variant = 0;
+    }
     int G = variant == 2 ? kMaxRows : (ctx->rows_per_wave > 0 ? ctx->rows_per_wave : default_rows_per_wave(C->b));
     if ((variant == 4 || variant == 5 || variant == 6) && (C->b == 4 || C->b == 9) && ctx->rows_per_wave == 0)
         G = variant == 4 && !(prec == BSM_BF16 && C->b == 9 && A == B) ? ring_rows(ctx, C) : 8;

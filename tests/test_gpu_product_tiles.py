@@ -81,3 +81,34 @@ def test_packed_copies_need_no_alignment(bsm, ctx, offset):
     assert torch.equal(C.blocks, D.blocks)
     bsm.multiply_truncate_pair(1.0, moved[0], A, moved[1], 0.0, C, D)
     assert torch.equal(C.blocks, D.blocks)
+
+
+@pytest.mark.parametrize("b", [5, 6, 7, 8, 10, 11, 12, 13, 14, 15, 16])
+def test_ring_of_other_block_sizes(bsm, ctx, b):
+    """The ring kernels of the other block sizes against the scalar-operand kernel (variant 0),
+    which sums the same terms in the same order, and against the oracle; a non-finite A block
+    reaches exactly the output blocks of its own triples."""
+    import torch
+    cutoffs = (8.0, 6.0, 10.0)
+    g, o, host, (A, B) = operands(bsm, ctx, (2, 2, 3), b, cutoffs)
+    ref = O.Matrix(o[10.0], b, np.zeros((o[10.0].nnz, b, b)))
+    O.multiply_truncate(1.0, O.Matrix(o[8.0], b, host[0]), O.Matrix(o[6.0], b, host[1]), 0.0, ref)
+    A.blocks[A.blocks.shape[0] // 2, 0, b - 1] = float("inf")
+    A2 = bsm.Matrix(A.pattern, torch.tensor(host[0], device=ctx.device))
+    for prec in (bsm.F64, bsm.F32):
+        got = {}
+        for variant, tmode in ((0, 1), (-1, 0), (-1, 2)):
+            ctx.set_product_variant(variant)
+            ctx.set_transposed_plans(tmode)
+            print("other b", b, prec, variant, tmode, flush=True)
+            C, D = bsm.Matrix(g[10.0]), bsm.Matrix(g[10.0])
+            bsm.multiply_truncate_prec(prec, 1.0, A2, B, 0.0, C)
+            bsm.multiply_truncate_prec(prec, 1.0, A, B, 0.0, D)
+            got[(variant, tmode)] = (C.blocks.cpu().numpy(), D.blocks.cpu().numpy())
+        if prec == bsm.F64:
+            assert np.abs(got[(0, 1)][0] - ref.blocks).max() <= 1e-12 * np.abs(ref.blocks).max()
+        assert not np.isfinite(got[(0, 1)][1]).all()
+        for key in ((-1, 0), (-1, 2)):
+            assert np.array_equal(got[key][0], got[(0, 1)][0]), key
+            if key == (-1, 0):   # the direct plan has the scalar kernel's operand order
+                assert np.array_equal(got[key][1], got[(0, 1)][1], equal_nan=True), key
