@@ -5,11 +5,9 @@
 // correction of the Hotelling or LNV start (include/bsm_guess.h).  Its
 // workload is small next to the block products (about 58 kFLOP per pair per
 // forward pass), so the kernels aim at plain, deterministic data flow:
-//   - training: one fused kernel runs forward and backward for tiles of 32
-//     samples with all activations in LDS; every thread owns a fixed set of
-//     parameter-gradient entries in registers, so no atomics are needed; each
-//     workgroup writes its partial gradient once and a fixed-order reduction
-//     adds the partials;
+//   - training: tiles of 16 samples run forward and backward on the FP32 matrix
+//     cores, weight gradients are contractions over ranges of samples, and a
+//     fixed-order reduction adds the ranges (no atomics);
 //   - inference (BF16): each wavefront pushes 16 samples through the three
 //     layers with 16x16x16 BF16 MFMAs (FP32 accumulation), weights pre-packed
 //     into the per-lane operand layout, activations staged in LDS.
@@ -26,7 +24,6 @@ constexpr int kD = BSM_DESC_DIM;    // descriptor length
 constexpr int kH = BSM_MLP_WIDTH;   // hidden width
 constexpr int kTS = 32;             // samples per training tile
 constexpr int kNT = 256;            // threads per workgroup
-constexpr int kMaxParts = 256;      // workgroups of a gradient launch
 
 struct Offs {
     int64_t w1, b1, w2, b2, w3, b3, total;
@@ -205,33 +202,18 @@ __device__ inline double wave_sum(double x)
     return x;
 }
 
-// Forward (GRAD = false: outputs to `out`) or forward + backward (GRAD = true:
-// per-workgroup partial gradients and partial sums of squared residuals) over
-// samples 0..n-1; sample s is row idx[s] of X and T (row s when idx is NULL).
-// Thread t serves hidden / output unit o = t % 128 for samples of its half
-// (t / 128) of the tile, and owns the gradient entries (k, o) with
-// k = t / 128 + 2 r of every weight matrix: it alone reads and writes them in
-// its workgroup's partial-gradient row, so the row needs no atomics.
-template <bool GRAD>
+// Forward pass over samples 0..n-1: thread t serves hidden / output unit o = t % 128 for
+// samples of its half (t / 128) of a 32-sample tile.
 __global__ __launch_bounds__(kNT) void k_mlp_f32(const float *__restrict__ prm, int M, int64_t n,
-                                                 const float *__restrict__ X, const int *__restrict__ idx,
-                                                 const float *__restrict__ T, float inv_n, Out out,
-                                                 float *__restrict__ gpart, double *__restrict__ lpart)
+                                                 const float *__restrict__ X, Out out)
 {
     __shared__ float xs[kTS][kD];
     __shared__ float a1[kTS][kH];
-    __shared__ float a2[kTS][kH];   // h2; in the backward pass dz1
-    __shared__ float dy[kTS][kH];
-    __shared__ float dz[kTS][kH];   // dz2
-    __shared__ double lsum[kNT / 64];
+    __shared__ float a2[kTS][kH];
     const Offs of = offsets(M);
     const float *W1 = prm + of.w1, *B1 = prm + of.b1, *W2 = prm + of.w2, *B2 = prm + of.b2, *W3 = prm + of.w3,
                 *B3 = prm + of.b3;
     const int t = threadIdx.x, o = t & (kH - 1), half = t >> 7, sb = half * (kTS / 2);
-    float *g = GRAD ? gpart + (int64_t)blockIdx.x * of.total : nullptr;
-    bool first = true;   // the first tile of this workgroup stores, later tiles add
-    auto acc_to = [&](int64_t at, float v) { g[at] = first ? v : g[at] + v; };
-    double lacc = 0.0;
     const int64_t ntiles = (n + kTS - 1) / kTS;
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const int64_t s0 = tile * kTS;
@@ -240,8 +222,7 @@ __global__ __launch_bounds__(kNT) void k_mlp_f32(const float *__restrict__ prm, 
             const int s = e / kD, k = e % kD;
             float v = 0.f;
             if (s < cnt) {
-                const int64_t src = idx ? (int64_t)idx[s0 + s] : s0 + s;
-                v = X[src * kD + k];
+                v = X[(s0 + s) * kD + k];
             }
             xs[s][k] = v;
         }
@@ -286,140 +267,318 @@ __global__ __launch_bounds__(kNT) void k_mlp_f32(const float *__restrict__ prm, 
                 for (int s = 0; s < 16; ++s) acc[s] = fmaf(a2[sb + s][k], w, acc[s]);
             }
         }
-        if (!GRAD) {
-            if (o < M)
-                for (int s = 0; s < 16; ++s)
-                    if (sb + s < cnt) put(out, (s0 + sb + s) * M + o, acc[s]);
-            continue;   // the next tile's first barrier orders the LDS reuse
-        }
-        // ---- backward: dy = (y - t) / n
-        if (o < M) {
-#pragma unroll
-            for (int s = 0; s < 16; ++s) {
-                float r = 0.f;
-                if (sb + s < cnt) {
-                    const int64_t src = idx ? (int64_t)idx[s0 + sb + s] : s0 + sb + s;
-                    r = acc[s] - T[src * M + o];
-                }
-                lacc += (double)(r * r);
-                dy[sb + s][o] = r * inv_n;
-            }
-        }
-        __syncthreads();
-        // dz2 = (dy W3^T) (1 - h2^2) for hidden unit o
-#pragma unroll
-        for (int s = 0; s < 16; ++s) acc[s] = 0.f;
-#pragma unroll 4
-        for (int m = 0; m < M; ++m) {
-            const float w = W3[o * M + m];
-#pragma unroll
-            for (int s = 0; s < 16; ++s) acc[s] = fmaf(dy[sb + s][m], w, acc[s]);
-        }
-#pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            const float h = a2[sb + s][o];
-            dz[sb + s][o] = acc[s] * (1.f - h * h);
-        }
-        if (o < M) {   // dW3 = h2^T dy, db3 = sum dy
-            float col[kTS];
-#pragma unroll
-            for (int s = 0; s < kTS; ++s) col[s] = dy[s][o];
-            for (int r = 0; r < 64; ++r) {
-                const int k = half + 2 * r;
-                float sum = 0.f;
-#pragma unroll
-                for (int s = 0; s < kTS; ++s) sum = fmaf(a2[s][k], col[s], sum);
-                acc_to(of.w3 + (int64_t)k * M + o, sum);
-            }
-            if (half == 0) {
-                float sum = 0.f;
-                for (int s = 0; s < kTS; ++s) sum += col[s];
-                acc_to(of.b3 + o, sum);
-            }
-        }
-        __syncthreads();
-        {   // dW2 = h1^T dz2, db2 = sum dz2
-            float col[kTS];
-#pragma unroll
-            for (int s = 0; s < kTS; ++s) col[s] = dz[s][o];
-            for (int r = 0; r < 64; ++r) {
-                const int k = half + 2 * r;
-                float sum = 0.f;
-#pragma unroll
-                for (int s = 0; s < kTS; ++s) sum = fmaf(a1[s][k], col[s], sum);
-                acc_to(of.w2 + (int64_t)k * kH + o, sum);
-            }
-            if (half == 0) {
-                float sum = 0.f;
-                for (int s = 0; s < kTS; ++s) sum += col[s];
-                acc_to(of.b2 + o, sum);
-            }
-        }
-        // dz1 = (dz2 W2^T) (1 - h1^2) into a2 (h2 is no longer read)
-#pragma unroll
-        for (int s = 0; s < 16; ++s) acc[s] = 0.f;
-#pragma unroll 4
-        for (int m = 0; m < kH; ++m) {
-            const float w = W2[o * kH + m];
-#pragma unroll
-            for (int s = 0; s < 16; ++s) acc[s] = fmaf(dz[sb + s][m], w, acc[s]);
-        }
-#pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            const float h = a1[sb + s][o];
-            a2[sb + s][o] = acc[s] * (1.f - h * h);
-        }
-        __syncthreads();
-        {   // dW1 = x^T dz1, db1 = sum dz1
-            float col[kTS];
-#pragma unroll
-            for (int s = 0; s < kTS; ++s) col[s] = a2[s][o];
-            for (int r = 0; r < kD / 2; ++r) {
-                const int k = half + 2 * r;
-                float sum = 0.f;
-#pragma unroll
-                for (int s = 0; s < kTS; ++s) sum = fmaf(xs[s][k], col[s], sum);
-                acc_to(of.w1 + (int64_t)k * kH + o, sum);
-            }
-            if (half == 0) {
-                float sum = 0.f;
-                for (int s = 0; s < kTS; ++s) sum += col[s];
-                acc_to(of.b1 + o, sum);
-            }
-        }
-        first = false;
-        __syncthreads();
-    }
-    if (GRAD) {
-        lacc = wave_sum(lacc);
-        if ((t & 63) == 0) lsum[t >> 6] = lacc;
-        __syncthreads();
-        if (t == 0) {
-            double s = 0.0;
-            for (int w = 0; w < kNT / 64; ++w) s += lsum[w];
-            lpart[blockIdx.x] = s;
-        }
+        if (o < M)
+            for (int s = 0; s < 16; ++s)
+                if (sb + s < cnt) put(out, (s0 + sb + s) * M + o, acc[s]);
+        // the next tile's first barrier orders the LDS reuse
     }
 }
 
-// grad[p] = sum over parts w (ascending) of gpart[w][p]
-__global__ void k_sum_partials(int64_t P, int parts, const float *__restrict__ gpart, float *__restrict__ grad)
+// ------------------------------------------------------------------ FP32 gradients
+// A minibatch's gradient in three launches over FP32 matrix cores: k_mlp_backprop runs
+// tiles of 16 samples forward and backward and keeps every layer's activations and
+// errors (n x 600 floats, resident in L2), k_mlp_wgrad contracts them over the samples
+// into partial gradients of kSplits sample ranges, k_sum_gradient adds the partials in
+// order.  The former kernel did all of it in one pass of 32-sample tiles on the vector
+// units, with a shared-memory read per fused multiply-add and a gradient row of 31
+// thousand floats per workgroup to write and add up: 85 + 31 + 8 us (forward and backward,
+// sum of the rows, loss by one thread) for 4096 samples and 81 outputs, on 128 of the 256
+// CUs, and 152 us a call; these take 20 + 12 + 4, and the call 43.  The products need 5 us
+// at the FP32 matrix rate: what is left is five layers' latency, each a row of loads,
+// products, a tanh and a barrier, with one workgroup per CU, and the way of the
+// activations through memory to the second launch.
+constexpr int kGS = 16;            // samples of a tile
+constexpr int kGradChunk = 8192;   // samples whose activations are held at once
+constexpr int kSplits = 32;        // sample ranges of the weight gradients, at most
+constexpr int kPast = kH;          // floats k_mlp_backprop may read past the parameters (and drops)
+constexpr int kStep = 32;          // pairs of samples k_mlp_wgrad loads at once
+
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef float f32x16v __attribute__((ext_vector_type(16)));
+
+inline int pad32(int M) { return (M + 31) / 32 * 32; }
+
+// activations and errors of a chunk: rows of samples, padded to whole tiles (errors of
+// padding samples and of columns past M are zero)
+struct Acts {
+    float *h1, *h2, *d1, *d2, *dy;   // [chunk][kH] four times, [chunk][pad32(M)]
+};
+
+// Weights of U tiles of 16 units for K terms, in the order gemm16 uses them: lane l holds unit l % 16 of each
+// tile and the terms 16 j + 4 (l / 16) + i.  A layer's loads are all in flight at once, and the next layer's
+// are started before this one's products: one tile of samples per workgroup leaves nothing else to hide them.
+template <int K, int U> struct Weights {
+    float w[U][K / 4];
+    template <class F> __device__ void load(F at)
+    {
+        const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+        for (int k = 0; k < K / 4; ++k)
+#pragma unroll
+            for (int u = 0; u < U; ++u) w[u][k] = at(16 * (k / 4) + 4 * g + k % 4, u);
+    }
+    // from rows of n <= K terms at row(u), for products with a transposed matrix: four terms a load, the lanes
+    // being rows apart; terms past n are read (kPast floats past the last row at most) and set to zero
+    template <class F> __device__ void load_rows(int n, F row)
+    {
+        const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+        for (int j = 0; j < K / 16; ++j)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = 16 * j + 4 * g;
+                float4 x;   // rows of any length: no alignment past a float's
+                __builtin_memcpy(&x, row(u) + k, 16);
+                w[u][4 * j] = k < n ? x.x : 0.f;
+                w[u][4 * j + 1] = k + 1 < n ? x.y : 0.f;
+                w[u][4 * j + 2] = k + 2 < n ? x.z : 0.f;
+                w[u][4 * j + 3] = k + 3 < n ? x.w : 0.f;
+            }
+    }
+};
+
+// acc[u] (16 samples x 16 units of tile u) += in (LDS rows of `ld`) times w; lane l receives samples
+// 4 (l / 16) .. + 3 of unit l % 16
+template <int K, int U>
+__device__ inline void gemm16(const float *in, int ld, const Weights<K, U> &w, f32x4v (&acc)[U])
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int l = threadIdx.x & 63;
+    const float *a = in + (l & 15) * ld + 4 * (l >> 4);
+#pragma unroll
+    for (int j = 0; j < K / 16; ++j) {
+        const float4 x = *reinterpret_cast<const float4 *>(a + 16 * j);
+        const float v[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[i], w.w[u][4 * j + i], acc[u], 0, 0, 0);
+    }
+}
+
+__global__ __launch_bounds__(kNT, 1) void k_mlp_backprop(const float *__restrict__ prm, int M, int MP, int64_t n,
+                                                      const float *__restrict__ X, const int *__restrict__ idx,
+                                                      const float *__restrict__ T, float inv_n, Acts out, int add,
+                                                      double *__restrict__ lpart)
+{
+    constexpr int LH = kH + 4, LX = kD + 4;   // padded LDS rows
+    __shared__ __attribute__((aligned(16))) float xs[kGS * LX], h1[kGS * LH], h2[kGS * LH], dy[kGS * LH], dz[kGS * LH];
+    __shared__ double lsum[kNT / 64];
+    const Offs of = offsets(M);
+    const float *W1 = prm + of.w1, *B1 = prm + of.b1, *W2 = prm + of.w2, *B2 = prm + of.b2, *W3 = prm + of.w3,
+                *B3 = prm + of.b3;
+    const int t = threadIdx.x, w = t >> 6, l = t & 63, m = l & 15, g = l >> 4;
+    double lacc = 0.0;
+    const int64_t s0 = (int64_t)blockIdx.x * kGS;
+    const int cnt = (int)min((int64_t)kGS, n - s0);
+    for (int e = t; e < kGS * kD; e += kNT) {
+        const int s = e / kD, k = e % kD;
+        float v = 0.f;
+        if (s < cnt) v = X[(idx ? (int64_t)idx[s0 + s] : s0 + s) * kD + k];
+        xs[s * LX + k] = v;
+    }
+    // units of this wave: two tiles of a hidden layer, up to two of the outputs
+    const int o0 = 32 * w + m, y0 = 16 * w + m;
+    const bool in3[2] = {y0 < M, y0 + 64 < M};
+    float c1[2], c2[2], c3[2], target[2][4];
+    int64_t row[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t s = s0 + min(4 * g + i, cnt - 1);
+        row[i] = (idx ? (int64_t)idx[s] : s) * M;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int y = min(y0 + 64 * u, M - 1);   // units past M are dropped below
+        c1[u] = B1[o0 + 16 * u];
+        c2[u] = B2[o0 + 16 * u];
+        c3[u] = B3[y];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) target[u][i] = T[row[i] + y];
+    }
+    Weights<kD, 2> w1;
+    Weights<kH, 2> w2;
+    w1.load([&](int k, int u) { return W1[k * kH + o0 + 16 * u]; });
+    w2.load([&](int k, int u) { return W2[k * kH + o0 + 16 * u]; });
+    __syncthreads();
+    {   // h1 = tanh(x W1 + b1)
+        f32x4v a[2] = {{c1[0], c1[0], c1[0], c1[0]}, {c1[1], c1[1], c1[1], c1[1]}};
+        gemm16(xs, LX, w1, a);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float h = tanhf(a[u][i]);
+                h1[(4 * g + i) * LH + o0 + 16 * u] = h;
+                out.h1[(s0 + 4 * g + i) * kH + o0 + 16 * u] = h;
+            }
+    }
+    Weights<kH, 2> w3;
+    w3.load([&](int k, int u) {   // units past M: some other weight, set to zero
+        const float v = W3[k * M + y0 + 64 * u];
+        return in3[u] ? v : 0.f;
+    });
+    __syncthreads();
+    {   // h2 = tanh(h1 W2 + b2)
+        f32x4v a[2] = {{c2[0], c2[0], c2[0], c2[0]}, {c2[1], c2[1], c2[1], c2[1]}};
+        gemm16(h1, LH, w2, a);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float h = tanhf(a[u][i]);
+                h2[(4 * g + i) * LH + o0 + 16 * u] = h;
+                out.h2[(s0 + 4 * g + i) * kH + o0 + 16 * u] = h;
+            }
+    }
+    Weights<kH, 2> w3t;   // terms past M meet zero weights
+    w3t.load_rows(M, [&](int u) { return W3 + (o0 + 16 * u) * M; });
+    __syncthreads();
+    {   // y = h2 W3 + b3, dy = (y - t) / n
+        f32x4v a[2] = {{c3[0], c3[0], c3[0], c3[0]}, {c3[1], c3[1], c3[1], c3[1]}};
+        gemm16(h2, LH, w3, a);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int o = y0 + 64 * u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int s = 4 * g + i;
+                float r = 0.f;
+                if (in3[u] && s < cnt) r = a[u][i] - target[u][i];
+                lacc += (double)(r * r);
+                r *= inv_n;
+                dy[s * LH + o] = r;
+                if (o < MP) out.dy[(s0 + s) * MP + o] = r;
+            }
+        }
+    }
+    Weights<kH, 2> w2t;
+    w2t.load_rows(kH, [&](int u) { return W2 + (o0 + 16 * u) * kH; });
+    __syncthreads();
+    {   // d2 = (dy W3^T) (1 - h2^2)
+        f32x4v a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        gemm16(dy, LH, w3t, a);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int at = (4 * g + i) * LH + o0 + 16 * u;
+                const float h = h2[at], d = a[u][i] * (1.f - h * h);
+                dz[at] = d;
+                out.d2[(s0 + 4 * g + i) * kH + o0 + 16 * u] = d;
+            }
+    }
+    __syncthreads();
+    {   // d1 = (d2 W2^T) (1 - h1^2)
+        f32x4v a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        gemm16(dz, LH, w2t, a);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float h = h1[(4 * g + i) * LH + o0 + 16 * u];
+                out.d1[(s0 + 4 * g + i) * kH + o0 + 16 * u] = a[u][i] * (1.f - h * h);
+            }
+    }
+    lacc = wave_sum(lacc);
+    if (l == 0) lsum[w] = lacc;
+    __syncthreads();
+    if (t == 0) {
+        double s = add ? lpart[blockIdx.x] : 0.0;
+        for (int q = 0; q < kNT / 64; ++q) s += lsum[q];
+        lpart[blockIdx.x] = s;
+    }
+}
+
+// One wave per 32 x 32 tile of a weight matrix and range of samples: part[range][...] (+)= in^T err over the
+// range.  Tiles: 16 of W2, then 4 per 32 columns of W3, then 4 of W1; the tiles of the first input rows also
+// sum the errors' columns, the bias gradients.
+__global__ __launch_bounds__(64, 1) void k_mlp_wgrad(int M, int MP, int64_t n, const float *__restrict__ X,
+                                                  const int *__restrict__ idx, Acts in, int add,
+                                                  float *__restrict__ part)
+{
+    const Offs of = offsets(M);
+    const int l = threadIdx.x, c = l & 31, kk = l >> 5, n3 = MP / 32;
+    const int tile = blockIdx.x;
+    const int64_t np = (n + kGS - 1) / kGS * kGS;   // padded samples
+    const int64_t span = (np + gridDim.y * 2 - 1) / (gridDim.y * 2) * 2;
+    const int64_t lo = min(np, span * blockIdx.y), hi = min(np, lo + span);
+    float *out = part + of.total * blockIdx.y;
+    const float *A, *E;
+    int lda, lde, mt, nt, N, ldo;
+    int64_t wo, bo;
+    bool gather = false;
+    if (tile < 16) {
+        A = in.h1; lda = kH; E = in.d2; lde = kH; mt = tile >> 2; nt = tile & 3; N = kH; ldo = kH; wo = of.w2; bo = of.b2;
+    } else if (tile < 16 + 4 * n3) {
+        const int x = tile - 16;
+        A = in.h2; lda = kH; E = in.dy; lde = MP; mt = x / n3; nt = x % n3; N = M; ldo = M; wo = of.w3; bo = of.b3;
+    } else {
+        A = X; lda = kD; E = in.d1; lde = kH; mt = 0; nt = tile - 16 - 4 * n3; N = kH; ldo = kH; wo = of.w1; bo = of.b1;
+        gather = true;
+    }
+    const float *e = E + 32 * nt + c;
+    f32x16v acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    float bias = 0.f;
+    const float *a = A + 32 * mt + c;
+    for (int64_t s0 = lo; s0 < hi; s0 += 2 * kStep) {
+        float x[kStep], d[kStep];   // all loads of a step in flight; zeros past the range
+#pragma unroll
+        for (int u = 0; u < kStep; ++u) {
+            const int64_t r = s0 + 2 * u + kk;
+            const bool live = r < hi && (!gather || r < n);
+            const int64_t q = live ? r : 0, row = gather && idx ? (int64_t)idx[q] : q;
+            x[u] = a[row * lda];
+            d[u] = e[q * lde];
+            if (!live) x[u] = d[u] = 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kStep; ++u) {
+            bias += d[u];
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u], d[u], acc, 0, 0, 0);
+        }
+    }
+    const int o = 32 * nt + c;
+    if (o < N) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = 32 * mt + 8 * (i >> 2) + 4 * kk + (i & 3);
+            const int64_t at = wo + (int64_t)r * ldo + o;
+            out[at] = add ? out[at] + acc[i] : acc[i];
+        }
+    }
+    bias += __shfl_xor(bias, 32, 64);
+    if (mt == 0 && kk == 0 && o < N) out[bo + o] = add ? out[bo + o] + bias : bias;
+}
+
+// grad[p] = sum over parts w (ascending) of part[w][p]; the last workgroup: loss[0] (+)= scale * sum of the
+// loss parts, in a fixed tree.
+__global__ __launch_bounds__(256) void k_sum_gradient(int64_t P, int parts, const float *__restrict__ part,
+                                                      float *__restrict__ grad, int lparts,
+                                                      const double *__restrict__ lpart, double scale, int accumulate,
+                                                      double *__restrict__ loss)
+{
+    __shared__ double red[256];
+    if (blockIdx.x == gridDim.x - 1) {
+        double s = 0.0;
+        for (int w = threadIdx.x; w < lparts; w += 256) s += lpart[w];
+        red[threadIdx.x] = s;
+        __syncthreads();
+        for (int off = 128; off > 0; off >>= 1) {
+            if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) loss[0] = (accumulate ? loss[0] : 0.0) + scale * red[0];
+        return;
+    }
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (p >= P) return;
     float s = 0.f;
-    for (int w = 0; w < parts; ++w) s += gpart[(int64_t)w * P + p];
+#pragma unroll 8
+    for (int w = 0; w < parts; ++w) s += part[(int64_t)w * P + p];
     grad[p] = s;
-}
-
-// acc[0] (+)= scale * sum of the parts, in part order
-__global__ void k_sum_loss(int parts, const double *__restrict__ lpart, double scale, int accumulate,
-                           double *__restrict__ acc)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double s = 0.0;
-    for (int w = 0; w < parts; ++w) s += lpart[w];
-    acc[0] = (accumulate ? acc[0] : 0.0) + scale * s;
 }
 
 __global__ void k_adam(int64_t P, float *__restrict__ prm, float *__restrict__ m, float *__restrict__ v,
@@ -573,9 +732,15 @@ struct bsm_mlp_s {
     Context *c = nullptr;
     int M = 0;
     int64_t P = 0;
-    DevBuf prm, m, v, grad, gpart, lpart, loss, pk1, pk2, pk3;
+    DevBuf prm, m, v, grad, gpart, lpart, loss, acts, pk1, pk2, pk3;
+    double *host_loss = nullptr;   // pinned: the loss of a gradient call, written by its last kernel
     bool packed = false;
     int64_t t = 0;   // Adam steps taken
+
+    ~bsm_mlp_s()
+    {
+        if (host_loss) (void)hipHostFree(host_loss);
+    }
 
     int nt3() const { return (M + 15) / 16; }
 
@@ -602,8 +767,7 @@ struct bsm_mlp_s {
         if (precision == BSM_F32) {
             const int64_t tiles = (n + kTS - 1) / kTS;
             const unsigned grid = (unsigned)std::min<int64_t>(tiles, 4096);
-            k_mlp_f32<false><<<grid, kNT, 0, st>>>(prm.as<float>(), M, n, X, nullptr, nullptr, 0.f, out, nullptr,
-                                                    nullptr);
+            k_mlp_f32<<<grid, kNT, 0, st>>>(prm.as<float>(), M, n, X, out);
         } else {
             pack();
             const Offs of = offsets(M);
@@ -615,18 +779,34 @@ struct bsm_mlp_s {
         BSM_HIP_TRY(hipGetLastError());
     }
 
-    // gradient of the minibatch (n samples; rows idx[s] or s) into grad; the
-    // loss sum (times `scale`) into loss[0], added when `accumulate`
-    void loss_grad(int64_t n, const float *X, const int *idx, const float *T, double scale, int accumulate)
+    // gradient of the minibatch (n samples; rows idx[s] or s) into g; the loss sum (times `scale`)
+    // into *loss_out (device-visible), added when `accumulate`
+    void loss_grad(int64_t n, const float *X, const int *idx, const float *T, double scale, int accumulate, float *g,
+                   double *loss_out)
     {
         hipStream_t st = c->stream;
-        const int64_t tiles = (n + kTS - 1) / kTS;
-        const int parts = (int)std::min<int64_t>(tiles, kMaxParts);
-        k_mlp_f32<true><<<parts, kNT, 0, st>>>(prm.as<float>(), M, n, X, idx, T, (float)(1.0 / (double)n),
-                                                Out{nullptr, nullptr, 0.0, 0.0}, gpart.as<float>(),
-                                                lpart.as<double>());
-        k_sum_partials<<<grid_for(P, 256), 256, 0, st>>>(P, parts, gpart.as<float>(), grad.as<float>());
-        k_sum_loss<<<1, 64, 0, st>>>(parts, lpart.as<double>(), scale, accumulate, loss.as<double>());
+        const int MP = pad32(M);
+        float *x = acts.as<float>();
+        const Acts a{x, x + (int64_t)kGradChunk * kH, x + (int64_t)kGradChunk * 2 * kH, x + (int64_t)kGradChunk * 3 * kH,
+                     x + (int64_t)kGradChunk * 4 * kH};
+        int splits = 0, lparts = 0;
+        for (int64_t s0 = 0; s0 < n; s0 += kGradChunk) {
+            const int64_t cnt = std::min<int64_t>(kGradChunk, n - s0);
+            const int64_t tiles = (cnt + kGS - 1) / kGS;
+            // a first chunk is the largest: later ones leave its other parts as they are
+            if (s0 == 0) {
+                splits = (int)std::min<int64_t>(kSplits, (tiles + 3) / 4);
+                lparts = (int)tiles;
+            }
+            const float *Xc = idx ? X : X + s0 * kD, *Tc = idx ? T : T + s0 * M;
+            const int *ic = idx ? idx + s0 : nullptr;
+            k_mlp_backprop<<<(unsigned)tiles, kNT, 0, st>>>(prm.as<float>(), M, MP, cnt, Xc, ic, Tc, (float)(1.0 / (double)n), a,
+                                                 s0 > 0, lpart.as<double>());
+            k_mlp_wgrad<<<dim3(16 + 4 * (MP / 32) + 4, splits), 64, 0, st>>>(M, MP, cnt, Xc, ic, a, s0 > 0,
+                                                                             gpart.as<float>());
+        }
+        k_sum_gradient<<<grid_for(P, 256) + 1, 256, 0, st>>>(P, splits, gpart.as<float>(), g, lparts,
+                                                             lpart.as<double>(), scale, accumulate, loss_out);
         BSM_HIP_TRY(hipGetLastError());
     }
 
@@ -678,13 +858,15 @@ int bsm_mlp_create(bsm_ctx ctx, const bsm_mlp_shape *shape, const float *params,
     net->M = shape->out_dim;
     net->P = offsets(net->M).total;
     const size_t pb = sizeof(float) * (size_t)net->P;
-    net->prm = DevBuf(c, pb);
+    net->prm = DevBuf(c, pb + sizeof(float) * kPast);
     net->m = DevBuf(c, pb);
     net->v = DevBuf(c, pb);
     net->grad = DevBuf(c, pb);
-    net->gpart = DevBuf(c, pb * kMaxParts);
-    net->lpart = DevBuf(c, sizeof(double) * kMaxParts);
+    net->gpart = DevBuf(c, pb * kSplits);
+    net->lpart = DevBuf(c, sizeof(double) * (kGradChunk / kGS));
+    net->acts = DevBuf(c, sizeof(float) * (size_t)kGradChunk * (4 * kH + pad32(net->M)));
     net->loss = DevBuf(c, sizeof(double) * 2);
+    BSM_HIP_TRY(hipHostMalloc((void **)&net->host_loss, sizeof(double), hipHostMallocDefault));
     net->pk1 = DevBuf(c, sizeof(unsigned short) * kKT1 * 8 * 256);
     net->pk2 = DevBuf(c, sizeof(unsigned short) * 8 * 8 * 256);
     net->pk3 = DevBuf(c, sizeof(unsigned short) * 8 * (size_t)net->nt3() * 256);
@@ -771,12 +953,9 @@ int bsm_mlp_loss_grad(bsm_mlp net, int64_t n, const float *X, const float *T, do
 {
     MLP_TRY
     BSM_REQUIRE(net && X && T && grad && n >= 1, BSM_EINVAL, "bad argument");
-    net->loss_grad(n, X, nullptr, T, 0.5 / (double)n, 0);
-    BSM_HIP_TRY(hipMemcpyAsync(grad, net->grad.ptr, sizeof(float) * net->P, hipMemcpyDeviceToDevice, net->c->stream));
-    double h = 0.0;
-    BSM_HIP_TRY(hipMemcpyAsync(&h, net->loss.ptr, sizeof(double), hipMemcpyDeviceToHost, net->c->stream));
+    net->loss_grad(n, X, nullptr, T, 0.5 / (double)n, 0, grad, net->host_loss);
     BSM_HIP_TRY(hipStreamSynchronize(net->c->stream));
-    if (loss) *loss = h;
+    if (loss) *loss = *net->host_loss;
     return BSM_OK;
     MLP_CATCH
 }
@@ -803,9 +982,10 @@ int bsm_mlp_train(bsm_mlp net, const bsm_mlp_train_params *p, int64_t n, const f
             const int64_t s0 = k * p->batch, cnt = std::min<int64_t>(p->batch, n - s0);
             const double scale = 0.5 / (double)cnt / (double)nb;   // mean over minibatches
             if (perm)
-                net->loss_grad(cnt, X, perm + s0, T, scale, k > 0);
+                net->loss_grad(cnt, X, perm + s0, T, scale, k > 0, net->grad.as<float>(), net->loss.as<double>());
             else
-                net->loss_grad(cnt, X + s0 * kD, nullptr, T + s0 * net->M, scale, k > 0);
+                net->loss_grad(cnt, X + s0 * kD, nullptr, T + s0 * net->M, scale, k > 0, net->grad.as<float>(),
+                               net->loss.as<double>());
             net->adam(p->opt, net->grad.as<float>());
         }
         double h = 0.0;
