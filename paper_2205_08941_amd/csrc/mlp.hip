@@ -10,7 +10,7 @@
 //     fixed-order reduction adds the ranges (no atomics);
 //   - inference (BF16): each wavefront pushes 16 samples through the three
 //     layers with 16x16x16 BF16 MFMAs (FP32 accumulation), weights pre-packed
-//     into the per-lane operand layout, activations staged in LDS.
+//     into the per-lane operand layout and kept in LDS, activations in registers.
 #include "bsm_internal.h"
 #include "bsm_guess.h"
 
@@ -62,6 +62,13 @@ __device__ inline void put(const Out &out, int64_t at, float y)
 
 // ------------------------------------------------------------------ descriptors
 
+// orders a wavefront's own shared-memory accesses across its lanes
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ inline double dmul(double a, double b) { return __dmul_rn(a, b); }
 __device__ inline double dadd(double a, double b) { return __dadd_rn(a, b); }
 
@@ -87,39 +94,88 @@ constexpr double kBond0 = 2.3512589712747505;   // 5.43 sqrt(3) / 4 rounded to F
 // 16, 19) weighted by exp(-d / 1.5 A)
 constexpr double kRho0 = 2.751647885181917;
 
+constexpr int kFrameAtoms = 16;   // atoms of a workgroup
+constexpr int kFrameLanes = 16;   // lanes of an atom
+
 // Per atom (see the header): fr[24 i] = s, fr[24 i + 1 + 3 a + c] = e[a][c],
 // fr[24 i + 13 + a] = l[a], fr[24 i + 17 + c] = c_i[c], fr[24 i + 20] = rho_i (the
 // sum over the row's other atoms of exp(-d / 1.5 A), in column order).
-__global__ void k_atom_frames(int n, const double *__restrict__ pos, double3 box, const int *__restrict__ rowptr,
-                              const int *__restrict__ cols, double *__restrict__ fr, int *__restrict__ bad)
+// Sixteen lanes per atom, a neighbour each at a time: distances and exponentials side by side, the sum in column
+// order from LDS, and the nearest four by the rank of every neighbour among the sixteen and the four kept so far
+// (by distance, then index; empty places are (infinity, INT_MAX)).  4096 atoms, 6 A rows: 18 us, against
+// 107 with a thread for all of an atom's neighbours and 40 with one lane of an atom walking the list.
+__global__ __launch_bounds__(kFrameAtoms * kFrameLanes) void k_atom_frames(int n, const double *__restrict__ pos,
+                                                                           double3 box, const int *__restrict__ rowptr,
+                                                                           const int *__restrict__ cols,
+                                                                           double *__restrict__ fr,
+                                                                           int *__restrict__ bad)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double bd[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
-    int bj[4] = {INT_MAX, INT_MAX, INT_MAX, INT_MAX};
-    double bv[4][3] = {};
+    constexpr int L = kFrameLanes;
+    __shared__ double sd[kFrameAtoms][L + 4], sx[kFrameAtoms][L], sr[kFrameAtoms][4][3];   // the kept ones last
+    __shared__ int sj[kFrameAtoms][L + 4];
+    const int w = threadIdx.x / L, l = threadIdx.x % L;
+    const int i = blockIdx.x * kFrameAtoms + w;
+    if (i >= n) return;   // no workgroup barriers below
+    if (l < 4) {
+        sd[w][L + l] = INFINITY;
+        sj[w][L + l] = INT_MAX;
+        for (int c = 0; c < 3; ++c) sr[w][l][c] = 0.0;
+    }
     int found = 0;
     double rho = 0.0;
-    for (int s = rowptr[i]; s < rowptr[i + 1]; ++s) {
-        const int j = cols[s];
-        if (j == i) continue;
-        ++found;
-        double r[3];
-        min_image(pos, box, i, j, r);
-        const double d2 = norm2(r);
-        rho = dadd(rho, exp(-sqrt(d2) / 1.5));
-        // insert (d2, j) into the sorted best-four list
-        int at = 4;
-        while (at > 0 && (d2 < bd[at - 1] || (d2 == bd[at - 1] && j < bj[at - 1]))) --at;
-        if (at == 4) continue;
-        for (int q = 3; q > at; --q) {
-            bd[q] = bd[q - 1];
-            bj[q] = bj[q - 1];
-            for (int c = 0; c < 3; ++c) bv[q][c] = bv[q - 1][c];
+    const int end = rowptr[i + 1];
+    for (int s0 = rowptr[i]; s0 < end; s0 += L) {
+        double r[3] = {0.0, 0.0, 0.0}, d2 = INFINITY, x = 0.0;
+        int j = s0 + l < end ? cols[s0 + l] : i;
+        if (j != i) {
+            ++found;
+            min_image(pos, box, i, j, r);
+            d2 = norm2(r);
+            x = exp(-sqrt(d2) / 1.5);
         }
-        bd[at] = d2;
-        bj[at] = j;
-        for (int c = 0; c < 3; ++c) bv[at][c] = r[c];
+        if (j == i || !(d2 == d2)) {   // not a neighbour to choose
+            d2 = INFINITY;
+            j = INT_MAX;
+        }
+        wave_sync();   // the neighbours before have been read, the kept ones written
+        sd[w][l] = d2;
+        sj[w][l] = j;
+        sx[w][l] = x;
+        wave_sync();
+        // rank of this lane's neighbour, and in the first four lanes of a kept one
+        const double k2 = sd[w][L + (l & 3)];
+        const int kj = sj[w][L + (l & 3)];
+        double kr[3];
+        for (int c = 0; c < 3; ++c) kr[c] = sr[w][l & 3][c];
+        int rank = 0, krank = 0;
+#pragma unroll
+        for (int q = 0; q < L + 4; ++q) {
+            const double e2 = sd[w][q];
+            const int ej = sj[w][q];
+            rank += e2 < d2 || (e2 == d2 && ej < j);
+            krank += e2 < k2 || (e2 == k2 && ej < kj);
+            if (q < L) rho = dadd(rho, sx[w][q]);
+        }
+        wave_sync();   // all ranks known: the first four become the kept ones
+        if (j != INT_MAX && rank < 4) {
+            sd[w][L + rank] = d2;
+            sj[w][L + rank] = j;
+            for (int c = 0; c < 3; ++c) sr[w][rank][c] = r[c];
+        }
+        if (l < 4 && kj != INT_MAX && krank < 4) {
+            sd[w][L + krank] = k2;
+            sj[w][L + krank] = kj;
+            for (int c = 0; c < 3; ++c) sr[w][krank][c] = kr[c];
+        }
+    }
+    for (int off = L / 2; off > 0; off >>= 1) found += __shfl_xor(found, off, 64);
+    wave_sync();
+    if (l != 0) return;
+    double bd[4], bv[4][3];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        bd[q] = sd[w][L + q];
+        for (int c = 0; c < 3; ++c) bv[q][c] = sr[w][q][c];
     }
     if (found < 4) {
         *bad = 1;
@@ -158,12 +214,17 @@ __global__ void k_atom_frames(int n, const double *__restrict__ pos, double3 box
     f[20] = rho;
 }
 
-__global__ void k_pair_desc(int64_t nnz, const int *__restrict__ rowidx, const int *__restrict__ cols,
+constexpr int kDescSlots = 128;   // threads of k_pair_desc
+
+// A thread per slot; a workgroup's descriptors, contiguous in memory, go through LDS into whole lines (43 us
+// for 856 thousand slots, 110 MB written, against 54 with each thread storing its own 128 bytes).
+__global__ __launch_bounds__(kDescSlots) void k_pair_desc(int64_t nnz, const int *__restrict__ rowidx, const int *__restrict__ cols,
                             const double *__restrict__ pos, double3 box, double rc, const double *__restrict__ fr,
                             float *__restrict__ X)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nnz) return;
+    __shared__ float sv[kDescSlots][kD + 1];
+    const int64_t s0 = (int64_t)blockIdx.x * kDescSlots;
+    const int64_t s = min(s0 + threadIdx.x, nnz - 1);   // threads past the end repeat the last slot
     const int i = rowidx[s], j = cols[s];
     double r[3];
     min_image(pos, box, i, j, r);
@@ -190,8 +251,14 @@ __global__ void k_pair_desc(int64_t nnz, const int *__restrict__ rowidx, const i
     }
     v[30] = (float)(10.0 * (fi[20] - kRho0));
     v[31] = (float)(10.0 * (fj[20] - kRho0));
-    float4 *o = reinterpret_cast<float4 *>(X + (int64_t)kD * s);
-    for (int q = 0; q < kD / 4; ++q) o[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    for (int q = 0; q < kD; ++q) sv[threadIdx.x][q] = v[q];
+    __syncthreads();
+    float4 *o = reinterpret_cast<float4 *>(X + (int64_t)kD * s0);
+    const int cnt = (int)min((int64_t)kDescSlots, nnz - s0) * (kD / 4);
+    for (int e = threadIdx.x; e < cnt; e += kDescSlots) {
+        const float *q = &sv[e / (kD / 4)][e % (kD / 4) * 4];
+        o[e] = make_float4(q[0], q[1], q[2], q[3]);
+    }
 }
 
 // ------------------------------------------------------------------ FP32 network
@@ -599,14 +666,8 @@ __global__ void k_adam(int64_t P, float *__restrict__ prm, float *__restrict__ m
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// round to nearest even; NaN stays NaN, infinities stay infinite
-__device__ inline unsigned short bf16_bits(float f)
-{
-    unsigned u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (unsigned short)((u | ((u & 0x007fffffu) ? 0x00400000u : 0u)) >> 16);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
+// round to nearest even; NaN stays NaN, infinities stay infinite (one instruction for two)
+__device__ inline unsigned short bf16_bits(float f) { return __builtin_bit_cast(unsigned short, (__bf16)f); }
 
 // Pack a K x N input-major weight matrix into the B-operand layout of the
 // 16x16x16 BF16 MFMA: tile (kt, nt), lane l, element e holds
@@ -621,92 +682,119 @@ __global__ void k_pack_bf16(const float *__restrict__ W, int K, int N, int KT, i
     out[q] = (k < K && c < N) ? bf16_bits(W[(int64_t)k * N + c]) : (unsigned short)0;
 }
 
-constexpr int kHP = kH + 8;   // padded LDS row (bf16 elements)
-constexpr int kKT1 = kD / 16;  // k-steps of the first layer
+constexpr int kKT1 = kD / 16;        // k-steps of the first layer
+constexpr int kBW = 16;              // wavefronts of a workgroup
+constexpr int kBGrid = 256;          // workgroups, at most: one per CU
 
-// 4 wavefronts x 16 samples.  For the 16x16x16 MFMA, lane l supplies row
-// l % 16 of A (k = 4 (l / 16) .. + 3) and column l % 16 of B, and receives
-// rows 4 (l / 16) .. + 3 of column l % 16 of the result.
-__global__ __launch_bounds__(256) void k_mlp_bf16(const unsigned short *__restrict__ P1,
-                                                  const unsigned short *__restrict__ P2,
-                                                  const unsigned short *__restrict__ P3,
-                                                  const float *__restrict__ B1, const float *__restrict__ B2,
-                                                  const float *__restrict__ B3, int M, int NT3, int64_t n,
-                                                  const float *__restrict__ X, Out out)
+__device__ inline bf16x4 bf16_of(const f32x4 &v)
 {
-    __shared__ __align__(16) unsigned short h[4][16][kHP];
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
-    const int64_t base = ((int64_t)blockIdx.x * 4 + w) * 16;
-    unsigned short (*hw)[kHP] = h[w];
-    const bf16x4 *p1 = reinterpret_cast<const bf16x4 *>(P1);
-    const bf16x4 *p2 = reinterpret_cast<const bf16x4 *>(P2);
-    const bf16x4 *p3 = reinterpret_cast<const bf16x4 *>(P3);
-    // layer 1: K = kD (kKT1 steps of 16)
-    f32x4 acc[8];
+    bf16x4 r;
 #pragma unroll
-    for (int nt = 0; nt < 8; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < 4; ++e) r[e] = (short)bf16_bits(v[e]);
+    return r;
+}
+
+// acc[nt] = sum over kt of weights(kt, nt)^T act[kt], units by samples
+template <int KT, int NTl> __device__ inline void layer(const bf16x4 *p, const bf16x4 *act, f32x4 (&acc)[NTl])
+{
+    const int l = threadIdx.x & 63;
 #pragma unroll
-    for (int kt = 0; kt < kKT1; ++kt) {
-        bf16x4 a;
-        const int64_t s = base + m;
-        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (s < n) x = *reinterpret_cast<const float4 *>(X + s * kD + kt * 16 + 4 * kq);
-        a[0] = (short)bf16_bits(x.x);
-        a[1] = (short)bf16_bits(x.y);
-        a[2] = (short)bf16_bits(x.z);
-        a[3] = (short)bf16_bits(x.w);
+    for (int nt = 0; nt < NTl; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int nt = 0; nt < 8; ++nt)
-            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, p1[(kt * 8 + nt) * 64 + l], acc[nt], 0, 0, 0);
-    }
+    for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-    for (int nt = 0; nt < 8; ++nt) {
-        const float bb = B1[nt * 16 + m];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) hw[4 * kq + e][nt * 16 + m] = bf16_bits(tanhf(acc[nt][e] + bb));
+        for (int nt = 0; nt < NTl; ++nt)
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(p[(kt * NTl + nt) * 64 + l], act[kt], acc[nt], 0, 0, 0);
+}
+
+// One wavefront per tile of 16 samples, tiles in turn.  The layers are computed transposed, units by samples:
+// lane l receives units 4 (l / 16) .. + 3 of sample l % 16 of each 16 x 16 result, which after the tanh are
+// exactly the four terms it supplies to the next layer's products, so activations never leave the registers.
+// The weights of all layers (64 KB at 81 outputs) stay in LDS for all of a workgroup's tiles; a tile's outputs,
+// contiguous in memory, are turned through 8 rows of LDS into whole lines.  What bounds it is the vector work
+// of 256 tanh and roundings a sample.  The former kernel read every weight from memory per 16 samples into 340
+// registers, one wavefront per SIMD with little in flight, and kept activations in LDS: 1828 us for the 856
+// thousand blocks of 4096 atoms at 10 A, b = 9; this one 239 us.
+template <int NT3>
+__global__ __launch_bounds__(64 * kBW) void k_mlp_bf16(const unsigned short *__restrict__ P1,
+                                                       const unsigned short *__restrict__ P2,
+                                                       const unsigned short *__restrict__ P3,
+                                                       const float *__restrict__ B1, const float *__restrict__ B2,
+                                                       const float *__restrict__ B3, int M, int64_t n,
+                                                       const float *__restrict__ X, Out out)
+{
+    constexpr int N1 = kKT1 * 8 * 64, N2 = 8 * 8 * 64, N3 = 8 * NT3 * 64;   // fragments of four
+    __shared__ bf16x4 p[N1 + N2 + N3];
+    __shared__ __attribute__((aligned(16))) float bias[3 * kH];
+    __shared__ float stage[kBW][8 * 16 * NT3];
+    const int t = threadIdx.x, w = t >> 6, l = t & 63, m = l & 15, kq = l >> 4;
+    for (int e = t; e < N1; e += 64 * kBW) p[e] = reinterpret_cast<const bf16x4 *>(P1)[e];
+    for (int e = t; e < N2; e += 64 * kBW) p[N1 + e] = reinterpret_cast<const bf16x4 *>(P2)[e];
+    for (int e = t; e < N3; e += 64 * kBW) p[N1 + N2 + e] = reinterpret_cast<const bf16x4 *>(P3)[e];
+    if (t < kH) {
+        bias[t] = B1[t];
+        bias[kH + t] = B2[t];
+        bias[2 * kH + t] = t < M ? B3[t] : 0.f;
     }
     __syncthreads();
-    // layer 2: K = 128
+    const int64_t tiles = (n + 15) / 16, step = (int64_t)gridDim.x * kBW;
+    float *st = stage[w];
+    // wavefronts of different workgroups take neighbouring tiles, so that few tiles fill the chip
+    int64_t tile = blockIdx.x + (int64_t)w * gridDim.x;
+    f32x4 x[kKT1];
+    const auto fetch = [&](int64_t at) {
 #pragma unroll
-    for (int nt = 0; nt < 8; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int kt = 0; kt < kKT1; ++kt) {
+            x[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (at * 16 + m < n) x[kt] = *reinterpret_cast<const f32x4 *>(X + (at * 16 + m) * kD + kt * 16 + 4 * kq);
+        }
+    };
+    if (tile < tiles) fetch(tile);
+    for (; tile < tiles; tile += step) {
+        bf16x4 a[8];
 #pragma unroll
-    for (int kt = 0; kt < 8; ++kt) {
-        const bf16x4 av = *reinterpret_cast<const bf16x4 *>(&hw[m][kt * 16 + 4 * kq]);
+        for (int kt = 0; kt < kKT1; ++kt) a[kt] = bf16_of(x[kt]);
+        if (tile + step < tiles) fetch(tile + step);   // the next tile's inputs
+        f32x4 acc[8];
+        const auto activate = [&](const float *b) {
 #pragma unroll
-        for (int nt = 0; nt < 8; ++nt)
-            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, p2[(kt * 8 + nt) * 64 + l], acc[nt], 0, 0, 0);
-    }
-    __syncthreads();
+            for (int nt = 0; nt < 8; ++nt) {
+                const f32x4 c = *reinterpret_cast<const f32x4 *>(b + nt * 16 + 4 * kq);
 #pragma unroll
-    for (int nt = 0; nt < 8; ++nt) {
-        const float bb = B2[nt * 16 + m];
+                for (int e = 0; e < 4; ++e) acc[nt][e] = tanhf(acc[nt][e] + c[e]);
+                a[nt] = bf16_of(acc[nt]);
+            }
+        };
+        layer<kKT1, 8>(p, a, acc);
+        activate(bias);
+        layer<8, 8>(p + N1, a, acc);
+        activate(bias + kH);
+        f32x4 y[NT3];
+        layer<8, NT3>(p + N1 + N2, a, y);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) hw[4 * kq + e][nt * 16 + m] = bf16_bits(tanhf(acc[nt][e] + bb));
-    }
-    __syncthreads();
-    // layer 3: K = 128, N = M (NT3 tiles of 16)
+        for (int half = 0; half < 2; ++half) {
+            const int64_t s0 = tile * 16 + 8 * half;
+            wave_sync();   // the rows before have been read
+            if (m >> 3 == half)
 #pragma unroll
-    for (int nt = 0; nt < 8; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int nt = 0; nt < NT3; ++nt)
 #pragma unroll
-    for (int kt = 0; kt < 8; ++kt) {
-        const bf16x4 av = *reinterpret_cast<const bf16x4 *>(&hw[m][kt * 16 + 4 * kq]);
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt)
-            if (nt < NT3)
-                acc[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, p3[(kt * NT3 + nt) * 64 + l], acc[nt], 0, 0, 0);
-    }
-#pragma unroll
-    for (int nt = 0; nt < 8; ++nt) {
-        const int col = nt * 16 + m;
-        if (nt >= NT3 || col >= M) continue;
-        const float bb = B3[col];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int64_t s = base + 4 * kq + e;
-            if (s < n) put(out, s * M + col, acc[nt][e] + bb);
+                    for (int e = 0; e < 4; ++e) {
+                        const int col = nt * 16 + 4 * kq + e;
+                        if (col < M) st[(m & 7) * M + col] = y[nt][e] + bias[2 * kH + col];
+                    }
+            wave_sync();
+            const int cnt = (int)max((int64_t)0, min((int64_t)8, n - s0)) * M;
+            for (int e = l; e < cnt; e += 64) put(out, s0 * M + e, st[e]);
         }
     }
 }
+
+using Bf16Kernel = void (*)(const unsigned short *, const unsigned short *, const unsigned short *, const float *,
+                            const float *, const float *, int, int64_t, const float *, Out);
+// by the tiles of 16 outputs
+constexpr Bf16Kernel kMlpBf16[8] = {k_mlp_bf16<1>, k_mlp_bf16<2>, k_mlp_bf16<3>, k_mlp_bf16<4>,
+                                    k_mlp_bf16<5>, k_mlp_bf16<6>, k_mlp_bf16<7>, k_mlp_bf16<8>};
 
 __global__ void k_fill_f64(int64_t n, double v, double *__restrict__ x)
 {
@@ -772,9 +860,10 @@ struct bsm_mlp_s {
             pack();
             const Offs of = offsets(M);
             const float *p = prm.as<float>();
-            k_mlp_bf16<<<grid_for(n, 64), 256, 0, st>>>(pk1.as<unsigned short>(), pk2.as<unsigned short>(),
-                                                       pk3.as<unsigned short>(), p + of.b1, p + of.b2, p + of.b3, M,
-                                                       nt3(), n, X, out);
+            const unsigned grid = (unsigned)std::min<int64_t>((n + 15) / 16, kBGrid);
+            kMlpBf16[nt3() - 1]<<<grid, 64 * kBW, 0, st>>>(pk1.as<unsigned short>(), pk2.as<unsigned short>(),
+                                                           pk3.as<unsigned short>(), p + of.b1, p + of.b2, p + of.b3, M,
+                                                           n, X, out);
         }
         BSM_HIP_TRY(hipGetLastError());
     }
@@ -923,7 +1012,7 @@ int bsm_pair_descriptors(bsm_ctx ctx, bsm_pattern NP, bsm_pattern P, float *desc
     const double3 box = make_double3(P->box[0], P->box[1], P->box[2]);
     DevBuf fr(c, sizeof(double) * kFrame * (size_t)std::max(1, n)), bad(c, sizeof(int));
     BSM_HIP_TRY(hipMemsetAsync(bad.ptr, 0, sizeof(int), st));
-    k_atom_frames<<<grid_for(n, 128), 128, 0, st>>>(n, NP->pos.as<double>(), box, NP->rowptr.as<int>(),
+    k_atom_frames<<<grid_for(n, kFrameAtoms), kFrameAtoms * kFrameLanes, 0, st>>>(n, NP->pos.as<double>(), box, NP->rowptr.as<int>(),
                                                     NP->cols.as<int>(), fr.as<double>(), bad.as<int>());
     BSM_HIP_TRY(hipGetLastError());
     int hbad = 0;
@@ -931,7 +1020,7 @@ int bsm_pair_descriptors(bsm_ctx ctx, bsm_pattern NP, bsm_pattern P, float *desc
     BSM_HIP_TRY(hipStreamSynchronize(st));
     BSM_REQUIRE(!hbad, BSM_EINVAL, "an atom has fewer than four neighbours in the neighbour pattern");
     if (P->nnzb > 0)
-        k_pair_desc<<<grid_for(P->nnzb, 256), 256, 0, st>>>(P->nnzb, P->rowidx.as<int>(), P->cols.as<int>(),
+        k_pair_desc<<<grid_for(P->nnzb, kDescSlots), kDescSlots, 0, st>>>(P->nnzb, P->rowidx.as<int>(), P->cols.as<int>(),
                                                             P->pos.as<double>(), box, P->cutoff, fr.as<double>(),
                                                             desc);
     BSM_HIP_TRY(hipGetLastError());
