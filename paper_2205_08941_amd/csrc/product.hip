@@ -38,8 +38,9 @@ constexpr int kXcd = 8;       // MI355X: 8 XCDs, workgroups dealt round-robin
 constexpr int kWaves = 4;     // wavefronts (tiles) per workgroup
 constexpr int kMaxRows = 16;  // rows of a tile, at most
 // entries past a plan's last that the kernels' prefetch reads: the rings read the slots of entry
-// 2 D - 2 past the tile's last and up to 16 slots more than one entry's (D <= 4)
+// 2 D - 2 past the tile's last and up to 16 slots more than one entry's
 constexpr int kSpareEntries = 12;
+static_assert(kSpareEntries >= 2 * kMaxRingDepth + 3, "spare entries");
 constexpr int kPlanThreads = 256;   // threads of a planner workgroup
 
 __device__ inline int64_t logical_workgroup(int64_t nwg_padded)
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(256) void k_product_wg(
 }
 
 // One wave tile per one-wave workgroup, operands through a per-wave LDS ring
-// (CP: kPointerCopies, kBufferCopies with resources of a_bytes and b_bytes, kPackedCopies).
+// (CP: kPointerCopies, kPackedCopies; kBufferCopies, kPackedBuffers with resources of a_bytes and b_bytes).
 template <int B, int G, int D, class T = double, int CP = kPointerCopies, int W = 1, int TR = 0>
 __global__ __launch_bounds__(64 * W) void k_product_ring(
     int64_t ntiles, int64_t nwg_padded, const int *__restrict__ order, const int *__restrict__ hdr,
@@ -641,7 +642,7 @@ void launch_wg(hipStream_t st, const Plan *plan, const double *A, const double *
                                                          plan->ent.as<int>(), A, Bm, C, alpha, beta);
 }
 
-// Packed copies read 16 bytes at a time.
+// Packed copies read 16 bytes at a time; through buffer resources where both operands fit one.
 inline bool aligned16(const void *a, const void *b, const void *c = nullptr)
 {
     return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | reinterpret_cast<uintptr_t>(c)) & 15) == 0;
@@ -660,7 +661,10 @@ void launch_ring_t(hipStream_t st, const Plan *plan, const T *A, const T *Bm, do
     };
     if constexpr (B == 4 && W == 1 && D == 2) {
         if (plan->variant == 4 && aligned16(A, Bm)) {
-            go(k_product_ring<B, G, kPackedDepth, T, kPackedCopies, W, TR>, false);
+            if (a_bytes <= (int64_t)kBufMaxBytes && b_bytes <= (int64_t)kBufMaxBytes)
+                go(k_product_ring<B, G, kPackedDepth, T, kPackedBuffers, W, TR>, true);
+            else
+                go(k_product_ring<B, G, kPackedDepth, T, kPackedCopies, W, TR>, false);
             return;
         }
     }
@@ -1169,7 +1173,8 @@ void launch_pair_g(hipStream_t st, const Plan *plan, const double *A, const doub
     };
     if constexpr (B == 4) {
         if (aligned16(A, A2, Bm)) {
-            go(k_product_ring_pair<B, G, kPackedDepth, kPackedCopies, TR>, false);
+            if (buf) go(k_product_ring_pair<B, G, kPackedDepth, kPackedBuffers, TR>, true);
+            else go(k_product_ring_pair<B, G, kPackedDepth, kPackedCopies, TR>, false);
             return;
         }
     }

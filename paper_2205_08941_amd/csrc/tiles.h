@@ -682,10 +682,16 @@ __device__ inline void dma_block_buf(__amdgpu_buffer_rsrc_t rs, unsigned vo, lds
 // How a ring copies its blocks: 64-bit addresses or buffer resources, 4 bytes per
 // lane and one block per load; or, where a block is a multiple of 16 bytes that
 // divides a load (b = 4), 16 bytes per lane and 64 / lanes-per-block blocks per load.
-// The last needs operands at 16-byte boundaries.  An entry of an 8-row tile takes 3
+// The packed copies need operands at 16-byte boundaries.  An entry of an 8-row tile takes 3
 // such loads instead of 24: b = 4, 8 rows, 1000 atoms, 14 A x 8 A -> 8 A 175 -> 137 us,
-// 216 atoms, 16 A 184 -> 156 us; 4096 atoms, 16 A, held by the bytes, 10.7 -> 10.5 ms.
-enum { kPointerCopies = 0, kBufferCopies = 1, kPackedCopies = 2 };
+// 216 atoms, 16 A 184 -> 156 us; 4096 atoms, 16 A, 10.7 -> 10.5 ms.  Through buffer
+// resources, a load per operand and one multiply-add per load instead of the 64-bit
+// addresses and selects of every lane, which then took most of an entry's time: the same
+// three 137 -> 100 us, 156 -> 73 us, 10.5 -> 8.95 ms, and 64 atoms, 16 A, 2 rows, 19.7 -> 16.5 us.
+// (A deeper ring gives these last nothing: 20.3 and 20.6 us at depths 8 and 6.)
+enum { kPointerCopies = 0, kBufferCopies = 1, kPackedCopies = 2, kPackedBuffers = 3 };
+
+constexpr int kMaxRingDepth = 4;   // entries of a ring, at most
 
 // Largest operand (bytes) the buffer copies address: absent-block offsets
 // (2^32 - block bytes and up) must lie past it.
@@ -694,7 +700,7 @@ constexpr unsigned kBufMaxBytes = 0xfffff000u;
 // T = double: FP64 product.  T = float: operands already rounded (FP32, or BF16
 // stored as FP32), FP32 fused multiply-adds in the same (k, m) order, the sums
 // widened to FP64 for alpha, beta and the store.
-// CP: how blocks are copied (above).  kBufferCopies: through raw buffer resources
+// CP: how blocks are copied (above).  kBufferCopies and kPackedBuffers: through raw buffer resources
 // over A and B (a_bytes, b_bytes, each at most kBufMaxBytes), one vector add per
 // block instead of 64-bit address arithmetic and a zero-block select.
 // W = 2: the tile has 2 JT columns and two waves of one workgroup share it,
@@ -735,13 +741,18 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
     constexpr int HS = GP + GP * JT * W;
     constexpr int ES = (GP + JT) * W;
     constexpr int NS = GP + JT;                // plan slots per entry and wave
-    constexpr bool PK = CP == kPackedCopies;
+    constexpr bool PB = CP == kPackedBuffers, PK = CP == kPackedCopies || PB;
     constexpr int NB = RE::kBlocks, DW = RE::kDwords, IPB = RE::kInstPerBlock;
-    constexpr int LPB = RE::kLanesPerBlock, BPI = RE::kBlocksPerInst, NP = RE::kPackedInst;
+    constexpr int LPB = RE::kLanesPerBlock, BPI = RE::kBlocksPerInst;
+    // packed loads of a step: over the blocks in a row, or (buffers) one of A's rows, for DU = 2 one of A2's
+    // with the same slots, and B's columns; NP: vectors of slots, one per load and operand
+    constexpr int NP = PB ? 1 + (JT + (BPI > 0 ? BPI : 1) - 1) / (BPI > 0 ? BPI : 1) : RE::kPackedInst;
+    constexpr int NPL = PB ? NP + DU - 1 : NP;
+    static_assert(!PB || GP <= BPI, "a load per operand's rows");
     static_assert(!PK || (BB * ESZ % 16 == 0 && LPB > 0 && 64 % (LPB > 0 ? LPB : 1) == 0 && NS <= 64), "packed copies");
     constexpr int NV = (NS + 15) / 16;         // vectors of 16 slots (one of all slots when packed)
     constexpr int NL = PK ? 1 : NV;            // DMA loads of an entry's slots
-    constexpr int NI = (PK ? NP : RE::kInst) + NL;   // DMA loads of a step
+    constexpr int NI = (PK ? NPL : RE::kInst) + NL;   // DMA loads of a step
     constexpr int NR = PK ? NP + 1 : NV;       // registers of an entry's slots
     // other b than 4 and 9 multiply no absent block, not even a non-finite A by zero
     constexpr bool SAFE = B != 4 && B != 9;
@@ -782,7 +793,10 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
     int at[NR];
 #pragma unroll
     for (int v = 0; v < NR; ++v) {
-        if constexpr (PK) {
+        if constexpr (PB) {
+            const int blk = lane / LPB;
+            at[v] = v == NP ? min(lane, NS - 1) : (v == 0 ? min(blk, GP - 1) : GP + min((v - 1) * BPI + blk, JT - 1));
+        } else if constexpr (PK) {
             const int blk = v * BPI + lane / LPB;
             at[v] = v == NP ? min(lane, NS - 1) : (blk < G ? blk % GP : min(GP + (blk - G), NS - 1));
         } else {
@@ -790,9 +804,9 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
         }
     }
     // packed copies: where a lane's operand begins, at the lane's place in a block
-    uint64_t from[PK ? NP : 1];
+    uint64_t from[PK && !PB ? NP : 1];
     const uint64_t zero = (uint64_t)zblk + (PK ? 16 * (lane % (LPB > 0 ? LPB : 1)) : 0);
-    if constexpr (PK) {
+    if constexpr (PK && !PB) {
         const uint64_t pa = (uint64_t)vA, pa2 = (uint64_t)(DU == 2 ? vA2 : vA), pb = (uint64_t)vB;
 #pragma unroll
         for (int v = 0; v < NP; ++v) {
@@ -820,7 +834,20 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
     // the same slots of A2), then B columns.  `gone`: bit s is set where slot s is absent.
     auto issue = [&](auto P, int q, const int (&sl)[NR], unsigned &gone) {
         lds_char_t *slot = ring + decltype(P)::value * RE::kStep;
-        if constexpr (PK) {
+        if constexpr (PB) {
+            gone = (unsigned)__ballot(sl[NP] < 0);
+            const auto copy = [&](const __amdgpu_buffer_rsrc_t &rs, int v, int first, int blocks) {
+                // absent blocks: offsets past the resource, as below
+                const unsigned vo = (unsigned)sl[v] * (unsigned)(BB * ESZ) + (unsigned)(16 * (lane % LPB));
+                if (blocks >= BPI || lane < blocks * LPB)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t *)(slot + first * (BB * ESZ)), 16, vo, 0, 0,
+                                                             0);
+            };
+            copy(rsA, 0, 0, GP);
+            if constexpr (DU == 2) copy(rsA2, 0, GP, GP);
+#pragma unroll
+            for (int v = 1; v < NP; ++v) copy(rsB, v, G + (v - 1) * BPI, JT - (v - 1) * BPI);
+        } else if constexpr (PK) {
             gone = (unsigned)__ballot(sl[NP] < 0);
 #pragma unroll
             for (int v = 0; v < NP; ++v) {
@@ -920,7 +947,7 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
             }
         }
     };
-    static_assert(D >= 2 && D <= 4, "ring depth 2 to 4");
+    static_assert(D >= 2 && D <= kMaxRingDepth, "ring depth");
 
     // Every step copies the entry D - 1 ahead, also past the tile's end (the
     // next tile's entries or the plan's spare entries: in bounds, never
@@ -936,8 +963,9 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
 #pragma unroll
         for (int d = 0; d < D; ++d) load_slots(d, first[d]);
         issue(std::integral_constant<int, 0>{}, 0, first[0], gone[0]);
-        if constexpr (D >= 3) issue(std::integral_constant<int, 1>{}, 1, first[1], gone[1]);
-        if constexpr (D >= 4) issue(std::integral_constant<int, 2>{}, 2, first[2], gone[2]);
+        slot_blocks([&](auto I) { issue(std::integral_constant<int, decltype(I)::value + 1>{}, decltype(I)::value + 1,
+                                        first[decltype(I)::value + 1], gone[decltype(I)::value + 1]); },
+                    std::make_integer_sequence<int, D - 2>{});
 #pragma unroll
         for (int v = 0; v < NR; ++v) next[v] = first[D - 1][v];
     }
@@ -954,10 +982,7 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
             read_slots(R, next);
             compute(R, gone[r]);
         };
-        step(std::integral_constant<int, 0>{});
-        step(std::integral_constant<int, 1>{});
-        if constexpr (D >= 3) step(std::integral_constant<int, 2>{});
-        if constexpr (D >= 4) step(std::integral_constant<int, 3>{});
+        slot_blocks(step, std::make_integer_sequence<int, D>{});
     }
     wait_vmcnt<0>();
 #pragma unroll
