@@ -100,42 +100,56 @@ __global__ void k_cell_scatter(int n, const int *__restrict__ cell, const int *_
     cellatoms[cellstart[c] + atomicAdd(&cellfill[c], 1)] = i;
 }
 
-// One thread per atom: visit the neighbour cells, count (mode 0) or write
-// (mode 1) the columns j with d^2 < r^2 (and j == i).
+constexpr int kRowsPerGroup = 4;   // atoms (wavefronts) of a workgroup
+
+// One wavefront per atom: visit the neighbour cells, a lane per atom of a cell, and count
+// (mode 0) or write (mode 1) the columns j with d^2 < r^2 (and j == i); the rows are sorted
+// afterwards.  A thread per atom walked its cells alone, a chain of dependent loads and
+// divisions: 78 and 96 us for 216 atoms at 8 A, 415 and 452 for 4096 at 10 A, against 6 and 6, 26 and 27.
 template <int MODE>
-__global__ void k_neighbors(int n, const double *__restrict__ pos, Grid g, double r2,
-                            const int *__restrict__ cell, const int *__restrict__ cellstart,
-                            const int *__restrict__ cellatoms, int *__restrict__ rowcount,
-                            const int *__restrict__ rowptr, int *__restrict__ cols)
+__global__ __launch_bounds__(64 * kRowsPerGroup) void k_neighbors(int n, const double *__restrict__ pos, Grid g,
+                                                                  double r2, const int *__restrict__ cell,
+                                                                  const int *__restrict__ cellstart,
+                                                                  const int *__restrict__ cellatoms,
+                                                                  int *__restrict__ rowcount,
+                                                                  const int *__restrict__ rowptr,
+                                                                  int *__restrict__ cols)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * kRowsPerGroup + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= n) return;
     int c = cell[i];
     int cz = c % g.nc[2], cy = (c / g.nc[2]) % g.nc[1], cx = c / (g.nc[2] * g.nc[1]);
     int cnt = 0;
-    int w = (MODE == 1) ? rowptr[i] : 0;
+    int *row = (MODE == 1) ? cols + rowptr[i] : nullptr;
+    // the atoms of the cells along z follow each other where the cells do: z cells as one or two runs
+    const int first = (g.noff[2] == 3) ? cz - 1 : cz, last = first + g.noff[2];   // [first, last), wrapped
     for (int ox = 0; ox < g.noff[0]; ++ox) {
         int ax = (g.noff[0] == 3) ? cx + ox - 1 : cx + ox;
         ax = ((ax % g.nc[0]) + g.nc[0]) % g.nc[0];
         for (int oy = 0; oy < g.noff[1]; ++oy) {
             int ay = (g.noff[1] == 3) ? cy + oy - 1 : cy + oy;
             ay = ((ay % g.nc[1]) + g.nc[1]) % g.nc[1];
-            for (int oz = 0; oz < g.noff[2]; ++oz) {
-                int az = (g.noff[2] == 3) ? cz + oz - 1 : cz + oz;
-                az = ((az % g.nc[2]) + g.nc[2]) % g.nc[2];
-                int cc = (ax * g.nc[1] + ay) * g.nc[2] + az;
-                for (int q = cellstart[cc]; q < cellstart[cc + 1]; ++q) {
-                    int j = cellatoms[q];
-                    if (j == i || min_image_d2(pos, g.box[0], g.box[1], g.box[2], i, j) < r2) {
-                        if (MODE == 1) cols[w] = j;
-                        ++w;
-                        ++cnt;
-                    }
+            const int base = (ax * g.nc[1] + ay) * g.nc[2];
+            const int lo = max(first, 0), hi = min(last, g.nc[2]);
+            const int q0 = cellstart[base + lo], n0 = cellstart[base + hi] - q0;
+            // what wraps: below 0 the top cells, past the end the bottom ones (never both: noff <= nc)
+            const int wl = first < 0 ? g.nc[2] + first : 0, wh = first < 0 ? g.nc[2] : last - hi;
+            const int q1 = cellstart[base + wl], n1 = cellstart[base + wh] - q1;
+            for (int x0 = 0; x0 < n0 + n1; x0 += 64) {
+                const int x = x0 + lane;
+                bool near = false;
+                int j = 0;
+                if (x < n0 + n1) {
+                    j = cellatoms[x < n0 ? q0 + x : q1 + (x - n0)];
+                    near = j == i || min_image_d2(pos, g.box[0], g.box[1], g.box[2], i, j) < r2;
                 }
+                const unsigned long long m = __ballot(near);
+                if (MODE == 1 && near) row[cnt + __popcll(m & ((1ull << lane) - 1ull))] = j;
+                cnt += __popcll(m);
             }
         }
     }
-    if (MODE == 0) rowcount[i] = cnt;
+    if (MODE == 0 && lane == 0) rowcount[i] = cnt;
 }
 
 // One workgroup per row: bitonic sort of the row's columns in LDS.
@@ -195,7 +209,7 @@ __global__ void k_tmap(int64_t nnz, const int *__restrict__ rowptr, const int *_
     if (s >= nnz) return;
     int t = find_in_row(rowptr, cols, cols[s], rowidx[s]);
     tmap[s] = t;
-    if (t < 0) atomicOr(bad, 1);
+    if (t < 0) *bad = 1;   // pinned host memory
 }
 
 __global__ void k_diag(int n, const int *__restrict__ rowptr, const int *__restrict__ cols,
@@ -205,10 +219,20 @@ __global__ void k_diag(int n, const int *__restrict__ rowptr, const int *__restr
     if (i < n) diag[i] = find_in_row(rowptr, cols, i, i);
 }
 
-__global__ void k_max_row(int n, const int *__restrict__ rowptr, int *__restrict__ mx)
+// One workgroup: what the host needs to go on, in pinned memory: flags 0 .. 4, the longest
+// row in place 2, and the number of slots in place 5.
+__global__ __launch_bounds__(1024) void k_row_info(int n, const int *__restrict__ rowptr, const int *__restrict__ fl,
+                                                   int *host)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) atomicMax(mx, rowptr[i + 1] - rowptr[i]);
+    __shared__ int longest;
+    if (threadIdx.x == 0) longest = 0;
+    __syncthreads();
+    int m = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) m = max(m, rowptr[i + 1] - rowptr[i]);
+    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(&longest, m);
+    __syncthreads();
+    if (threadIdx.x < 6) host[threadIdx.x] = threadIdx.x == 2 ? longest : threadIdx.x == 5 ? rowptr[n] : fl[threadIdx.x];
 }
 
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
@@ -263,18 +287,17 @@ bsm_pattern_s *make_pattern(Context *ctx, int natoms, int b, const double *pos_d
     k_cell_scatter<<<blocks_for(natoms, 256), 256, 0, st>>>(natoms, cell.as<int>(), cellstart.as<int>(),
                                                               cellfill.as<int>(), cellatoms.as<int>());
     double r2 = cutoff * cutoff;
-    k_neighbors<0><<<blocks_for(natoms, 128), 128, 0, st>>>(natoms, p->pos.as<double>(), g, r2,
+    k_neighbors<0><<<blocks_for(natoms, kRowsPerGroup), 64 * kRowsPerGroup, 0, st>>>(natoms, p->pos.as<double>(), g, r2,
                                                             cell.as<int>(), cellstart.as<int>(),
                                                             cellatoms.as<int>(), rowcount.as<int>(),
                                                             nullptr, nullptr);
     p->rowptr = DevBuf(ctx, sizeof(int) * (natoms + 1));
     k_scan<<<1, 1024, 0, st>>>(natoms, rowcount.as<int>(), p->rowptr.as<int>(), fl + 1);
-    k_max_row<<<blocks_for(natoms, 256), 256, 0, st>>>(natoms, p->rowptr.as<int>(), fl + 2);
-    int hostv[5] = {0, 0, 0, 0, 0};
-    int total = 0;
-    BSM_HIP_TRY(hipMemcpyAsync(hostv, fl, sizeof(int) * 5, hipMemcpyDeviceToHost, st));
-    BSM_HIP_TRY(hipMemcpyAsync(&total, p->rowptr.as<int>() + natoms, sizeof(int), hipMemcpyDeviceToHost, st));
+    int *hostv = reinterpret_cast<int *>(ctx->host_scalars);
+    k_row_info<<<1, 1024, 0, st>>>(natoms, p->rowptr.as<int>(), fl, hostv);
+    BSM_HIP_TRY(hipGetLastError());
     BSM_HIP_TRY(hipStreamSynchronize(st));
+    const int total = hostv[5];
     BSM_REQUIRE(hostv[4] == 0, BSM_EINVAL, "positions are not finite");
     BSM_REQUIRE(hostv[1] == 0, BSM_EINVAL, "pattern has more than 2^31-1 blocks");
     BSM_REQUIRE(hostv[2] <= kMaxRow, BSM_EINVAL, "a pattern row is longer than 8192 blocks");
@@ -282,7 +305,7 @@ bsm_pattern_s *make_pattern(Context *ctx, int natoms, int b, const double *pos_d
     p->max_row = hostv[2];
 
     p->cols = DevBuf(ctx, sizeof(int) * (size_t)total);
-    k_neighbors<1><<<blocks_for(natoms, 128), 128, 0, st>>>(natoms, p->pos.as<double>(), g, r2,
+    k_neighbors<1><<<blocks_for(natoms, kRowsPerGroup), 64 * kRowsPerGroup, 0, st>>>(natoms, p->pos.as<double>(), g, r2,
                                                             cell.as<int>(), cellstart.as<int>(),
                                                             cellatoms.as<int>(), nullptr,
                                                             p->rowptr.as<int>(), p->cols.as<int>());
@@ -292,14 +315,14 @@ bsm_pattern_s *make_pattern(Context *ctx, int natoms, int b, const double *pos_d
     k_rows_of_slots<<<natoms, 64, 0, st>>>(natoms, p->rowptr.as<int>(), p->rowidx.as<int>());
     p->tmap = DevBuf(ctx, sizeof(int) * (size_t)total);
     p->diag = DevBuf(ctx, sizeof(int) * natoms);
+    hostv[0] = 0;
     k_tmap<<<blocks_for(total, 256), 256, 0, st>>>(total, p->rowptr.as<int>(), p->cols.as<int>(),
-                                                   p->rowidx.as<int>(), p->tmap.as<int>(), fl + 3);
+                                                   p->rowidx.as<int>(), p->tmap.as<int>(), hostv);
     k_diag<<<blocks_for(natoms, 256), 256, 0, st>>>(natoms, p->rowptr.as<int>(), p->cols.as<int>(),
                                                     p->diag.as<int>());
-    int bad = 0;
-    BSM_HIP_TRY(hipMemcpyAsync(&bad, fl + 3, sizeof(int), hipMemcpyDeviceToHost, st));
+    BSM_HIP_TRY(hipGetLastError());
     BSM_HIP_TRY(hipStreamSynchronize(st));
-    BSM_REQUIRE(bad == 0, BSM_EINVAL, "pattern is not symmetric (non-finite positions?)");
+    BSM_REQUIRE(hostv[0] == 0, BSM_EINVAL, "pattern is not symmetric (non-finite positions?)");
     return p.release();
 }
 

@@ -213,6 +213,7 @@ __global__ __launch_bounds__(64) void k_product_mfma_bf16(
 // a launch's workgroups in rows of gridDim.x (its threads along x must stay below 2^32)
 __device__ inline int64_t plan_item() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 __device__ inline void plan_sync() { __syncthreads(); }
+__device__ inline int plan_place(int64_t item);   // where an item's totals go
 __device__ inline void plan_or(unsigned *p, unsigned v) { atomicOr(p, v); }
 __device__ inline void plan_or(unsigned long long *p, unsigned long long v) { atomicOr(p, v); }
 // exclusive sum over the workgroup's threads, and the total; every thread calls it
@@ -242,6 +243,7 @@ __device__ inline unsigned plan_scan(unsigned v, unsigned &total)
 constexpr int kPlanThreads = 1;
 inline int64_t plan_item() { return blockIdx.x; }
 inline void plan_sync() {}
+inline int plan_place(int64_t) { return 0; }
 inline void plan_or(unsigned *p, unsigned v) { *p |= v; }
 inline void plan_or(unsigned long long *p, unsigned long long v) { *p |= v; }
 inline unsigned plan_scan(unsigned v, unsigned &total)
@@ -251,6 +253,9 @@ inline unsigned plan_scan(unsigned v, unsigned &total)
 }
 #endif
 
+// Tiles add their triples and rows to one of kTotalLanes places, a cache line each: one place for all
+// took the atomics of thousands of tiles in turn (k_tile_entries<0>, 216 atoms, b = 9: 70 -> 15 us).
+constexpr int kTotalLanes = 64, kTotalStride = 16;
 constexpr int kUnionWords = 4096;   // bit words of a column window (131072 atoms)
 constexpr int kEntryWindow = 1024;  // atoms k of an entry window
 
@@ -545,8 +550,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_entries(
         plan_scan(rw, srw);
         if (tid == 0) {
             nent[tc] = scnt;
-            atomicAdd(triples, (unsigned long long)stri);   // integers: order-independent
-            atomicAdd(rowwork, (unsigned long long)srw);
+            atomicAdd(triples + plan_place(tc), (unsigned long long)stri);   // integers: order-independent
+            atomicAdd(rowwork + plan_place(tc), (unsigned long long)srw);
         }
     }
 }
@@ -580,7 +585,8 @@ __global__ void k_map_cslots(int64_t ntiles, int G, int jt, const int *__restric
         if (h[x] >= 0) h[x] = tmC[h[x]];
 }
 
-__global__ __launch_bounds__(1024) void k_scan64(int64_t n, const int64_t *__restrict__ in, int64_t *__restrict__ out)
+__global__ __launch_bounds__(1024) void k_scan64(int64_t n, const int64_t *__restrict__ in, int64_t *__restrict__ out,
+                                                 int64_t *host)   // host: also the total, in pinned memory
 {
     __shared__ long long part[1024];
     const int t = threadIdx.x, nt = blockDim.x;
@@ -601,7 +607,22 @@ __global__ __launch_bounds__(1024) void k_scan64(int64_t n, const int64_t *__res
         out[k] = run;
         run += in[k];
     }
-    if (t == nt - 1) out[n] = part[t];
+    if (t == nt - 1) {
+        out[n] = part[t];
+        if (host) *host = part[t];
+    }
+}
+
+__device__ inline int plan_place(int64_t item) { return (int)(item & (kTotalLanes - 1)) * kTotalStride; }
+
+// One wave: the sums of the places (triples, then rows multiplied) to pinned memory.
+__global__ __launch_bounds__(kTotalLanes) void k_plan_totals(const unsigned long long *__restrict__ totals,
+                                                             unsigned long long *host)
+{
+    unsigned long long v[2] = {totals[threadIdx.x * kTotalStride], totals[threadIdx.x * kTotalStride + 1]};
+    for (int off = kTotalLanes / 2; off > 0; off >>= 1)
+        for (int k = 0; k < 2; ++k) v[k] += __shfl_xor(v[k], off, kTotalLanes);
+    if (threadIdx.x < 2) host[threadIdx.x] = v[threadIdx.x];
 }
 
 __global__ void k_int_to_i64(int n, const int *__restrict__ in, int64_t *__restrict__ out)
@@ -859,7 +880,8 @@ constexpr float kClusterRow = 20.0f;
 // Counted on 4096 atoms, b = 9: 16 A x 16 A -> 16 A 13% fewer entries and 6% fewer rows
 // multiplied, 8 A x 10 A -> 18 A 12% and 12%, 10 A x 6 A -> 16 A 11% and 10%.
 // hdr and tcols hold the row-set order (k_group_tiles) and are rewritten; scr as there.
-// Ties go to the lower column, so the tiles do not depend on timing.
+// Ties go to the lower column, so the tiles do not depend on timing.  A serial chain of picks, each a minimum
+// over the wave: by DPP moves instead of shuffles 101 -> 78 us for 216 atoms.
 __global__ __launch_bounds__(64) void k_cluster_tiles(int n, int G, int jt, const double *__restrict__ pos, double bx,
                                                       double by, double bz, const int64_t *__restrict__ toff,
                                                       int64_t ntiles, int *__restrict__ hdr, int *__restrict__ tcols,
@@ -907,9 +929,18 @@ __global__ __launch_bounds__(64) void k_cluster_tiles(int n, int G, int jt, cons
     // integer minimum gives the nearest (distances are told apart to 1 part in 4096, then by column).
     auto pack = [](float d, int u) { return (__float_as_uint(d) & ~(unsigned)(kClusterCols - 1)) | (unsigned)u; };
     constexpr unsigned kNone = 0xffffffffu;
-    auto least = [&](unsigned v) {   // over the wave
-        for (int off = 1; off < 64; off <<= 1) v = min(v, (unsigned)__shfl_xor((int)v, off, 64));
-        return v;
+    auto least = [&](unsigned v) {   // over the wave: within rows of 16, then across them, to the last lane
+        const auto with = [&](auto C, auto R) {
+            v = min(v, (unsigned)__builtin_amdgcn_update_dpp((int)kNone, (int)v, decltype(C)::value, decltype(R)::value,
+                                                             0xf, false));
+        };
+        with(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});   // row_shr 1, 2, 4, 8
+        with(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+        with(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+        with(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+        with(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast 15, 31
+        with(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+        return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
     };
     for (int t = 0; t < nt; ++t) {
         unsigned best = kNone;
@@ -972,10 +1003,10 @@ void make_tiles(Context *ctx, const bsm_pattern_s *PC, int G, int waves, bool cl
     ts.toff = DevBuf(ctx, sizeof(int64_t) * (ng + 1));
     k_group_union<<<ng, kPlanThreads, 0, st>>>(n, G, PC->rowptr.as<int>(), PC->cols.as<int>(), jt, ts.ntile.as<int>());
     k_int_to_i64<<<(ng + 255) / 256, 256, 0, st>>>(ng, ts.ntile.as<int>(), ts.ntile64.as<int64_t>());
-    k_scan64<<<1, 1024, 0, st>>>(ng, ts.ntile64.as<int64_t>(), ts.toff.as<int64_t>());
-    BSM_HIP_TRY(hipMemcpyAsync(&ts.nt, ts.toff.as<int64_t>() + ng, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars);   // counts come back in pinned memory
+    k_scan64<<<1, 1024, 0, st>>>(ng, ts.ntile64.as<int64_t>(), ts.toff.as<int64_t>(), host);
     BSM_HIP_TRY(hipStreamSynchronize(st));
-    const int64_t nt = ts.nt;
+    const int64_t nt = ts.nt = *host;
     BSM_REQUIRE(nt < (int64_t)INT32_MAX, BSM_EINVAL, "too many product tiles");
     ts.hdr = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt * (G + G * jt)));
     ts.tcols = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt * jt));
@@ -1006,24 +1037,28 @@ void count_entries(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *P
     plan->ntiles = nt;
     plan->transposed = transposed;
     plan->ebeg = DevBuf(ctx, sizeof(int64_t) * (size_t)(nt + 1));
-    BSM_HIP_TRY(hipMemsetAsync(plan->ebeg.ptr, 0, sizeof(int64_t) * (size_t)(nt + 1), st));
+    if (nt == 0) BSM_HIP_TRY(hipMemsetAsync(plan->ebeg.ptr, 0, sizeof(int64_t), st));
     if (nt > 0) {
         ec.nent = DevBuf(ctx, sizeof(int64_t) * (size_t)nt);
-        ec.totals = DevBuf(ctx, 2 * sizeof(unsigned long long));
+        const size_t places = sizeof(unsigned long long) * kTotalLanes * kTotalStride;
+        ec.totals = DevBuf(ctx, places);
         ec.ebeg = DevBuf(ctx, sizeof(int64_t) * (size_t)(nt + 1));
         unsigned long long *tri = ec.totals.as<unsigned long long>();
-        BSM_HIP_TRY(hipMemsetAsync(tri, 0, 2 * sizeof(unsigned long long), st));
+        BSM_HIP_TRY(hipMemsetAsync(tri, 0, places, st));
         k_tile_entries<0><<<tile_grid(nt), kPlanThreads, 0, st>>>(
             nt, 1, PA->natoms, ts.G, ts.jt, ts.waves, transposed, ts.hdr.as<int>(), ts.tcols.as<int>(),
             PA->rowptr.as<int>(), PA->cols.as<int>(), PA->tmap.as<int>(), PB->rowptr.as<int>(), PB->cols.as<int>(),
             PB->tmap.as<int>(), ec.nent.as<int64_t>(), tri, tri + 1, nullptr, nullptr);
         k_pad_counts<<<(unsigned)((nt + 127) / 128), 128, 0, st>>>(nt, 1, ec.nent.as<int64_t>());
-        k_scan64<<<1, 1024, 0, st>>>(nt, ec.nent.as<int64_t>(), ec.ebeg.as<int64_t>());
+        int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars);
+        k_plan_totals<<<1, kTotalLanes, 0, st>>>(tri, reinterpret_cast<unsigned long long *>(host) + 1);
+        k_scan64<<<1, 1024, 0, st>>>(nt, ec.nent.as<int64_t>(), ec.ebeg.as<int64_t>(), host);
         k_tile_ebeg<<<(unsigned)((nt + 1 + 127) / 128), 128, 0, st>>>(nt, 1, ec.ebeg.as<int64_t>(),
                                                                       plan->ebeg.as<int64_t>());
-        BSM_HIP_TRY(hipMemcpyAsync(&ec.ne, ec.ebeg.as<int64_t>() + nt, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        BSM_HIP_TRY(hipMemcpyAsync(ec.ntri, tri, sizeof(ec.ntri), hipMemcpyDeviceToHost, st));
         BSM_HIP_TRY(hipStreamSynchronize(st));
+        ec.ne = host[0];
+        ec.ntri[0] = (unsigned long long)host[1];
+        ec.ntri[1] = (unsigned long long)host[2];
     }
     plan->nentries = ec.ne;
     plan->triples = (int64_t)ec.ntri[0];
@@ -1102,11 +1137,10 @@ static int64_t tiles_of_8(Context *ctx, const bsm_pattern_s *PC)
     k_group_union<<<ng, kPlanThreads, 0, st>>>(PC->natoms, 8, PC->rowptr.as<int>(), PC->cols.as<int>(), 64 / PC->b,
                                                ntile.as<int>());
     k_int_to_i64<<<(ng + 255) / 256, 256, 0, st>>>(ng, ntile.as<int>(), ntile64.as<int64_t>());
-    k_scan64<<<1, 1024, 0, st>>>(ng, ntile64.as<int64_t>(), toff.as<int64_t>());
-    int64_t nt = 0;
-    BSM_HIP_TRY(hipMemcpyAsync(&nt, toff.as<int64_t>() + ng, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars);
+    k_scan64<<<1, 1024, 0, st>>>(ng, ntile64.as<int64_t>(), toff.as<int64_t>(), host);
     BSM_HIP_TRY(hipStreamSynchronize(st));
-    return PC->tiles8 = nt;
+    return PC->tiles8 = *host;
 }
 
 // Rows per tile of the ring kernels (b = 4 and 9).  8-row tiles copy the fewest blocks per
