@@ -190,7 +190,7 @@ int bsm_ctx_create(int device, void *hip_stream, bsm_alloc_fn alloc, bsm_free_fn
     c->c.err_flag = DevBuf(&c->c, 256);
     c->c.zero_block = DevBuf(&c->c, sizeof(double) * 256);
     BSM_HIP_TRY(hipMemset(c->c.zero_block.ptr, 0, sizeof(double) * 256));
-    BSM_HIP_TRY(hipHostMalloc((void **)&c->c.host_scalars, sizeof(double) * 64, hipHostMallocDefault));
+    BSM_HIP_TRY(hipHostMalloc((void **)&c->c.host_scalars, sizeof(double) * kHostScalars, hipHostMallocDefault));
     trace_scratch_setup(device);   // the allocation-free trace's scratch on this device
     *out = c.release();
     return BSM_OK;

@@ -99,7 +99,7 @@ class Context {
     DevBuf red_partials;        // double[kRedBlocks * kRedSlots]
     DevBuf err_flag;            // int
     DevBuf zero_block;          // 16 x 16 FP64 zeros (absent B blocks in the DPP product)
-    double *host_scalars = nullptr;  // pinned host, kRedSlots doubles
+    double *host_scalars = nullptr;  // pinned host, kHostScalars doubles
     // product timing (bsm_ctx_set_profiling)
     struct ProfRec {
         const Plan *plan;
@@ -138,6 +138,9 @@ class Context {
 };
 
 static constexpr int kRedBlocks = 1024;   // fixed grid for deterministic reductions
+// host_scalars: results of reductions first, then counts of plans and patterns (a plan may be built
+// between a reduction and its read-back)
+static constexpr int kHostScalars = 64, kHostCounts = 48;
 static constexpr int kRedSlots = 16;      // traces computed by one fused launch, at most
 
 }  // namespace bsm
@@ -214,9 +217,53 @@ void trace_products(Context *ctx, int count, const bsm_pattern_s *PA, const doub
 // (each loaded once): kTracesEnergy, A = {X, W}, B = {Y, X}: Tr XY, Tr WY,
 // Tr XX, Tr WX; kTracesLineSearch, A = {X_D, X, M1, W, Q}, B = {Y, Y_D, X_D, X}:
 // the 15 traces of the line-search polynomials.  Same bits as trace_products.
+// (kTracesLineSearch takes W1 = (X + X_D)^2 for M1 and forms M1 = W1 - W - Q as it reads.)
 enum { kTracesEnergy = 0, kTracesLineSearch = 1 };
 void trace_set(Context *ctx, int kind, const bsm_pattern_s *P, const double *const *A, const double *const *B,
                double *out);
+// The same without a synchronisation: the traces go to sc[0 ..] on the device and to
+// host_scalars[host ..], valid once the stream is synchronised.
+void trace_set_to(Context *ctx, int kind, const bsm_pattern_s *P, const double *const *A, const double *const *B,
+                  double *sc, int host);
+void dots_to(Context *ctx, int count, const bsm_pattern_s *P, const double *const *A, const double *const *B,
+             double *sc, int host);
+
+// One conjugate-gradient step of the LNV solver without a round trip to the host: the scalars stay
+// on the device (and go to host_scalars at the same places), each formed by the host's expressions.
+enum CgScalar {
+    kCgEnergy = 0,       // the 4 energy traces
+    kCgGnPn = 4,         // <G_N, P_N>, <G_N, P_E>
+    kCgDen = 6,          // <g_prev, Mg_prev>, <g, Mg - Mg_prev>
+    kCgGd = 8,           // <g, D>, <G_N, D>, <G_N, Mg> with D = -Mg + beta D_prev
+    kCgLine = 11,        // the 15 line-search traces
+    kCgMin = 26,         // the step, the N correction, 0 (or 1: no minimum)
+    kCgScalars = 29
+};
+static_assert(kCgScalars <= kHostCounts, "places of host_scalars");
+struct CgState {
+    const double *GE, *GN, *PE, *PN, *gprev, *Mgprev, *Dprev;
+    double *g, *Mg, *D;
+    double *sc;          // device, kCgScalars doubles
+    double mu;           // of the grand-canonical mode, or where no mu can be had
+    int canonical;       // mode
+    int use_prev;        // beta from the previous step, else 0
+};
+// Chemical potential and beta from the scalars (beta before the descent test of kCgGd).
+__host__ __device__ inline bool cg_canonical(const double *sc, int mode) { return mode && sc[kCgGnPn] > 0.0; }
+__host__ __device__ inline double cg_mu(const double *sc, int mode, double mu)
+{
+    return cg_canonical(sc, mode) ? sc[kCgGnPn + 1] / sc[kCgGnPn] : mu;
+}
+__host__ __device__ inline double cg_beta(const double *sc, int use_prev)
+{
+    const double q = use_prev ? sc[kCgDen + 1] / sc[kCgDen] : 0.0;
+    return 0.0 < q ? q : 0.0;
+}
+// g = G_E - mu G_N, Mg = P_E - mu P_N, and D's scalars (kCgDen, kCgGd); then D.
+void cg_direction(Context *ctx, const bsm_pattern_s *P, const CgState &s);
+// L <- L + a D + delta P_N with a, delta at min[0], min[1], symmetrised; nothing where min[2] != 0.
+void cg_update(Context *ctx, const bsm_pattern_s *P, const double *min, const double *D, const double *PN, double *L);
+
 // <A_n, B_n> (same pattern) for up to kRedSlots pairs.  Synchronises.
 void dots(Context *ctx, int count, const bsm_pattern_s *P, const double *const *A,
           const double *const *B, double *out);

@@ -113,6 +113,46 @@ __global__ __launch_bounds__(kT) void k_symmetrize(int64_t nnz, int b_arg, const
         }
 }
 
+// L <- L + a D + delta P_N, then symmetrised in place as k_symmetrize does, in one pass; a, delta and
+// whether to step at all come from device memory.
+template <int BC>
+__global__ __launch_bounds__(kT) void k_cg_update(int64_t nnz, int b_arg, const int *__restrict__ tmap,
+                                                  const double *__restrict__ min, const double *__restrict__ D,
+                                                  const double *__restrict__ PN, double *L)
+{
+    if (min[2] != 0.0) return;
+    const double a = min[0], delta = min[1];
+    const int b = BC > 0 ? BC : b_arg, bb = b * b;
+    const int64_t nel = nnz * bb, e0 = (int64_t)blockIdx.x * (kT * kUnroll) + threadIdx.x;
+    int64_t at[kUnroll];
+    double x[kUnroll], y[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t e = e0 + u * kT;
+        at[u] = -1;
+        if (e >= nel) continue;
+        const int64_t s = e / bb;
+        const int r = (int)(e - s * bb), p = r / b, q = r - p * b;
+        const int64_t t = tmap[s];
+        if (t < s || (t == s && p > q)) continue;
+        at[u] = t * bb + q * b + p;
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+        if (at[u] >= 0) {
+            const int64_t e = e0 + u * kT, f = at[u];
+            x[u] = fma(1.0, L[e], fma(a, D[e], delta * PN[e]));
+            y[u] = fma(1.0, L[f], fma(a, D[f], delta * PN[f]));
+        }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+        if (at[u] >= 0) {
+            const double v = 0.5 * (x[u] + y[u]);
+            L[e0 + u * kT] = v;
+            L[at[u]] = v;
+        }
+}
+
 // out[s] <- alpha (M[s] + M[t]^T) + beta out[s]
 template <int BC>
 __global__ void k_add_transpose(int64_t nnz, int b_arg, const int *__restrict__ tmap, double alpha,
@@ -242,6 +282,18 @@ void symmetrize(Context *ctx, const bsm_pattern_s *P, double *M)
         kern<<<grid1((n + kUnroll - 1) / kUnroll), kT, 0, ctx->stream>>>(P->nnzb, P->b, P->tmap.as<int>(), M);
     };
     P->b == 9 ? go(k_symmetrize<9>) : P->b == 4 ? go(k_symmetrize<4>) : go(k_symmetrize<0>);
+    BSM_HIP_TRY(hipGetLastError());
+}
+
+void cg_update(Context *ctx, const bsm_pattern_s *P, const double *min, const double *D, const double *PN, double *L)
+{
+    const int64_t n = nelems(P);
+    if (n <= 0) return;
+    auto go = [&](auto kern) {
+        kern<<<grid1((n + kUnroll - 1) / kUnroll), kT, 0, ctx->stream>>>(P->nnzb, P->b, P->tmap.as<int>(), min, D, PN,
+                                                                        L);
+    };
+    P->b == 9 ? go(k_cg_update<9>) : P->b == 4 ? go(k_cg_update<4>) : go(k_cg_update<0>);
     BSM_HIP_TRY(hipGetLastError());
 }
 

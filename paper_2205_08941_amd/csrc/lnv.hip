@@ -88,6 +88,54 @@ __global__ __launch_bounds__(kForceThreads) void k_row_forces(int b, const int *
     if (threadIdx.x < 3) out[3 * I + threadIdx.x] = 4.0 * red[threadIdx.x][0];
 }
 
+// The minimum of Omega along L + a D, a cubic in a, from the traces (CgScalar places of sc): its
+// coefficients c, the step a and the multiple delta of P_N that brings N(a) back to N_e; status 1
+// where the line has no minimum.  One function for the device, which steps by it, and the host,
+// which reports it: no contraction, so both round alike.
+struct LineMin {
+    double c[4], a, delta;
+    int status;
+};
+__host__ __device__ inline void line_minimum(const double *sc, int mode, double mu0, double n_electrons, LineMin &o)
+{
+#pragma clang fp contract(off)
+    const double *tr0 = sc + kCgEnergy, *tr = sc + kCgLine;
+    const double mu = cg_mu(sc, mode, mu0);
+    const double f[4] = {tr0[0], tr[0] + tr[1], tr[2], 0.0};
+    const double h[4] = {tr0[2], 2.0 * tr[3], tr[4], 0.0};
+    const double gg[4] = {tr0[1], tr[5] + tr[6], tr[7] + tr[8], tr[9]};
+    const double kk[4] = {tr0[3], tr[10] + tr[11], tr[12] + tr[13], tr[14]};
+    double nn[4];
+    for (int m = 0; m < 4; ++m) {
+        const double e = 2.0 * (3.0 * f[m] - 2.0 * gg[m]);
+        nn[m] = 2.0 * (3.0 * h[m] - 2.0 * kk[m]);
+        o.c[m] = e - mu * nn[m];
+    }
+    o.a = o.delta = 0.0;
+    o.status = 1;
+    const double disc = o.c[2] * o.c[2] - 3.0 * o.c[1] * o.c[3];
+    if (!(disc >= 0.0)) return;
+    const double den = o.c[2] + sqrt(disc);
+    if (!(den > 0.0)) return;
+    o.status = 0;
+    const double a = -o.c[1] / den;
+    o.a = a;
+    if (cg_canonical(sc, mode)) {
+        const double Na = nn[0] + a * (nn[1] + a * (nn[2] + a * nn[3]));
+        o.delta = (n_electrons - Na) / sc[kCgGnPn];
+    }
+}
+__global__ void k_line_minimum(double *sc, int mode, double mu, double n_electrons, double *host)
+{
+    LineMin o;
+    line_minimum(sc, mode, mu, n_electrons, o);
+    // no step from an energy or electron count that is not finite either
+    const double *t = sc + kCgEnergy;
+    const bool finite = isfinite(3.0 * t[0] - 2.0 * t[1]) && isfinite(3.0 * t[2] - 2.0 * t[3]);
+    const double v[3] = {o.a, o.delta, finite ? (double)o.status : 1.0};
+    for (int k = 0; k < 3; ++k) host[k] = sc[kCgMin + k] = v[k];
+}
+
 }  // namespace
 }  // namespace bsm
 
@@ -109,6 +157,7 @@ struct lnv_state_s {
     Mat ZG;
     // P_L
     Mat GE, GN, PE, PN, g, Mg, D, Dprev, gprev, Mgprev, t1, t2;
+    DevBuf scalars;   // CgScalar places
     double flops = 0.0;
 
     int prec = BSM_F64;   // precision of the step's products
@@ -248,14 +297,6 @@ struct lnv_state_s {
         axpbypcz(c, nl, 12.0, t1.d(), -12.0, t2.d(), 0.0, GN.d());
         symmetrize(c, PL, GN.d());
     }
-
-    double dot1(const Mat &A, const Mat &B)
-    {
-        const double *a = A.d(), *b = B.d();
-        double r = 0.0;
-        dots(c, 1, A.p, &a, &b, &r);
-        return r;
-    }
 };
 
 extern "C" int lnv_state_create(bsm_ctx ctx, const bsm_matrix *S, const bsm_matrix *H, const bsm_matrix *Z,
@@ -293,6 +334,7 @@ extern "C" int lnv_state_create(bsm_ctx ctx, const bsm_matrix *S, const bsm_matr
         for (Mat *m : {&st->GE, &st->GN, &st->PE, &st->PN, &st->g, &st->Mg, &st->D, &st->Dprev, &st->gprev,
                        &st->Mgprev, &st->t1, &st->t2})
             *m = Mat(c, PL);
+        st->scalars = DevBuf(c, sizeof(double) * kCgScalars);
         st->reset(*prm);
         *out = st.release();
         return BSM_OK;
@@ -396,24 +438,15 @@ int lnv_state_s::step(lnv_result *res)
         const int64_t nl = nelems(PL), nx = nelems(st->PX);
         Mat &X = st->X, &Y = st->Y, &W = st->W, &U = st->U, &XD = st->XD, &YD = st->YD, &Q = st->Q, &W1 = st->W1;
 
+        // Every scalar of the step stays on the device until its one read-back at the end (sc, CgScalar).
+        double *sc = st->scalars.as<double>();
+
         // ---- evaluate: X = LS, Y = LH, W = XX, U = YX; E, N from traces
         st->mul_pair_sh(PL, st->L, X.p, X.d(), Y.d());               // X = L S, Y = L H
         st->mul_pair(X, Y, X, W, U);                                 // W = X X, U = Y X
-        double tr0[4];
         {
             const double *a[2] = {X.d(), W.d()}, *b[2] = {Y.d(), X.d()};   // Tr XY, Tr WY, Tr XX, Tr WX
-            trace_set(c, kTracesEnergy, X.p, a, b, tr0);
-        }
-        const double E = 2.0 * (3.0 * tr0[0] - 2.0 * tr0[1]);
-        const double N = 2.0 * (3.0 * tr0[2] - 2.0 * tr0[3]);
-        res->E = E;
-        res->N = N;
-        res->mu = st->mu;
-        if (!(std::isfinite(E) && std::isfinite(N))) {
-            res->status = BSM_ENONFINITE;
-            res->Omega = NAN;
-            res->dE = NAN;
-            return fail(BSM_ENONFINITE, "LNV energy is not finite");
+            trace_set_to(c, kTracesEnergy, X.p, a, b, sc + kCgEnergy, kCgEnergy);
         }
 
         // ---- gradients on P_L
@@ -424,90 +457,72 @@ int lnv_state_s::step(lnv_result *res)
         Mat &PE = st->PE, &PN = st->PN, &g = st->g, &Mg = st->Mg, &D = st->D;
         st->precondition(GE, PE);
         st->precondition(GN, PN);
-        double gp[2];
         {
             const double *a[2] = {GN.d(), GN.d()}, *b[2] = {PN.d(), PE.d()};
-            dots(c, 2, PL, a, b, gp);
+            dots_to(c, 2, PL, a, b, sc + kCgGnPn, kCgGnPn);
         }
-        const double gn_pn = gp[0];
-        const bool canonical = st->prm.mode == LNV_CANONICAL && gn_pn > 0.0;
-        const double mu = canonical ? gp[1] / gn_pn : st->mu;
-        axpbypcz(c, nl, 1.0, GE.d(), -mu, GN.d(), 0.0, g.d());
-        axpbypcz(c, nl, 1.0, PE.d(), -mu, PN.d(), 0.0, Mg.d());
-        double beta = 0.0;
-        if (st->n > 0 && st->n % 50 != 0 && st->have_prev) {
-            const double den = st->dot1(st->gprev, st->Mgprev);
-            axpbypcz(c, nl, 1.0, Mg.d(), -1.0, st->Mgprev.d(), 0.0, t1.d());
-            beta = std::max(0.0, st->dot1(g, t1) / den);
-        }
-        // D = R + beta D_prev with R = -M(g)
-        if (beta != 0.0) axpbypcz(c, nl, -1.0, Mg.d(), beta, st->Dprev.d(), 0.0, D.d());
-        else axpby(c, nl, -1.0, Mg.d(), 0.0, D.d());
-        if (st->dot1(g, D) >= 0.0) {
-            beta = 0.0;
-            axpby(c, nl, -1.0, Mg.d(), 0.0, D.d());
-        }
-        if (canonical) {
-            const double proj = st->dot1(GN, D) / gn_pn;
-            axpby(c, nl, -proj, PN.d(), 1.0, D.d());
-        }
+        CgState cg{};
+        cg.GE = GE.d();
+        cg.GN = GN.d();
+        cg.PE = PE.d();
+        cg.PN = PN.d();
+        cg.gprev = st->gprev.d();
+        cg.Mgprev = st->Mgprev.d();
+        cg.Dprev = st->Dprev.d();
+        cg.g = g.d();
+        cg.Mg = Mg.d();
+        cg.D = D.d();
+        cg.sc = sc;
+        cg.mu = st->mu;
+        cg.canonical = st->prm.mode == LNV_CANONICAL;
+        cg.use_prev = st->n > 0 && st->n % 50 != 0 && st->have_prev;
+        cg_direction(c, PL, cg);   // D = -M(g) + beta D_prev, or -M(g) where that does not descend; N held
 
         // ---- exact line search along L + a D
         st->mul_pair_sh(PL, D.d(), XD.p, XD.d(), YD.d());            // X_D = D S, Y_D = D H
         st->mul(XD, XD, Q);                                          // Q = X_D X_D
         axpbypcz(c, nx, 1.0, X.d(), 1.0, XD.d(), 0.0, U.d());        // X1 = X + X_D (U is free now)
         st->mul(U, U, W1);                                           // W1 = X1 X1
-        axpbypcz(c, nx, -1.0, W.d(), -1.0, Q.d(), 1.0, W1.d());      // M1 = W1 - W - Q = X X_D + X_D X
-        Mat &M1 = W1;
-        double tr[15];
         {
             // Tr of (X_D Y, X Y_D, X_D Y_D, X X_D, X_D X_D, M1 Y, W Y_D, Q Y, M1 Y_D, Q Y_D,
-            //        M1 X, W X_D, Q X, M1 X_D, Q X_D)
-            const double *a[5] = {XD.d(), X.d(), M1.d(), W.d(), Q.d()};
+            //        M1 X, W X_D, Q X, M1 X_D, Q X_D), M1 = W1 - W - Q = X X_D + X_D X
+            const double *a[5] = {XD.d(), X.d(), W1.d(), W.d(), Q.d()};
             const double *b[4] = {Y.d(), YD.d(), XD.d(), X.d()};
-            trace_set(c, kTracesLineSearch, X.p, a, b, tr);
+            trace_set_to(c, kTracesLineSearch, X.p, a, b, sc + kCgLine, kCgLine);
         }
-        const double f[4] = {tr0[0], tr[0] + tr[1], tr[2], 0.0};
-        const double h[4] = {tr0[2], 2.0 * tr[3], tr[4], 0.0};
-        const double gg[4] = {tr0[1], tr[5] + tr[6], tr[7] + tr[8], tr[9]};
-        const double kk[4] = {tr0[3], tr[10] + tr[11], tr[12] + tr[13], tr[14]};
-        double e[4], nn[4], cc[4];
-        for (int m = 0; m < 4; ++m) {
-            e[m] = 2.0 * (3.0 * f[m] - 2.0 * gg[m]);
-            nn[m] = 2.0 * (3.0 * h[m] - 2.0 * kk[m]);
-            cc[m] = e[m] - mu * nn[m];
-            res->c[m] = cc[m];
+        const double *h = c->host_scalars;
+        k_line_minimum<<<1, 1, 0, c->stream>>>(sc, cg.canonical, cg.mu, st->prm.n_electrons, c->host_scalars + kCgMin);
+        BSM_HIP_TRY(hipGetLastError());
+        cg_update(c, PL, sc + kCgMin, D.d(), PN.d(), st->L);   // nothing where the line has no minimum
+        BSM_HIP_TRY(hipStreamSynchronize(c->stream));
+
+        const double E = 2.0 * (3.0 * h[0] - 2.0 * h[1]);
+        const double N = 2.0 * (3.0 * h[2] - 2.0 * h[3]);
+        res->E = E;
+        res->N = N;
+        res->mu = st->mu;
+        if (!(std::isfinite(E) && std::isfinite(N))) {   // the polynomials have no minimum then: L is as it was
+            res->status = BSM_ENONFINITE;
+            res->Omega = NAN;
+            res->dE = NAN;
+            return fail(BSM_ENONFINITE, "LNV energy is not finite");
         }
-        const double disc = cc[2] * cc[2] - 3.0 * cc[1] * cc[3];
-        int status = BSM_OK;
-        double den = 0.0;
-        if (!(disc >= 0.0)) {
-            status = BSM_ERUNAWAY;
-        } else {
-            den = cc[2] + std::sqrt(disc);
-            if (!(den > 0.0)) status = BSM_ERUNAWAY;
-        }
+        const double mu = cg_mu(h, cg.canonical, cg.mu);
+        LineMin lm;
+        line_minimum(h, cg.canonical, cg.mu, st->prm.n_electrons, lm);
+        for (int m = 0; m < 4; ++m) res->c[m] = lm.c[m];
         const double dE = (st->n > 0) ? E - st->E_prev : NAN;
         res->Omega = E - mu * N;
         res->mu = mu;
-        res->beta = beta;
+        res->beta = h[kCgGd] >= 0.0 ? 0.0 : cg_beta(h, cg.use_prev);
         res->dE = dE;
         res->product_flops = st->flops;
-        if (status != BSM_OK) {
-            res->status = status;
-            return fail(status, "LNV line search found no minimum (L left the basin)");
+        if (h[kCgMin + 2] != 0.0) {
+            res->status = BSM_ERUNAWAY;
+            return fail(BSM_ERUNAWAY, "LNV line search found no minimum (L left the basin)");
         }
-        const double a = -cc[1] / den;
-        double delta = 0.0;
-        if (canonical) {
-            const double Na = nn[0] + a * (nn[1] + a * (nn[2] + a * nn[3]));
-            delta = (st->prm.n_electrons - Na) / gn_pn;
-        }
-        axpbypcz(c, nl, a, D.d(), delta, PN.d(), 1.0, st->L);
-        symmetrize(c, PL, st->L);
-        BSM_HIP_TRY(hipStreamSynchronize(c->stream));
 
-        res->alpha = a;
+        res->alpha = h[kCgMin];
         res->converged = (st->n > 0 && std::fabs(dE) < st->prm.tol_E) ? 1 : 0;
         res->status = BSM_OK;
         st->E_prev = E;

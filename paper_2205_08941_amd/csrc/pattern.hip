@@ -293,7 +293,7 @@ bsm_pattern_s *make_pattern(Context *ctx, int natoms, int b, const double *pos_d
                                                             nullptr, nullptr);
     p->rowptr = DevBuf(ctx, sizeof(int) * (natoms + 1));
     k_scan<<<1, 1024, 0, st>>>(natoms, rowcount.as<int>(), p->rowptr.as<int>(), fl + 1);
-    int *hostv = reinterpret_cast<int *>(ctx->host_scalars);
+    int *hostv = reinterpret_cast<int *>(ctx->host_scalars + kHostCounts);
     k_row_info<<<1, 1024, 0, st>>>(natoms, p->rowptr.as<int>(), fl, hostv);
     BSM_HIP_TRY(hipGetLastError());
     BSM_HIP_TRY(hipStreamSynchronize(st));

@@ -1032,7 +1032,7 @@ void make_tiles(Context *ctx, const bsm_pattern_s *PC, int G, int waves, bool cl
     ts.toff = DevBuf(ctx, sizeof(int64_t) * (ng + 1));
     k_group_union<<<ng, kPlanThreads, 0, st>>>(n, G, PC->rowptr.as<int>(), PC->cols.as<int>(), jt, ts.ntile.as<int>());
     k_int_to_i64<<<(ng + 255) / 256, 256, 0, st>>>(ng, ts.ntile.as<int>(), ts.ntile64.as<int64_t>());
-    int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars);   // counts come back in pinned memory
+    int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars + kHostCounts);   // counts come back in pinned memory
     k_scan64<<<1, 1024, 0, st>>>(ng, ts.ntile64.as<int64_t>(), ts.toff.as<int64_t>(), host);
     BSM_HIP_TRY(hipStreamSynchronize(st));
     const int64_t nt = ts.nt = *host;
@@ -1079,7 +1079,7 @@ void count_entries(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *P
             PA->rowptr.as<int>(), PA->cols.as<int>(), PA->tmap.as<int>(), PB->rowptr.as<int>(), PB->cols.as<int>(),
             PB->tmap.as<int>(), ec.nent.as<int64_t>(), tri, tri + 1, nullptr, nullptr);
         k_pad_counts<<<(unsigned)((nt + 127) / 128), 128, 0, st>>>(nt, 1, ec.nent.as<int64_t>());
-        int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars);
+        int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars + kHostCounts);
         k_plan_totals<<<1, kTotalLanes, 0, st>>>(tri, reinterpret_cast<unsigned long long *>(host) + 1);
         k_scan64<<<1, 1024, 0, st>>>(nt, ec.nent.as<int64_t>(), ec.ebeg.as<int64_t>(), host);
         k_tile_ebeg<<<(unsigned)((nt + 1 + 127) / 128), 128, 0, st>>>(nt, 1, ec.ebeg.as<int64_t>(),
@@ -1166,7 +1166,7 @@ static int64_t tiles_of_8(Context *ctx, const bsm_pattern_s *PC)
     k_group_union<<<ng, kPlanThreads, 0, st>>>(PC->natoms, 8, PC->rowptr.as<int>(), PC->cols.as<int>(), 64 / PC->b,
                                                ntile.as<int>());
     k_int_to_i64<<<(ng + 255) / 256, 256, 0, st>>>(ng, ntile.as<int>(), ntile64.as<int64_t>());
-    int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars);
+    int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars + kHostCounts);
     k_scan64<<<1, 1024, 0, st>>>(ng, ntile64.as<int64_t>(), toff.as<int64_t>(), host);
     BSM_HIP_TRY(hipStreamSynchronize(st));
     return PC->tiles8 = *host;

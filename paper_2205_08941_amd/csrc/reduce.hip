@@ -12,6 +12,7 @@
 
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 namespace bsm {
 namespace {
@@ -103,7 +104,7 @@ struct EnergyTraces {   // Tr XY, Tr WY, Tr XX, Tr WX from A = {X, W}, B = {Y, X
     static constexpr int na = 2, nb = 2, count = 4;
     static constexpr int ai[count] = {0, 1, 0, 1}, bi[count] = {0, 0, 1, 1};
 };
-struct LineSearchTraces {   // A = {X_D, X, M1, W, Q}, B = {Y, Y_D, X_D, X}
+struct LineSearchTraces {   // A = {X_D, X, M1 (given as W1), W, Q}, B = {Y, Y_D, X_D, X}
     static constexpr int na = 5, nb = 4, count = 15;
     static constexpr int ai[count] = {0, 1, 0, 1, 0, 2, 3, 4, 2, 4, 2, 3, 4, 2, 4};
     static constexpr int bi[count] = {0, 1, 1, 2, 2, 0, 1, 0, 1, 1, 3, 2, 3, 2, 2};
@@ -138,6 +139,8 @@ __global__ __launch_bounds__(kThreads) void k_trace_set(int b_arg, int64_t nnz, 
             for (int j = 0; j < TS::na; ++j) av[j] = A.p[j][ia];
 #pragma unroll
             for (int j = 0; j < TS::nb; ++j) bv[j] = Bp.p[j][ib];
+            // M1 = W1 - W - Q, as axpbypcz forms it
+            if constexpr (std::is_same_v<TS, LineSearchTraces>) av[2] = fma(1.0, av[2], fma(-1.0, av[3], -1.0 * av[4]));
 #pragma unroll
             for (int n = 0; n < TS::count; ++n) acc[n] = fma(av[TS::ai[n]], bv[TS::bi[n]], acc[n]);
         }
@@ -218,7 +221,8 @@ __global__ __launch_bounds__(kThreads) void k_dist_identity(int64_t nnz, int b_a
 }
 
 // Partial sums of slot n added in workgroup order, by one workgroup.
-__device__ inline void k_finish_body(int n, int nparts, const double *__restrict__ partials, double *__restrict__ out)
+__device__ inline void k_finish_body(int n, int nparts, const double *__restrict__ partials, double *__restrict__ out,
+                                     double *__restrict__ dev = nullptr)
 {
     __shared__ double red[kThreads];
     double v = 0.0;
@@ -231,15 +235,104 @@ __device__ inline void k_finish_body(int n, int nparts, const double *__restrict
         if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[n] = red[0];
+    if (threadIdx.x == 0) {
+        out[n] = red[0];
+        if (dev) dev[n] = red[0];
+    }
 }
 
 // One workgroup per slot; `out` is the context's pinned host memory, read after the
-// stream is synchronised (no copy in between).
+// stream is synchronised (no copy in between), `dev` device memory for kernels that go on
+// with the result (or NULL).
 __global__ __launch_bounds__(kThreads) void k_finish(int nparts, const double *__restrict__ partials,
-                                                     double *__restrict__ out)
+                                                     double *__restrict__ out, double *__restrict__ dev)
 {
-    k_finish_body(blockIdx.x, nparts, partials, out);
+    k_finish_body(blockIdx.x, nparts, partials, out, dev);
+}
+
+// The scalars between the vector passes of a conjugate-gradient step stay on the device: a host
+// that reads them back waits for the stream and starts it again five times a step, which on 64
+// atoms took as long as a product each time (four LNV steps of 64 atoms, b = 4: 1339 -> 1047 us).
+constexpr int kCgUnroll = 4;
+// g, Mg and the partial sums of kCgDen; ranges and order as k_dots.
+__global__ __launch_bounds__(kThreads) void k_cg_gradient(int64_t nel, CgState s, double *__restrict__ partials)
+{
+    const double mu = cg_mu(s.sc, s.canonical, s.mu);
+    double acc[2] = {0.0, 0.0};
+    const int64_t per = (nel + gridDim.x - 1) / gridDim.x;
+    const int64_t lo = per * blockIdx.x, hi = min(nel, lo + per);
+    for (int64_t x0 = lo + threadIdx.x; x0 < hi; x0 += kCgUnroll * kThreads) {
+        double ge[kCgUnroll], gn[kCgUnroll], pe[kCgUnroll], pn[kCgUnroll], gp[kCgUnroll], mp[kCgUnroll];
+#pragma unroll
+        for (int u = 0; u < kCgUnroll; ++u) {   // all loads before the stores
+            const int64_t e = min(x0 + u * kThreads, hi - 1);
+            ge[u] = s.GE[e];
+            gn[u] = s.GN[e];
+            pe[u] = s.PE[e];
+            pn[u] = s.PN[e];
+            if (s.use_prev) {
+                gp[u] = s.gprev[e];
+                mp[u] = s.Mgprev[e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kCgUnroll; ++u) {
+            const int64_t e = x0 + u * kThreads;
+            if (e >= hi) continue;
+            const double g = fma(1.0, ge[u], -mu * gn[u]), mg = fma(1.0, pe[u], -mu * pn[u]);
+            s.g[e] = g;
+            s.Mg[e] = mg;
+            if (s.use_prev) {
+                acc[0] = fma(gp[u], mp[u], acc[0]);
+                acc[1] = fma(g, fma(1.0, mg, -1.0 * mp[u]), acc[1]);
+            }
+        }
+    }
+    block_reduce_store<2>(acc, 2, partials);
+}
+
+// D before its projection
+__device__ inline double cg_plain(const CgState &s, double beta, int64_t e)
+{
+    return beta != 0.0 ? fma(-1.0, s.Mg[e], beta * s.Dprev[e]) : -s.Mg[e];
+}
+
+// the partial sums of kCgGd
+__global__ __launch_bounds__(kThreads) void k_cg_dots(int64_t nel, CgState s, double *__restrict__ partials)
+{
+    const double beta = cg_beta(s.sc, s.use_prev);
+    double acc[3] = {0.0, 0.0, 0.0};
+    const int64_t per = (nel + gridDim.x - 1) / gridDim.x;
+    const int64_t lo = per * blockIdx.x, hi = min(nel, lo + per);
+#pragma unroll 4
+    for (int64_t e = lo + threadIdx.x; e < hi; e += kThreads) {
+        const double d = cg_plain(s, beta, e), gn = s.GN[e];
+        acc[0] = fma(s.g[e], d, acc[0]);
+        acc[1] = fma(gn, d, acc[1]);
+        acc[2] = fma(gn, s.Mg[e], acc[2]);
+    }
+    block_reduce_store<3>(acc, 3, partials);
+}
+
+// D: steepest descent where the conjugate direction does not descend, then N held to first order
+__global__ __launch_bounds__(kThreads) void k_cg_direction(int64_t nel, CgState s)
+{
+    const bool reset = s.sc[kCgGd] >= 0.0;
+    const double beta = reset ? 0.0 : cg_beta(s.sc, s.use_prev);
+    const bool project = cg_canonical(s.sc, s.canonical);
+    const double gnd = reset ? -s.sc[kCgGd + 2] : s.sc[kCgGd + 1];
+    const double proj = project ? gnd / s.sc[kCgGnPn] : 0.0;
+    const int64_t e0 = (int64_t)blockIdx.x * (kCgUnroll * kThreads) + threadIdx.x;
+    double d[kCgUnroll];
+#pragma unroll
+    for (int u = 0; u < kCgUnroll; ++u) {   // all loads before the stores
+        const int64_t e = min(e0 + u * kThreads, nel - 1);
+        d[u] = cg_plain(s, beta, e);
+        if (project) d[u] = fma(1.0, d[u], -proj * s.PN[e]);
+    }
+#pragma unroll
+    for (int u = 0; u < kCgUnroll; ++u)
+        if (e0 + u * kThreads < nel) s.D[e0 + u * kThreads] = d[u];
 }
 
 // Largest absolute row sum (max over scalar rows of sum_j |A_ij|); max is
@@ -281,10 +374,17 @@ int grid_for(int64_t work)
 void finish(Context *ctx, int count, int nparts, double *out)
 {
     hipStream_t st = ctx->stream;
-    k_finish<<<count, kThreads, 0, st>>>(nparts, ctx->red_partials.as<double>(), ctx->host_scalars);
+    k_finish<<<count, kThreads, 0, st>>>(nparts, ctx->red_partials.as<double>(), ctx->host_scalars, nullptr);
     BSM_HIP_TRY(hipGetLastError());
     BSM_HIP_TRY(hipStreamSynchronize(st));
     for (int n = 0; n < count; ++n) out[n] = ctx->host_scalars[n];
+}
+
+// without waiting: to sc[..] on the device and host_scalars[host ..]
+void finish_to(Context *ctx, int count, int nparts, double *sc, int host)
+{
+    k_finish<<<count, kThreads, 0, ctx->stream>>>(nparts, ctx->red_partials.as<double>(), ctx->host_scalars + host, sc);
+    BSM_HIP_TRY(hipGetLastError());
 }
 
 }  // namespace
@@ -389,14 +489,14 @@ void trace_product_noalloc(Context *ctx, const bsm_pattern_s *PA, const double *
     BSM_HIP_TRY(hipGetLastError());
 }
 
-void trace_set(Context *ctx, int kind, const bsm_pattern_s *P, const double *const *A, const double *const *B,
-               double *out)
+static int trace_set_launch(Context *ctx, int kind, const bsm_pattern_s *P, const double *const *A,
+                            const double *const *B, int &count)
 {
     BSM_REQUIRE(kind == kTracesEnergy || kind == kTracesLineSearch, BSM_EINVAL, "bad trace set");
     Ptrs pa{}, pb{};
     const int na = kind == kTracesEnergy ? EnergyTraces::na : LineSearchTraces::na;
     const int nb = kind == kTracesEnergy ? EnergyTraces::nb : LineSearchTraces::nb;
-    const int count = kind == kTracesEnergy ? EnergyTraces::count : LineSearchTraces::count;
+    count = kind == kTracesEnergy ? EnergyTraces::count : LineSearchTraces::count;
     for (int j = 0; j < na; ++j) pa.p[j] = A[j];
     for (int j = 0; j < nb; ++j) pb.p[j] = B[j];
     const int64_t nchunks = (P->nnzb + kChunk - 1) / kChunk;
@@ -419,11 +519,26 @@ void trace_set(Context *ctx, int kind, const bsm_pattern_s *P, const double *con
     if (kind == kTracesEnergy) go(EnergyTraces{}, std::integral_constant<int, 4>{});
     else go(LineSearchTraces{}, std::integral_constant<int, kRedSlots>{});
     BSM_HIP_TRY(hipGetLastError());
+    return grid;
+}
+
+void trace_set(Context *ctx, int kind, const bsm_pattern_s *P, const double *const *A, const double *const *B,
+               double *out)
+{
+    int count;
+    const int grid = trace_set_launch(ctx, kind, P, A, B, count);
     finish(ctx, count, grid, out);
 }
 
-void dots(Context *ctx, int count, const bsm_pattern_s *P, const double *const *A, const double *const *B,
-          double *out)
+void trace_set_to(Context *ctx, int kind, const bsm_pattern_s *P, const double *const *A, const double *const *B,
+                  double *sc, int host)
+{
+    int count;
+    const int grid = trace_set_launch(ctx, kind, P, A, B, count);
+    finish_to(ctx, count, grid, sc, host);
+}
+
+static int dots_launch(Context *ctx, int count, const bsm_pattern_s *P, const double *const *A, const double *const *B)
 {
     BSM_REQUIRE(count >= 1 && count <= kRedSlots, BSM_EINVAL, "bad dot count");
     Ptrs pa{}, pb{};
@@ -438,7 +553,34 @@ void dots(Context *ctx, int count, const bsm_pattern_s *P, const double *const *
     else if (count <= 4) k_dots<4><<<grid, kThreads, 0, st>>>(count, nel, pa, pb, ctx->red_partials.as<double>());
     else k_dots<kRedSlots><<<grid, kThreads, 0, st>>>(count, nel, pa, pb, ctx->red_partials.as<double>());
     BSM_HIP_TRY(hipGetLastError());
-    finish(ctx, count, grid, out);
+    return grid;
+}
+
+void dots(Context *ctx, int count, const bsm_pattern_s *P, const double *const *A, const double *const *B,
+          double *out)
+{
+    finish(ctx, count, dots_launch(ctx, count, P, A, B), out);
+}
+
+void dots_to(Context *ctx, int count, const bsm_pattern_s *P, const double *const *A, const double *const *B,
+             double *sc, int host)
+{
+    finish_to(ctx, count, dots_launch(ctx, count, P, A, B), sc, host);
+}
+
+void cg_direction(Context *ctx, const bsm_pattern_s *P, const CgState &s)
+{
+    const int64_t nel = nelems(P);
+    const int grid = grid_for(nel);
+    hipStream_t st = ctx->stream;
+    double *partials = ctx->red_partials.as<double>();
+    k_cg_gradient<<<grid, kThreads, 0, st>>>(nel, s, partials);
+    finish_to(ctx, 2, grid, s.sc + kCgDen, kCgDen);
+    k_cg_dots<<<grid, kThreads, 0, st>>>(nel, s, partials);
+    finish_to(ctx, 3, grid, s.sc + kCgGd, kCgGd);
+    k_cg_direction<<<(unsigned)((nel + kCgUnroll * kThreads - 1) / (kCgUnroll * kThreads)), kThreads, 0, st>>>(
+        nel, s);
+    BSM_HIP_TRY(hipGetLastError());
 }
 
 double trace_single(Context *ctx, const bsm_pattern_s *P, const double *A)
