@@ -53,6 +53,20 @@ struct DevBuf {
     template <class T> T *as() const { return static_cast<T *>(ptr); }
 };
 
+// Arrays cut from one allocation, each at a 256-byte boundary: an allocation is a call to the
+// owner's allocator, some 10 us through Python, and a plan or a pattern needs a dozen arrays.
+struct Cut {
+    char *base;
+    size_t used = 0;
+    static size_t room(size_t bytes) { return (bytes + 255) / 256 * 256; }
+    template <class T> T *take(int64_t n)
+    {
+        T *p = reinterpret_cast<T *>(base + used);
+        used += room(sizeof(T) * (size_t)n);
+        return p;
+    }
+};
+
 // Product plan for C = mask_{P_C}(A B): tiles of (G rows, up to jt output
 // columns) and, per tile, the list of k with the slots of A_{i_a k} and B_kj.
 // Built on the GPU on first use, cached per (P_A, P_B, P_C).

@@ -272,27 +272,26 @@ bsm_pattern_s *make_pattern(Context *ctx, int natoms, int b, const double *pos_d
         ncells *= nc;
     }
 
-    DevBuf cell(ctx, sizeof(int) * natoms), cellcount(ctx, sizeof(int) * ncells),
-        cellstart(ctx, sizeof(int) * (ncells + 1)), cellfill(ctx, sizeof(int) * ncells),
-        cellatoms(ctx, sizeof(int) * natoms), rowcount(ctx, sizeof(int) * natoms),
-        flags(ctx, sizeof(int) * 8);
-    BSM_HIP_TRY(hipMemsetAsync(cellcount.ptr, 0, sizeof(int) * ncells, st));
-    BSM_HIP_TRY(hipMemsetAsync(cellfill.ptr, 0, sizeof(int) * ncells, st));
-    BSM_HIP_TRY(hipMemsetAsync(flags.ptr, 0, sizeof(int) * 8, st));
-    int *fl = flags.as<int>();
+    const size_t ra = Cut::room(sizeof(int) * natoms), rc = Cut::room(sizeof(int) * ncells);
+    DevBuf work(ctx, 256 + 2 * rc + Cut::room(sizeof(int) * (ncells + 1)) + 3 * ra);
+    Cut cut{work.as<char>()};
+    int *fl = cut.take<int>(8), *cellcount = cut.take<int>(ncells), *cellfill = cut.take<int>(ncells);
+    BSM_HIP_TRY(hipMemsetAsync(work.ptr, 0, cut.used, st));   // flags and counts
+    int *cellstart = cut.take<int>(ncells + 1), *cell = cut.take<int>(natoms), *cellatoms = cut.take<int>(natoms),
+        *rowcount = cut.take<int>(natoms);
 
-    k_cell_index<<<blocks_for(natoms, 256), 256, 0, st>>>(natoms, p->pos.as<double>(), g, cell.as<int>(),
-                                                            cellcount.as<int>(), fl + 4);
-    k_scan<<<1, 1024, 0, st>>>((int)ncells, cellcount.as<int>(), cellstart.as<int>(), fl + 0);
-    k_cell_scatter<<<blocks_for(natoms, 256), 256, 0, st>>>(natoms, cell.as<int>(), cellstart.as<int>(),
-                                                              cellfill.as<int>(), cellatoms.as<int>());
+    k_cell_index<<<blocks_for(natoms, 256), 256, 0, st>>>(natoms, p->pos.as<double>(), g, cell,
+                                                            cellcount, fl + 4);
+    k_scan<<<1, 1024, 0, st>>>((int)ncells, cellcount, cellstart, fl + 0);
+    k_cell_scatter<<<blocks_for(natoms, 256), 256, 0, st>>>(natoms, cell, cellstart,
+                                                              cellfill, cellatoms);
     double r2 = cutoff * cutoff;
     k_neighbors<0><<<blocks_for(natoms, kRowsPerGroup), 64 * kRowsPerGroup, 0, st>>>(natoms, p->pos.as<double>(), g, r2,
-                                                            cell.as<int>(), cellstart.as<int>(),
-                                                            cellatoms.as<int>(), rowcount.as<int>(),
+                                                            cell, cellstart,
+                                                            cellatoms, rowcount,
                                                             nullptr, nullptr);
     p->rowptr = DevBuf(ctx, sizeof(int) * (natoms + 1));
-    k_scan<<<1, 1024, 0, st>>>(natoms, rowcount.as<int>(), p->rowptr.as<int>(), fl + 1);
+    k_scan<<<1, 1024, 0, st>>>(natoms, rowcount, p->rowptr.as<int>(), fl + 1);
     int *hostv = reinterpret_cast<int *>(ctx->host_scalars + kHostCounts);
     k_row_info<<<1, 1024, 0, st>>>(natoms, p->rowptr.as<int>(), fl, hostv);
     BSM_HIP_TRY(hipGetLastError());
@@ -306,8 +305,8 @@ bsm_pattern_s *make_pattern(Context *ctx, int natoms, int b, const double *pos_d
 
     p->cols = DevBuf(ctx, sizeof(int) * (size_t)total);
     k_neighbors<1><<<blocks_for(natoms, kRowsPerGroup), 64 * kRowsPerGroup, 0, st>>>(natoms, p->pos.as<double>(), g, r2,
-                                                            cell.as<int>(), cellstart.as<int>(),
-                                                            cellatoms.as<int>(), nullptr,
+                                                            cell, cellstart,
+                                                            cellatoms, nullptr,
                                                             p->rowptr.as<int>(), p->cols.as<int>());
     k_sort_rows<<<natoms, 256, 0, st>>>(natoms, p->rowptr.as<int>(), p->cols.as<int>());
 

@@ -615,14 +615,14 @@ __global__ void k_map_cslots(int64_t ntiles, int G, int jt, const int *__restric
 }
 
 __global__ __launch_bounds__(1024) void k_scan64(int64_t n, const int64_t *__restrict__ in, int64_t *__restrict__ out,
-                                                 int64_t *host)   // host: also the total, in pinned memory
-{
+                                                 int64_t *host, const int *__restrict__ in32)
+{   // host: also the total, in pinned memory; in32: ints instead of `in`
     __shared__ long long part[1024];
     const int t = threadIdx.x, nt = blockDim.x;
     const int64_t chunk = (n + nt - 1) / nt;
     const int64_t lo = min(n, (int64_t)t * chunk), hi = min(n, lo + chunk);
     long long s = 0;
-    for (int64_t k = lo; k < hi; ++k) s += in[k];
+    for (int64_t k = lo; k < hi; ++k) s += in32 ? in32[k] : in[k];
     part[t] = s;
     __syncthreads();
     for (int off = 1; off < nt; off <<= 1) {
@@ -634,7 +634,7 @@ __global__ __launch_bounds__(1024) void k_scan64(int64_t n, const int64_t *__res
     long long run = part[t] - s;
     for (int64_t k = lo; k < hi; ++k) {
         out[k] = run;
-        run += in[k];
+        run += in32 ? in32[k] : in[k];
     }
     if (t == nt - 1) {
         out[n] = part[t];
@@ -652,12 +652,6 @@ __global__ __launch_bounds__(kTotalLanes) void k_plan_totals(const unsigned long
     for (int off = kTotalLanes / 2; off > 0; off >>= 1)
         for (int k = 0; k < 2; ++k) v[k] += __shfl_xor(v[k], off, kTotalLanes);
     if (threadIdx.x < 2) host[threadIdx.x] = v[threadIdx.x];
-}
-
-__global__ void k_int_to_i64(int n, const int *__restrict__ in, int64_t *__restrict__ out)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = in[i];
 }
 
 template <int B, int G, class T = double>
@@ -868,7 +862,9 @@ namespace {
 struct TileSet {
     int G = 0, waves = 1, jt = 0, ng = 0;
     int64_t nt = 0;
-    DevBuf ntile, ntile64, toff, hdr, tcols, scr;
+    DevBuf hdr, groups, columns;              // what the pointers below point into
+    int *ntile = nullptr, *tcols = nullptr, *scr = nullptr;
+    int64_t *toff = nullptr;
 };
 // Workgroups of a launch over the tiles
 dim3 tile_grid(int64_t nt)
@@ -877,7 +873,8 @@ dim3 tile_grid(int64_t nt)
     return dim3((unsigned)x, (unsigned)((nt + x - 1) / x));
 }
 struct EntryCount {
-    DevBuf nent, totals, ebeg;
+    DevBuf buf;   // what the pointers below point into
+    int64_t *nent = nullptr, *ebeg = nullptr;
     int64_t ne = 0;
     unsigned long long ntri[2] = {0, 0};   // triples, rows multiplied
 };
@@ -1027,26 +1024,28 @@ void make_tiles(Context *ctx, const bsm_pattern_s *PC, int G, int waves, bool cl
     ts.waves = waves;
     ts.jt = jt;
     ts.ng = ng;
-    ts.ntile = DevBuf(ctx, sizeof(int) * ng);
-    ts.ntile64 = DevBuf(ctx, sizeof(int64_t) * ng);
-    ts.toff = DevBuf(ctx, sizeof(int64_t) * (ng + 1));
-    k_group_union<<<ng, kPlanThreads, 0, st>>>(n, G, PC->rowptr.as<int>(), PC->cols.as<int>(), jt, ts.ntile.as<int>());
-    k_int_to_i64<<<(ng + 255) / 256, 256, 0, st>>>(ng, ts.ntile.as<int>(), ts.ntile64.as<int64_t>());
+    ts.groups = DevBuf(ctx, Cut::room(sizeof(int) * ng) + Cut::room(sizeof(int64_t) * (ng + 1)));
+    Cut g{ts.groups.as<char>()};
+    ts.ntile = g.take<int>(ng);
+    ts.toff = g.take<int64_t>(ng + 1);
+    k_group_union<<<ng, kPlanThreads, 0, st>>>(n, G, PC->rowptr.as<int>(), PC->cols.as<int>(), jt, ts.ntile);
     int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars + kHostCounts);   // counts come back in pinned memory
-    k_scan64<<<1, 1024, 0, st>>>(ng, ts.ntile64.as<int64_t>(), ts.toff.as<int64_t>(), host);
+    k_scan64<<<1, 1024, 0, st>>>(ng, nullptr, ts.toff, host, ts.ntile);
     BSM_HIP_TRY(hipStreamSynchronize(st));
     const int64_t nt = ts.nt = *host;
     BSM_REQUIRE(nt < (int64_t)INT32_MAX, BSM_EINVAL, "too many product tiles");
     ts.hdr = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt * (G + G * jt)));
-    ts.tcols = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, nt * jt));
-    ts.scr = DevBuf(ctx, sizeof(int) * (size_t)std::max<int64_t>(1, (5 + G) * nt * jt));
+    ts.columns = DevBuf(ctx, Cut::room(sizeof(int) * (size_t)(nt * jt)) + sizeof(int) * (size_t)((5 + G) * nt * jt));
+    Cut c{ts.columns.as<char>()};
+    ts.tcols = c.take<int>(nt * jt);
+    ts.scr = c.take<int>((5 + G) * nt * jt);
     k_group_tiles<<<ng, kPlanThreads, 0, st>>>(n, G, jt, ctx->column_order, PC->rowptr.as<int>(), PC->cols.as<int>(),
-                                               ts.toff.as<int64_t>(), nt, ts.hdr.as<int>(), ts.tcols.as<int>(),
-                                               ts.scr.as<int>());
+                                               ts.toff, nt, ts.hdr.as<int>(), ts.tcols,
+                                               ts.scr);
     if (cluster)
         k_cluster_tiles<<<ng, 64, 0, st>>>(n, G, jt, PC->pos.as<double>(), PC->box[0], PC->box[1], PC->box[2],
-                                           ts.toff.as<int64_t>(), nt, ts.hdr.as<int>(), ts.tcols.as<int>(),
-                                           ts.scr.as<int>());
+                                           ts.toff, nt, ts.hdr.as<int>(), ts.tcols,
+                                           ts.scr);
     BSM_HIP_TRY(hipGetLastError());
 }
 
@@ -1068,21 +1067,22 @@ void count_entries(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *P
     plan->ebeg = DevBuf(ctx, sizeof(int64_t) * (size_t)(nt + 1));
     if (nt == 0) BSM_HIP_TRY(hipMemsetAsync(plan->ebeg.ptr, 0, sizeof(int64_t), st));
     if (nt > 0) {
-        ec.nent = DevBuf(ctx, sizeof(int64_t) * (size_t)nt);
         const size_t places = sizeof(unsigned long long) * kTotalLanes * kTotalStride;
-        ec.totals = DevBuf(ctx, places);
-        ec.ebeg = DevBuf(ctx, sizeof(int64_t) * (size_t)(nt + 1));
-        unsigned long long *tri = ec.totals.as<unsigned long long>();
+        ec.buf = DevBuf(ctx, places + Cut::room(sizeof(int64_t) * (size_t)nt) + Cut::room(sizeof(int64_t) * (size_t)(nt + 1)));
+        Cut c{ec.buf.as<char>()};
+        unsigned long long *tri = c.take<unsigned long long>(kTotalLanes * kTotalStride);
+        ec.nent = c.take<int64_t>(nt);
+        ec.ebeg = c.take<int64_t>(nt + 1);
         BSM_HIP_TRY(hipMemsetAsync(tri, 0, places, st));
         k_tile_entries<0><<<tile_grid(nt), kPlanThreads, 0, st>>>(
-            nt, 1, PA->natoms, ts.G, ts.jt, ts.waves, transposed, ts.hdr.as<int>(), ts.tcols.as<int>(),
+            nt, 1, PA->natoms, ts.G, ts.jt, ts.waves, transposed, ts.hdr.as<int>(), ts.tcols,
             PA->rowptr.as<int>(), PA->cols.as<int>(), PA->tmap.as<int>(), PB->rowptr.as<int>(), PB->cols.as<int>(),
-            PB->tmap.as<int>(), ec.nent.as<int64_t>(), tri, tri + 1, nullptr, nullptr);
-        k_pad_counts<<<(unsigned)((nt + 127) / 128), 128, 0, st>>>(nt, 1, ec.nent.as<int64_t>());
+            PB->tmap.as<int>(), ec.nent, tri, tri + 1, nullptr, nullptr);
+        k_pad_counts<<<(unsigned)((nt + 127) / 128), 128, 0, st>>>(nt, 1, ec.nent);
         int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars + kHostCounts);
         k_plan_totals<<<1, kTotalLanes, 0, st>>>(tri, reinterpret_cast<unsigned long long *>(host) + 1);
-        k_scan64<<<1, 1024, 0, st>>>(nt, ec.nent.as<int64_t>(), ec.ebeg.as<int64_t>(), host);
-        k_tile_ebeg<<<(unsigned)((nt + 1 + 127) / 128), 128, 0, st>>>(nt, 1, ec.ebeg.as<int64_t>(),
+        k_scan64<<<1, 1024, 0, st>>>(nt, ec.nent, ec.ebeg, host, nullptr);
+        k_tile_ebeg<<<(unsigned)((nt + 1 + 127) / 128), 128, 0, st>>>(nt, 1, ec.ebeg,
                                                                       plan->ebeg.as<int64_t>());
         BSM_HIP_TRY(hipStreamSynchronize(st));
         ec.ne = host[0];
@@ -1114,12 +1114,12 @@ void fill_entries(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *PB
     plan->ent = DevBuf(ctx, sizeof(int) * (size_t)((ne + kSpareEntries) * es));
     BSM_HIP_TRY(hipMemsetAsync(plan->ent.as<int>() + ne * es, 0xff, sizeof(int) * kSpareEntries * es, st));
     if (nt > 0) {
-        k_tile_order<<<ts.ng, 256, 0, st>>>(ts.ng, plan->span, ts.ntile.as<int>(), ts.toff.as<int64_t>(),
+        k_tile_order<<<ts.ng, 256, 0, st>>>(ts.ng, plan->span, ts.ntile, ts.toff,
                                             plan->order.as<int>());
         k_tile_entries<1><<<tile_grid(nt), kPlanThreads, 0, st>>>(
-            nt, 1, PA->natoms, ts.G, ts.jt, ts.waves, transposed, ts.hdr.as<int>(), ts.tcols.as<int>(),
+            nt, 1, PA->natoms, ts.G, ts.jt, ts.waves, transposed, ts.hdr.as<int>(), ts.tcols,
             PA->rowptr.as<int>(), PA->cols.as<int>(), PA->tmap.as<int>(), PB->rowptr.as<int>(), PB->cols.as<int>(),
-            PB->tmap.as<int>(), nullptr, nullptr, nullptr, ec.ebeg.as<int64_t>(), plan->ent.as<int>());
+            PB->tmap.as<int>(), nullptr, nullptr, nullptr, ec.ebeg, plan->ent.as<int>());
         if (transposed)   // outputs go to the slot of (j, i)
             k_map_cslots<<<(unsigned)((nt + 127) / 128), 128, 0, st>>>(nt, ts.G, ts.jt, PC->tmap.as<int>(),
                                                                        ts.hdr.as<int>());
@@ -1162,12 +1162,14 @@ static int64_t tiles_of_8(Context *ctx, const bsm_pattern_s *PC)
     if (PC->tiles8 >= 0) return PC->tiles8;
     hipStream_t st = ctx->stream;
     const int ng = (PC->natoms + 7) / 8;
-    DevBuf ntile(ctx, sizeof(int) * ng), ntile64(ctx, sizeof(int64_t) * ng), toff(ctx, sizeof(int64_t) * (ng + 1));
+    DevBuf buf(ctx, Cut::room(sizeof(int) * ng) + Cut::room(sizeof(int64_t) * (ng + 1)));
+    Cut cut{buf.as<char>()};
+    int *ntile = cut.take<int>(ng);
+    int64_t *toff = cut.take<int64_t>(ng + 1);
     k_group_union<<<ng, kPlanThreads, 0, st>>>(PC->natoms, 8, PC->rowptr.as<int>(), PC->cols.as<int>(), 64 / PC->b,
-                                               ntile.as<int>());
-    k_int_to_i64<<<(ng + 255) / 256, 256, 0, st>>>(ng, ntile.as<int>(), ntile64.as<int64_t>());
+                                               ntile);
     int64_t *host = reinterpret_cast<int64_t *>(ctx->host_scalars + kHostCounts);
-    k_scan64<<<1, 1024, 0, st>>>(ng, ntile64.as<int64_t>(), toff.as<int64_t>(), host);
+    k_scan64<<<1, 1024, 0, st>>>(ng, nullptr, toff, host, ntile);
     BSM_HIP_TRY(hipStreamSynchronize(st));
     return PC->tiles8 = *host;
 }
