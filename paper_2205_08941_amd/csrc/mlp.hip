@@ -821,14 +821,8 @@ struct bsm_mlp_s {
     int M = 0;
     int64_t P = 0;
     DevBuf prm, m, v, grad, gpart, lpart, loss, acts, pk1, pk2, pk3;
-    double *host_loss = nullptr;   // pinned: the loss of a gradient call, written by its last kernel
     bool packed = false;
     int64_t t = 0;   // Adam steps taken
-
-    ~bsm_mlp_s()
-    {
-        if (host_loss) (void)hipHostFree(host_loss);
-    }
 
     int nt3() const { return (M + 15) / 16; }
 
@@ -955,7 +949,6 @@ int bsm_mlp_create(bsm_ctx ctx, const bsm_mlp_shape *shape, const float *params,
     net->lpart = DevBuf(c, sizeof(double) * (kGradChunk / kGS));
     net->acts = DevBuf(c, sizeof(float) * (size_t)kGradChunk * (4 * kH + pad32(net->M)));
     net->loss = DevBuf(c, sizeof(double) * 2);
-    BSM_HIP_TRY(hipHostMalloc((void **)&net->host_loss, sizeof(double), hipHostMallocDefault));
     net->pk1 = DevBuf(c, sizeof(unsigned short) * kKT1 * 8 * 256);
     net->pk2 = DevBuf(c, sizeof(unsigned short) * 8 * 8 * 256);
     net->pk3 = DevBuf(c, sizeof(unsigned short) * 8 * (size_t)net->nt3() * 256);
@@ -1042,9 +1035,10 @@ int bsm_mlp_loss_grad(bsm_mlp net, int64_t n, const float *X, const float *T, do
 {
     MLP_TRY
     BSM_REQUIRE(net && X && T && grad && n >= 1, BSM_EINVAL, "bad argument");
-    net->loss_grad(n, X, nullptr, T, 0.5 / (double)n, 0, grad, net->host_loss);
+    double *host = net->c->host_scalars;   // pinned
+    net->loss_grad(n, X, nullptr, T, 0.5 / (double)n, 0, grad, host);
     BSM_HIP_TRY(hipStreamSynchronize(net->c->stream));
-    if (loss) *loss = *net->host_loss;
+    if (loss) *loss = *host;
     return BSM_OK;
     MLP_CATCH
 }
