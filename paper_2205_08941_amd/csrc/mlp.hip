@@ -820,7 +820,7 @@ struct bsm_mlp_s {
     Context *c = nullptr;
     int M = 0;
     int64_t P = 0;
-    DevBuf prm, m, v, grad, gpart, lpart, loss, acts, pk1, pk2, pk3;
+    DevBuf prm, m, v, grad, work, lpart, loss, pk1, pk2, pk3;   // work: activations, then partial gradients
     bool packed = false;
     int64_t t = 0;   // Adam steps taken
 
@@ -869,7 +869,7 @@ struct bsm_mlp_s {
     {
         hipStream_t st = c->stream;
         const int MP = pad32(M);
-        float *x = acts.as<float>();
+        float *x = work.as<float>(), *gpart = x + (int64_t)kGradChunk * (4 * kH + MP);
         const Acts a{x, x + (int64_t)kGradChunk * kH, x + (int64_t)kGradChunk * 2 * kH, x + (int64_t)kGradChunk * 3 * kH,
                      x + (int64_t)kGradChunk * 4 * kH};
         int splits = 0, lparts = 0;
@@ -886,9 +886,9 @@ struct bsm_mlp_s {
             k_mlp_backprop<<<(unsigned)tiles, kNT, 0, st>>>(prm.as<float>(), M, MP, cnt, Xc, ic, Tc, (float)(1.0 / (double)n), a,
                                                  s0 > 0, lpart.as<double>());
             k_mlp_wgrad<<<dim3(16 + 4 * (MP / 32) + 4, splits), 64, 0, st>>>(M, MP, cnt, Xc, ic, a, s0 > 0,
-                                                                             gpart.as<float>());
+                                                                             gpart);
         }
-        k_sum_gradient<<<grid_for(P, 256) + 1, 256, 0, st>>>(P, splits, gpart.as<float>(), g, lparts,
+        k_sum_gradient<<<grid_for(P, 256) + 1, 256, 0, st>>>(P, splits, gpart, g, lparts,
                                                              lpart.as<double>(), scale, accumulate, loss_out);
         BSM_HIP_TRY(hipGetLastError());
     }
@@ -945,9 +945,8 @@ int bsm_mlp_create(bsm_ctx ctx, const bsm_mlp_shape *shape, const float *params,
     net->m = DevBuf(c, pb);
     net->v = DevBuf(c, pb);
     net->grad = DevBuf(c, pb);
-    net->gpart = DevBuf(c, pb * kSplits);
+    net->work = DevBuf(c, sizeof(float) * (size_t)kGradChunk * (4 * kH + pad32(net->M)) + pb * kSplits);
     net->lpart = DevBuf(c, sizeof(double) * (kGradChunk / kGS));
-    net->acts = DevBuf(c, sizeof(float) * (size_t)kGradChunk * (4 * kH + pad32(net->M)));
     net->loss = DevBuf(c, sizeof(double) * 2);
     net->pk1 = DevBuf(c, sizeof(unsigned short) * kKT1 * 8 * 256);
     net->pk2 = DevBuf(c, sizeof(unsigned short) * 8 * 8 * 256);
