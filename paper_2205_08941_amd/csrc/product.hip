@@ -1181,10 +1181,19 @@ static int64_t tiles_of_8(Context *ctx, const bsm_pattern_s *PC)
 // b = 9 and as many with b = 4, this line is within 2.3% and 0.4% of the best choice in the mean,
 // always 8 rows 46% and 51% slower; 64 atoms, b = 9, 8 A: 124 us with 8 rows, 44 with two;
 // 512 atoms, 8 A x 6 A -> 14 A: 276 with 8, 232 with four; 1000 atoms, 16 A: 20.2 ms with 8, 22.3 with four.
-static int ring_rows(Context *ctx, const bsm_pattern_s *PC)
+// Where all three patterns are narrow (mean rows of at most 128 blocks with b = 9, 64 with b = 4: 8 and
+// 6 A of silicon) the lists of k are short, a tile's start and end weigh more, and narrower tiles win at
+// every count: 1728 atoms, b = 9, 8 A, 706 us with four rows, 617 with two; 4096 atoms, 6 A, 426 with 8,
+// 346 with two; 8000 atoms, 8 A, 2979 with 8, 2700 with four; b = 4, 4096 atoms, 6 A, 93 with 8, 75 with
+// four.  A wide operand takes that back: 4096 atoms, b = 9, 10 A x 8 A -> 8 A, 1970 with two, 1826 with
+// four, 1813 with 8; b = 4, 13824 atoms, 8 A x 6 A -> 8 A, 428 with four, 356 with 8.
+static int ring_rows(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC)
 {
     const int64_t nt = tiles_of_8(ctx, PC);
-    return nt < 1600 ? 2 : nt < (PC->b == 9 ? 4000 : 2500) ? 4 : 8;
+    const int64_t widest = std::max({PA->nnzb, PB->nnzb, PC->nnzb});
+    if (nt < 1600) return 2;
+    if (widest <= (PC->b == 9 ? 128 : 64) * (int64_t)PC->natoms) return PC->b == 9 && nt < 8000 ? 2 : 4;
+    return nt < (PC->b == 9 ? 4000 : 2500) ? 4 : 8;
 }
 
 // Rows of a paired launch's plan: its tiles take them twice.
@@ -1498,7 +1507,7 @@ Plan *get_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, con
     }
     int G = variant == 2 ? kMaxRows : (ctx->rows_per_wave > 0 ? ctx->rows_per_wave : default_rows_per_wave(C->b));
     if ((variant == 4 || variant == 5 || variant == 6) && (C->b == 4 || C->b == 9) && ctx->rows_per_wave == 0)
-        G = variant == 4 && !(prec == BSM_BF16 && C->b == 9 && A == B) ? ring_rows(ctx, C) : 8;
+        G = variant == 4 && !(prec == BSM_BF16 && C->b == 9 && A == B) ? ring_rows(ctx, A, B, C) : 8;
     if ((variant == 5 || variant == 6) && G < 4) G = 4;   // two-wave and matrix-core tiles take 4 or 8 rows
     if (variant == 4 && C->b == 9 && A == B && ctx->column_order == 1) {
         // BF16 products of this class run on the matrix cores, which sum an entry pair by pair:
