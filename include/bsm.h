@@ -168,8 +168,8 @@ int bsm_ctx_set_group_span(bsm_ctx ctx, int span);
  * the columns grouped by the set of the group's rows that hold an output in them.  For
  * finite operands FP64 and FP32 products are equal under both orders (each
  * element sums the same nonzero terms in ascending k); BF16 matrix-core products
- * pair entries differently and may differ in rounding (under order 1 they keep the
- * row-set runs, on a plan of their own while device memory for it is easily spared).  order must be 0 or 1.  Clears cached plans (destroy batches first). */
+ * pair entries differently and may differ in rounding.  order must be 0 or 1.
+ * Clears cached plans (destroy batches first). */
 int bsm_ctx_set_column_order(bsm_ctx ctx, int order);
 
 /* Transposed plans for the default product kernel (variant 4, 2, 4 or 8 rows per

@@ -106,8 +106,8 @@ class Context {
     int column_order = 1;       // tile columns: 0 ascending, 1 grouped by the rows they hold outputs for
     // derived patterns (same atoms, another cutoff), owned here, keyed by (source id, cutoff)
     std::map<std::pair<uint64_t, double>, bsm_pattern_s *> derived;
-    // (A, B, C, variant, rows, transposed plans allowed, tiles in runs of the column order)
-    std::map<std::tuple<uint64_t, uint64_t, uint64_t, int, int, int, int>, std::unique_ptr<Plan>> plans;
+    // (A, B, C, variant, rows, transposed plans allowed)
+    std::map<std::tuple<uint64_t, uint64_t, uint64_t, int, int, int>, std::unique_ptr<Plan>> plans;
     int transposed_plans = 1;   // 0 never, 1 when estimated cheaper, 2 whenever allowed
     // reduction scratch
     DevBuf red_partials;        // double[kRedBlocks * kRedSlots]
@@ -195,7 +195,7 @@ Plan *get_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, con
 // rings, 5: rings with tiles shared by two waves, 6: ring tiles on the FP64 matrix cores) and rows
 // per tile; transposed plans only where allowed (variant 4 launches).
 Plan *get_plan_kind(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C,
-                    int variant, int G, bool allow_transposed = false, bool sets = false);
+                    int variant, int G, bool allow_transposed = false);
 
 // ---------------------------------------------------------------- launches
 void launch_product_f64(Context *ctx, const Plan *plan, double alpha, const bsm_pattern_s *PA,

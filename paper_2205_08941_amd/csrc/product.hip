@@ -1200,13 +1200,13 @@ static int ring_rows(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s 
 static int pair_rows(Context *ctx, const bsm_pattern_s *PC) { return tiles_of_8(ctx, PC) < 1600 ? 2 : 4; }
 
 static Plan *find_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C, int variant,
-                       int G, int transposed, int sets)
+                       int G, int transposed)
 {
-    auto it = ctx->plans.find(std::make_tuple(A->id, B->id, C->id, variant, G, transposed, sets));
+    auto it = ctx->plans.find(std::make_tuple(A->id, B->id, C->id, variant, G, transposed));
     return it == ctx->plans.end() ? nullptr : it->second.get();
 }
 
-// A second plan beside the class's default one: a paired launch's 4-row plan, estimated from the class's default plan (about 1.3 times its
+// A second plan beside the class's default one: a paired launch's plan, estimated from the class's default plan (about 1.3 times its
 // size), fits when free device memory holds twice the estimate and a quarter of the device more.
 static bool pair_plan_fits(Context *ctx, const Plan *one)
 {
@@ -1223,7 +1223,7 @@ Plan *get_pair_plan(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *
     if (ctx->product_variant >= 0 && ctx->product_variant != 4) return nullptr;
     // direct ring plan of half the paired tile's rows
     const int G = pair_rows(ctx, PC);
-    if (Plan *p = find_plan(ctx, PA, PB, PC, 4, G, 0, 0)) return p;
+    if (Plan *p = find_plan(ctx, PA, PB, PC, 4, G, 0)) return p;
     // The 4-row plan is a second plan beside the default one (about 1.3 times its size, 4.9 GB
     // for the 16 A class at 4096 atoms, eight times that at 32768): built only while free
     // device memory holds twice that and a quarter of the device besides (room for what the
@@ -1297,7 +1297,7 @@ Plan *get_pair_plan_a(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s
     if (ctx->product_variant >= 0 && ctx->product_variant != 4) return nullptr;
     // transposed ring plan: the tiles' rows walk B and B2, the shared A is the copied operand
     const int G = pair_rows(ctx, PC);
-    if (Plan *p = find_plan(ctx, PA, PB, PC, 4, G, 2, 0)) return p;
+    if (Plan *p = find_plan(ctx, PA, PB, PC, 4, G, 2)) return p;
     if (!pair_plan_fits(ctx, get_plan(ctx, PA, PB, PC))) return nullptr;
     return get_transposed_plan(ctx, PA, PB, PC, G);
 }
@@ -1441,17 +1441,16 @@ static bool cluster_pays(const bsm_pattern_s *PA, const bsm_pattern_s *PB, const
 }
 
 // direct, transposed, or (both) the one with the smaller estimated cost: both are
-// counted, one is written.  sets: tiles are runs of the context's column order.
+// counted, one is written.
 static std::unique_ptr<Plan> new_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B,
-                                      const bsm_pattern_s *C, int variant, int G, bool direct, bool transposed,
-                                      bool sets)
+                                      const bsm_pattern_s *C, int variant, int G, bool direct, bool transposed)
 {
     TileSet tiles[2];   // plain, clustered
     std::unique_ptr<Plan> plan;
     EntryCount ec;
     TileSet *used = nullptr;
     for (int tr = direct ? 0 : 1; tr <= (transposed ? 1 : 0); ++tr) {
-        const bool near = !sets && variant == 4 && ctx->column_order == 1 && (tr ? cluster_pays(B, A, C) : cluster_pays(A, B, C));
+        const bool near = variant == 4 && ctx->column_order == 1 && (tr ? cluster_pays(B, A, C) : cluster_pays(A, B, C));
         TileSet &ts = tiles[near ? 1 : 0];
         if (ts.G == 0) make_tiles(ctx, C, G, variant == 5 ? 2 : 1, near, ts);
         std::unique_ptr<Plan> p = named_plan(A, B, C, variant);
@@ -1468,27 +1467,27 @@ static std::unique_ptr<Plan> new_plan(Context *ctx, const bsm_pattern_s *A, cons
 
 Plan *get_transposed_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C, int G)
 {
-    auto key = std::make_tuple(A->id, B->id, C->id, 4, G, 2, 0);
+    auto key = std::make_tuple(A->id, B->id, C->id, 4, G, 2);
     auto it = ctx->plans.find(key);
     if (it != ctx->plans.end()) return it->second.get();
-    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, 4, G, false, true, false);
+    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, 4, G, false, true);
     Plan *raw = plan.get();
     ctx->plans[key] = std::move(plan);
     return raw;
 }
 
 Plan *get_plan_kind(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C,
-                    int variant, int G, bool allow_transposed, bool sets)
+                    int variant, int G, bool allow_transposed)
 {
     // C = (B^T A^T)^T is an option for the default ring kernel when A and B lie on
     // different patterns (all patterns are symmetric): a wide A times a narrow B
     // then walks the narrow pattern, with far fewer idle lanes
     const bool try_t = allow_transposed && ctx->transposed_plans > 0 && variant == 4 && G <= 8 &&
                        (C->b == 4 || C->b == 9 || any_b_ring(C->b)) && A->id != B->id;
-    auto key = std::make_tuple(A->id, B->id, C->id, variant, G, try_t ? 1 : 0, sets ? 1 : 0);
+    auto key = std::make_tuple(A->id, B->id, C->id, variant, G, try_t ? 1 : 0);
     auto it = ctx->plans.find(key);
     if (it != ctx->plans.end()) return it->second.get();
-    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, variant, G, !(try_t && ctx->transposed_plans == 2), try_t, sets);
+    std::unique_ptr<Plan> plan = new_plan(ctx, A, B, C, variant, G, !(try_t && ctx->transposed_plans == 2), try_t);
     Plan *raw = plan.get();
     ctx->plans[key] = std::move(plan);
     return raw;
@@ -1509,16 +1508,6 @@ Plan *get_plan(Context *ctx, const bsm_pattern_s *A, const bsm_pattern_s *B, con
     if ((variant == 4 || variant == 5 || variant == 6) && (C->b == 4 || C->b == 9) && ctx->rows_per_wave == 0)
         G = variant == 4 && !(prec == BSM_BF16 && C->b == 9 && A == B) ? ring_rows(ctx, A, B, C) : 8;
     if ((variant == 5 || variant == 6) && G < 4) G = 4;   // two-wave and matrix-core tiles take 4 or 8 rows
-    if (variant == 4 && C->b == 9 && A == B && ctx->column_order == 1) {
-        // BF16 products of this class run on the matrix cores, which sum an entry pair by pair:
-        // they keep the row-set order's entries.  Two plans of one class stand side by side only
-        // while the second's memory is easily spared; else the one that is there serves both.
-        const int sets = prec == BSM_BF16 ? 1 : 0;
-        if (Plan *own = find_plan(ctx, A, B, C, variant, G, 0, sets)) return own;
-        Plan *other = find_plan(ctx, A, B, C, variant, G, 0, 1 - sets);
-        if (other && !pair_plan_fits(ctx, other)) return other;
-        return get_plan_kind(ctx, A, B, C, variant, G, false, sets != 0);
-    }
     return get_plan_kind(ctx, A, B, C, variant, G, true);
 }
 
