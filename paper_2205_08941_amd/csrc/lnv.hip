@@ -96,6 +96,13 @@ struct LineMin {
     double c[4], a, delta;
     int status;
 };
+// 2 (3 x - 2 y): E of Tr XY and Tr WY, N of Tr XX and Tr WX, the same for the device, which takes no
+// step where it is not finite, and the host, which says so.
+__host__ __device__ inline double twice_mcweeny(double x, double y)
+{
+#pragma clang fp contract(off)
+    return 2.0 * (3.0 * x - 2.0 * y);
+}
 __host__ __device__ inline void line_minimum(const double *sc, int mode, double mu0, double n_electrons, LineMin &o)
 {
 #pragma clang fp contract(off)
@@ -107,8 +114,8 @@ __host__ __device__ inline void line_minimum(const double *sc, int mode, double 
     const double kk[4] = {tr0[3], tr[10] + tr[11], tr[12] + tr[13], tr[14]};
     double nn[4];
     for (int m = 0; m < 4; ++m) {
-        const double e = 2.0 * (3.0 * f[m] - 2.0 * gg[m]);
-        nn[m] = 2.0 * (3.0 * h[m] - 2.0 * kk[m]);
+        const double e = twice_mcweeny(f[m], gg[m]);
+        nn[m] = twice_mcweeny(h[m], kk[m]);
         o.c[m] = e - mu * nn[m];
     }
     o.a = o.delta = 0.0;
@@ -131,7 +138,7 @@ __global__ void k_line_minimum(double *sc, int mode, double mu, double n_electro
     line_minimum(sc, mode, mu, n_electrons, o);
     // no step from an energy or electron count that is not finite either
     const double *t = sc + kCgEnergy;
-    const bool finite = isfinite(3.0 * t[0] - 2.0 * t[1]) && isfinite(3.0 * t[2] - 2.0 * t[3]);
+    const bool finite = isfinite(twice_mcweeny(t[0], t[1])) && isfinite(twice_mcweeny(t[2], t[3]));
     const double v[3] = {o.a, o.delta, finite ? (double)o.status : 1.0};
     for (int k = 0; k < 3; ++k) host[k] = sc[kCgMin + k] = v[k];
 }
@@ -496,12 +503,12 @@ int lnv_state_s::step(lnv_result *res)
         cg_update(c, PL, sc + kCgMin, D.d(), PN.d(), st->L);   // nothing where the line has no minimum
         BSM_HIP_TRY(hipStreamSynchronize(c->stream));
 
-        const double E = 2.0 * (3.0 * h[0] - 2.0 * h[1]);
-        const double N = 2.0 * (3.0 * h[2] - 2.0 * h[3]);
+        const double E = twice_mcweeny(h[0], h[1]);
+        const double N = twice_mcweeny(h[2], h[3]);
         res->E = E;
         res->N = N;
         res->mu = st->mu;
-        if (!(std::isfinite(E) && std::isfinite(N))) {   // the polynomials have no minimum then: L is as it was
+        if (!(std::isfinite(E) && std::isfinite(N))) {   // no step was taken: L is as it was
             res->status = BSM_ENONFINITE;
             res->Omega = NAN;
             res->dE = NAN;
