@@ -155,8 +155,8 @@ int bsm_ctx_set_product_variant(bsm_ctx ctx, int variant);
 /* Launch order of product tiles in plans built from now on: tiles of `span`
  * consecutive row groups are interleaved by column position (1 = group by
  * group), so that groups over similar columns share B blocks in L2.
- * 1 <= span <= 4096 (until set: 4, or 1 where four groups' A blocks overflow an L2).
- * Clears cached plans. */
+ * 1 <= span <= 4096; 0 restores the default: 4, or 1 where four groups' A blocks
+ * overflow an L2.  Clears cached plans. */
 int bsm_ctx_set_group_span(bsm_ctx ctx, int span);
 
 /* Columns of the tiles of product plans built from now on.  Each group of

@@ -269,7 +269,7 @@ class Context:
         _check(_lib.bsm_ctx_set_product_variant(self.handle, int(variant)))
 
     def set_group_span(self, span: int) -> None:
-        """Row groups interleaved by column position in the product launch order."""
+        """Row groups interleaved by column position in the product launch order (0 = default)."""
         _check(_lib.bsm_ctx_set_group_span(self.handle, int(span)))
 
     def set_column_order(self, order: int) -> None:

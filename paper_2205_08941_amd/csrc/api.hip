@@ -248,7 +248,7 @@ int bsm_ctx_set_group_span(bsm_ctx ctx, int span)
 {
     BSM_API_BEGIN
     BSM_REQUIRE(ctx != nullptr, BSM_EINVAL, "ctx is NULL");
-    BSM_REQUIRE(span >= 1 && span <= 4096, BSM_EINVAL, "span must be in 1..4096");
+    BSM_REQUIRE(span >= 0 && span <= 4096, BSM_EINVAL, "span must be in 0..4096");
     BSM_HIP_TRY(hipStreamSynchronize(ctx->c.stream));
     ctx->c.retire_profile([](const Plan *) { return true; });
     ctx->c.plans.clear();
