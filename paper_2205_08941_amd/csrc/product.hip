@@ -245,6 +245,7 @@ __device__ inline void plan_sync() { __syncthreads(); }
 __device__ inline int plan_place(int64_t item);   // where an item's totals go
 __device__ inline void plan_or(unsigned *p, unsigned v) { atomicOr(p, v); }
 __device__ inline void plan_or(unsigned long long *p, unsigned long long v) { atomicOr(p, v); }
+__device__ inline void plan_min(int *p, int v) { atomicMin(p, v); }
 // exclusive sum over the workgroup's threads, and the total; every thread calls it
 __device__ inline unsigned plan_scan(unsigned v, unsigned &total)
 {
@@ -275,6 +276,7 @@ inline void plan_sync() {}
 inline int plan_place(int64_t) { return 0; }
 inline void plan_or(unsigned *p, unsigned v) { *p |= v; }
 inline void plan_or(unsigned long long *p, unsigned long long v) { *p |= v; }
+inline void plan_min(int *p, int v) { *p = min(*p, v); }
 inline unsigned plan_scan(unsigned v, unsigned &total)
 {
     total = v;
@@ -302,6 +304,20 @@ __device__ inline void union_bits(unsigned *bits, int words, int k0, int lo, int
     plan_sync();
 }
 
+// First and last column of a group's rows of P_C (no row is empty: its diagonal is there).
+// Windows span these only: over all atoms, each of a long system's groups would clear and scan
+// words for every atom of it.
+__device__ inline void group_reach(const int *__restrict__ rpC, const int *__restrict__ cC, int i0, int gr, int &first,
+                                   int &last)
+{
+    first = 0x7fffffff;
+    last = 0;
+    for (int a = 0; a < gr; ++a) {
+        first = min(first, cC[rpC[i0 + a]]);
+        last = max(last, cC[rpC[i0 + a + 1] - 1]);
+    }
+}
+
 // One workgroup per row group: tiles that the union of the group's rows of P_C takes.
 __global__ __launch_bounds__(kPlanThreads) void k_group_union(int n, int G, const int *__restrict__ rpC,
                                                               const int *__restrict__ cC, int jt,
@@ -311,10 +327,12 @@ __global__ __launch_bounds__(kPlanThreads) void k_group_union(int n, int G, cons
     const int g = blockIdx.x;
     const int i0 = g * G, gr = min(G, n - i0);
     const int lo = rpC[i0], hi = rpC[i0 + gr];   // the group's rows follow each other
+    int first, last;
+    group_reach(rpC, cC, i0, gr, first, last);
     unsigned cnt = 0;
-    for (int k0 = 0; k0 < n; k0 += 32 * kUnionWords) {
-        const int words = min(kUnionWords, (n - k0 + 31) / 32);
-        union_bits(bits, words, k0, lo, hi, cC);
+    for (int64_t k0 = first; k0 <= last; k0 += 32 * kUnionWords) {
+        const int words = (int)min((int64_t)kUnionWords, (last - k0) / 32 + 1);
+        union_bits(bits, words, (int)k0, lo, hi, cC);
         for (int w = threadIdx.x; w < words; w += blockDim.x) cnt += __popc(bits[w]);
         plan_sync();
     }
@@ -341,7 +359,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_group_tiles(int n, int G, int 
                                                               int *__restrict__ hdr, int *__restrict__ tcols,
                                                               int *__restrict__ scr)
 {
-    BSM_PLAN_SHARED unsigned bits[kUnionWords], first[kUnionWords];
+    BSM_PLAN_SHARED unsigned bits[kUnionWords], rank[kUnionWords];
     BSM_PLAN_SHARED unsigned hist[16 * kPlanThreads];
     const int g = blockIdx.x, t = threadIdx.x, nt = blockDim.x;
     const int hs = G + G * jt;
@@ -353,16 +371,18 @@ __global__ __launch_bounds__(kPlanThreads) void k_group_tiles(int n, int G, int 
         *x1 = scr + 4 * cap + o, *sl = scr + 5 * cap + o * G;
     for (int64_t e = t; e < (int64_t)room * G; e += nt) sl[e] = -1;
     // the union's columns in ascending order, and every (column, row)'s C slot
+    int first, last;
+    group_reach(rpC, cC, i0, gr, first, last);
     unsigned cnt = 0;
-    for (int k0 = 0; k0 < n; k0 += 32 * kUnionWords) {
-        const int words = min(kUnionWords, (n - k0 + 31) / 32);
+    for (int64_t kw = first; kw <= last; kw += 32 * kUnionWords) {
+        const int k0 = (int)kw, words = (int)min((int64_t)kUnionWords, (last - kw) / 32 + 1);
         union_bits(bits, words, k0, lo, hi, cC);
         const int per = (words + nt - 1) / nt, w0 = min(words, t * per), w1 = min(words, w0 + per);
         unsigned mine = 0, total;
         for (int w = w0; w < w1; ++w) mine += __popc(bits[w]);
         unsigned run = cnt + plan_scan(mine, total);
         for (int w = w0; w < w1; ++w) {
-            first[w] = run;
+            rank[w] = run;
             run += __popc(bits[w]);
         }
         plan_sync();
@@ -371,7 +391,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_group_tiles(int n, int G, int 
             if (d < 0 || d >= 32 * words) continue;
             int a = 0;
             while (p >= rpC[i0 + a + 1]) ++a;
-            const int u = (int)(first[d >> 5] + __popc(bits[d >> 5] & ((1u << (d & 31)) - 1u)));
+            const int u = (int)(rank[d >> 5] + __popc(bits[d >> 5] & ((1u << (d & 31)) - 1u)));
             col[u] = k;
             sl[(int64_t)u * G + a] = p;
         }
@@ -435,7 +455,12 @@ __global__ __launch_bounds__(kPlanThreads) void k_group_tiles(int n, int G, int 
 // chunk writes the padding entry that makes the tile's count even (its count
 // includes it, k_pad_counts).  Each window of kEntryWindow atoms is held as two
 // masks per k, the rows a with (i_a, k) in P_A and the columns x with (k, j_x) in
-// P_B, filled from the tile's G + jt pattern rows, 64 threads to a row.  An A row
+// P_B, filled from the tile's G + jt pattern rows, 64 threads to a row.  A window
+// starts at the first k that a row still reaches, and the last is the last that
+// both A rows and B columns reach: over all windows of a long system, a tile that
+// reaches a few of them spent its time in empty ones (plan and product, 327680
+// atoms, b = 2, 4 A: 337 -> 9.5 ms; 110592 atoms, b = 4, 6 A: 89 -> 9.8 ms; 16 A of
+// 4096 atoms, whose tiles reach every window, 11.18 and 11.32).  An A row
 // (B column) of an entry with no live triple would only meet zero blocks or
 // outputs outside P_C: it is dropped, so that the kernels neither copy nor
 // multiply it.  W = 2 (tiles shared by two waves): each entry is two halves, one
@@ -455,6 +480,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_entries(
     BSM_PLAN_SHARED int eidx[MODE == 1 ? kEntryWindow : 1];
     BSM_PLAN_SHARED int beg[kRows], end[kRows], nxt[kRows];
     BSM_PLAN_SHARED unsigned long long cmask[kMaxRows];    // columns with an output in row a
+    BSM_PLAN_SHARED int reach[2][2];                       // first k of the A rows, of the B columns: now, next
     const int64_t tc = plan_item();
     if (tc >= ntiles * nch) return;
     const int64_t t = tc / nch;
@@ -462,6 +488,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_entries(
     const int k0 = (int)((int64_t)c * natoms / nch), k1 = (int)((int64_t)(c + 1) * natoms / nch);
     const int hs = G + G * jt, es = W * G + jt, jh = jt / W, nr = G + jt;
     const int *h = hdr + t * hs;
+    const bool one = k1 - k0 <= kEntryWindow;   // one window: nothing to skip
     const int tid = threadIdx.x, nt = blockDim.x;
     const int sub = nt >= 64 ? 64 : nt, lane = tid % sub, grp = tid / sub, ngrp = nt / sub;
     for (int r = tid; r < nr; r += nt) {
@@ -480,6 +507,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_entries(
         beg[r] = lo;
         end[r] = e;
     }
+    if (tid == 0) reach[0][0] = reach[0][1] = one ? k0 : k1;
     for (int a = tid; a < G; a += nt) {
         unsigned long long m = 0;
         for (int x = 0; x < jt; ++x)
@@ -490,12 +518,20 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_entries(
     const unsigned long long half0 = W == 1 ? ~0ull : (1ull << jh) - 1ull;
     int64_t w = (MODE == 1) ? ebeg[tc] : 0;
     unsigned cnt = 0, tri = 0, rw = 0;
-    for (int kw = k0; kw < k1; kw += kEntryWindow) {
-        const int ke = min(k1, kw + kEntryWindow), len = ke - kw;
+    if (!one) {
+        for (int r = tid; r < nr; r += nt)
+            if (beg[r] < end[r]) plan_min(&reach[0][r < G ? 0 : 1], (r < G ? cA : cB)[beg[r]]);
+        plan_sync();
+    }
+    for (int now = 0;; now ^= 1) {
+        const int ka = reach[now][0], kb = reach[now][1], kw = min(ka, kb);
+        if (max(ka, kb) >= k1) break;   // no k left that both reach
+        const int ke = k1 - kw > kEntryWindow ? kw + kEntryWindow : k1, len = ke - kw;
         for (int d = tid; d < len; d += nt) {
             am[d] = 0u;
             bm[d] = 0ull;
         }
+        if (tid == 0) reach[now ^ 1][0] = reach[now ^ 1][1] = k1;
         plan_sync();
         for (int r = grp; r < nr; r += ngrp) {
             const int *cols = r < G ? cA : cB;
@@ -503,7 +539,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_entries(
             for (int p = b0 + lane; p <= b1; p += sub) {
                 const int k = p < b1 ? cols[p] : 0x7fffffff;
                 if (k >= ke) {   // the first position past the window starts the next one
-                    if (p == b0 || cols[p - 1] < ke) nxt[r] = p;
+                    if (p == b0 || cols[p - 1] < ke) {
+                        nxt[r] = p;
+                        if (k < k1) plan_min(&reach[now ^ 1][r < G ? 0 : 1], k);
+                    }
                     break;
                 }
                 if (r < G) plan_or(&am[k - kw], 1u << r);
