@@ -180,10 +180,14 @@ __device__ inline int find_in_row(const int *__restrict__ rowptr, const int *__r
 }
 
 // One workgroup per chunk of destination slots: look up the source slot, copy or zero.
-// Chunks of 64 slots: 256 left the narrow patterns (6 A at 4096 atoms: 680 chunks) too few
-// workgroups to cover the loads.
-constexpr int kMaskSlots = 64;
-template <int BC>
+// A chunk has to be small where there are few of them, so that workgroups cover the loads (b = 9,
+// onto 4096 atoms, 6 A: 26 us with 64 slots, 30 with 256; 216 atoms, 6.4 and 15.9), and large where
+// they are many and their blocks small, as all the threads of a workgroup look a slot up and with 64
+// slots three quarters idle meanwhile (b = 4, onto 4096 atoms, 10 A: 32.7 us with 64, 24.5 with 256;
+// b = 1, 11.9 and 5.8; b = 9, 16 A, 790 and 677).
+constexpr int kFewMaskSlots = 64, kManyMaskSlots = kT;
+inline bool many_mask_slots(int64_t nnz, int b) { return nnz >= (b <= 5 ? 1 << 17 : 1 << 21); }
+template <int BC, int kMaskSlots>
 __global__ __launch_bounds__(kT) void k_mask_copy(int64_t nnzd, int b_arg, const int *__restrict__ rowsD,
                                                   const int *__restrict__ colsD, const int *__restrict__ rpS,
                                                   const int *__restrict__ colsS, const double *__restrict__ src,
@@ -311,12 +315,19 @@ void add_transpose(Context *ctx, const bsm_pattern_s *P, double alpha, const dou
 void mask_copy(Context *ctx, const bsm_pattern_s *Ps, const double *src, const bsm_pattern_s *Pd, double *dst)
 {
     if (Pd->nnzb <= 0) return;
-    auto go = [&](auto kern) {
-        kern<<<(unsigned)((Pd->nnzb + kMaskSlots - 1) / kMaskSlots), kT, 0, ctx->stream>>>(
+    auto go = [&](auto kern, int slots) {
+        kern<<<(unsigned)((Pd->nnzb + slots - 1) / slots), kT, 0, ctx->stream>>>(
             Pd->nnzb, Pd->b, Pd->rowidx.as<int>(), Pd->cols.as<int>(), Ps->rowptr.as<int>(), Ps->cols.as<int>(), src,
             dst);
     };
-    Pd->b == 9 ? go(k_mask_copy<9>) : Pd->b == 4 ? go(k_mask_copy<4>) : go(k_mask_copy<0>);
+    auto block = [&](auto BC) {
+        constexpr int bc = decltype(BC)::value;
+        many_mask_slots(Pd->nnzb, Pd->b) ? go(k_mask_copy<bc, kManyMaskSlots>, kManyMaskSlots)
+                                         : go(k_mask_copy<bc, kFewMaskSlots>, kFewMaskSlots);
+    };
+    if (Pd->b == 9) block(std::integral_constant<int, 9>{});
+    else if (Pd->b == 4) block(std::integral_constant<int, 4>{});
+    else block(std::integral_constant<int, 0>{});
     BSM_HIP_TRY(hipGetLastError());
 }
 
