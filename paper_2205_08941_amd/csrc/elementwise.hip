@@ -17,28 +17,19 @@ __global__ void k_axpby(int64_t n, double a, const double *x, double b, double *
     y[e] = (b == 0.0) ? a * x[e] : fma(b, y[e], a * x[e]);
 }
 
-// The same for 16-byte aligned arrays of an even count: kUnroll pairs per thread, all loads
-// before the stores (each element is the fma above, written out so that both give the same bits).
-constexpr int kUnroll = 4;
+// The same for 16-byte aligned arrays of an even count, a pair per thread (each element is the fma
+// above, written out so that both give the same bits).
 __global__ __launch_bounds__(kT) void k_axpby2(int64_t n2, double a, const double2 *x, double b, double2 *y)
 {
-    const int64_t e0 = (int64_t)blockIdx.x * (kT * kUnroll) + threadIdx.x;
-    double2 xv[kUnroll], yv[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-        const int64_t e = e0 + u * kT;
-        if (e >= n2) continue;
-        xv[u] = x[e];
-        if (b != 0.0) yv[u] = y[e];
+    const int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (e >= n2) return;
+    const double2 xv = x[e];
+    double2 v = make_double2(a * xv.x, a * xv.y);
+    if (b != 0.0) {
+        const double2 yv = y[e];
+        v = make_double2(fma(b, yv.x, v.x), fma(b, yv.y, v.y));
     }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-        const int64_t e = e0 + u * kT;
-        if (e >= n2) continue;
-        double2 v = make_double2(a * xv[u].x, a * xv[u].y);
-        if (b != 0.0) v = make_double2(fma(b, yv[u].x, v.x), fma(b, yv[u].y, v.y));
-        y[e] = v;
-    }
+    y[e] = v;
 }
 
 // z <- a x + b y + c z, one element per thread (x or y may be z).  Each element
@@ -53,29 +44,22 @@ __global__ void k_axpbypcz(int64_t n, double a, const double *x, double b, const
     z[e] = (c == 0.0) ? v : fma(c, z[e], v);
 }
 
-// The same for an even count of 16-byte aligned elements, kUnroll pairs per thread.
+// The same for an even count of 16-byte aligned elements, a pair per thread.
 __global__ __launch_bounds__(kT) void k_axpbypcz2(int64_t n2, double a, const double2 *x, double b, const double2 *y,
                                                   double c, double2 *z)
 {
-    const int64_t e0 = (int64_t)blockIdx.x * (kT * kUnroll) + threadIdx.x;
-    double2 xv[kUnroll], yv[kUnroll], zv[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-        const int64_t e = e0 + u * kT;
-        if (e >= n2) continue;
-        xv[u] = x[e];
-        yv[u] = y[e];
-        if (c != 0.0) zv[u] = z[e];
+    const int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (e >= n2) return;
+    const double2 xv = x[e], yv = y[e];
+    double2 v = make_double2(fma(a, xv.x, b * yv.x), fma(a, xv.y, b * yv.y));
+    if (c != 0.0) {
+        const double2 zv = z[e];
+        v = make_double2(fma(c, zv.x, v.x), fma(c, zv.y, v.y));
     }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-        const int64_t e = e0 + u * kT;
-        if (e >= n2) continue;
-        double2 v = make_double2(fma(a, xv[u].x, b * yv[u].x), fma(a, xv[u].y, b * yv[u].y));
-        if (c != 0.0) v = make_double2(fma(c, zv[u].x, v.x), fma(c, zv[u].y, v.y));
-        z[e] = v;
-    }
+    z[e] = v;
 }
+
+constexpr int kUnroll = 4;   // elements per thread of the kernels below
 
 // In place (M_ij, M_ji) <- ((M_ij + M_ji^T)/2, its transpose).  The thread of
 // element (p, q) of slot s with s < t (or s == t and p <= q) writes both partners.
@@ -253,12 +237,18 @@ static bool pairs_of_16(int64_t n, const double *x, const double *y, const doubl
                            reinterpret_cast<uintptr_t>(z)) % 16 == 0);
 }
 
+// axpby reads pairs, except where it reads y as well and the arrays are far beyond the caches:
+// single elements then stream faster.  b = 9, 10 A, beta != 0: 1000 atoms (128 MB an array) 52.1 us
+// in pairs, 55.3 single; 4096 atoms (522 MB) 267 and 253; beta = 0: 35.7 and 41.0, 170 and 188.
+// (Four pairs a thread with all loads first took 54, 286, 36.8 and 181.)
+constexpr int64_t kSingleElements = 25000000;
+
 void axpby(Context *ctx, int64_t n, double alpha, const double *x, double beta, double *y)
 {
     if (n <= 0) return;
-    if (pairs_of_16(n, x, y, y))
-        k_axpby2<<<grid1((n / 2 + kUnroll - 1) / kUnroll), kT, 0, ctx->stream>>>(
-            n / 2, alpha, reinterpret_cast<const double2 *>(x), beta, reinterpret_cast<double2 *>(y));
+    if (pairs_of_16(n, x, y, y) && (beta == 0.0 || n < kSingleElements))
+        k_axpby2<<<grid1(n / 2), kT, 0, ctx->stream>>>(n / 2, alpha, reinterpret_cast<const double2 *>(x), beta,
+                                                       reinterpret_cast<double2 *>(y));
     else
         k_axpby<<<grid1(n), kT, 0, ctx->stream>>>(n, alpha, x, beta, y);
     BSM_HIP_TRY(hipGetLastError());
@@ -270,7 +260,7 @@ void axpbypcz(Context *ctx, int64_t n, double a, const double *x, double b, cons
     if (n <= 0) return;
     const bool paired = pairs_of_16(n, x, y, z);
     if (paired)
-        k_axpbypcz2<<<grid1((n / 2 + kUnroll - 1) / kUnroll), kT, 0, ctx->stream>>>(n / 2, a, reinterpret_cast<const double2 *>(x), b,
+        k_axpbypcz2<<<grid1(n / 2), kT, 0, ctx->stream>>>(n / 2, a, reinterpret_cast<const double2 *>(x), b,
                                                           reinterpret_cast<const double2 *>(y), c,
                                                           reinterpret_cast<double2 *>(z));
     else
