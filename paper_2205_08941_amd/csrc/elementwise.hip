@@ -63,16 +63,16 @@ constexpr int kUnroll = 4;   // elements per thread of the kernels below
 
 // In place (M_ij, M_ji) <- ((M_ij + M_ji^T)/2, its transpose).  The thread of
 // element (p, q) of slot s with s < t (or s == t and p <= q) writes both partners.
-// Four elements per thread, all loads before the stores.
-template <int BC>
+// U elements per thread, all loads before the stores.
+template <int BC, int U>
 __global__ __launch_bounds__(kT) void k_symmetrize(int64_t nnz, int b_arg, const int *__restrict__ tmap, double *M)
 {
     const int b = BC > 0 ? BC : b_arg, bb = b * b;
-    const int64_t nel = nnz * bb, e0 = (int64_t)blockIdx.x * (kT * kUnroll) + threadIdx.x;
-    int64_t at[kUnroll];
-    double x[kUnroll], y[kUnroll];
+    const int64_t nel = nnz * bb, e0 = (int64_t)blockIdx.x * (kT * U) + threadIdx.x;
+    int64_t at[U];
+    double x[U], y[U];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
+    for (int u = 0; u < U; ++u) {
         const int64_t e = e0 + u * kT;
         at[u] = -1;
         if (e >= nel) continue;
@@ -83,13 +83,13 @@ __global__ __launch_bounds__(kT) void k_symmetrize(int64_t nnz, int b_arg, const
         at[u] = t * bb + q * b + p;
     }
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
+    for (int u = 0; u < U; ++u)
         if (at[u] >= 0) {
             x[u] = M[e0 + u * kT];
             y[u] = M[at[u]];
         }
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
+    for (int u = 0; u < U; ++u)
         if (at[u] >= 0) {
             const double v = 0.5 * (x[u] + y[u]);
             M[e0 + u * kT] = v;
@@ -272,10 +272,21 @@ void symmetrize(Context *ctx, const bsm_pattern_s *P, double *M)
 {
     const int64_t n = nelems(P);
     if (n <= 0) return;
-    auto go = [&](auto kern) {
-        kern<<<grid1((n + kUnroll - 1) / kUnroll), kT, 0, ctx->stream>>>(P->nnzb, P->b, P->tmap.as<int>(), M);
+    auto go = [&](auto kern, int u) {
+        kern<<<grid1((n + u - 1) / u), kT, 0, ctx->stream>>>(P->nnzb, P->b, P->tmap.as<int>(), M);
     };
-    P->b == 9 ? go(k_symmetrize<9>) : P->b == 4 ? go(k_symmetrize<4>) : go(k_symmetrize<0>);
+    // Few elements fill the chip only one to a thread, and so do small blocks, whose threads mostly
+    // end at once.  b = 9: 64 atoms, 8 A, 3.4 us with one, 4.1 with four; 216 atoms, 6 A, 4.7 and
+    // 5.1; 216 atoms, 8 A, 7.7 and 7.8; 512 atoms, 16.2 and 14.3; 4096 atoms, 10 A, 248 and 227;
+    // b = 3, 10 A, 34.0 and 35.7; b = 1, 16 A, 54.7 and 58.8.
+    const bool one = n < (1 << 21) || P->b <= 3;
+    auto block = [&](auto BC) {
+        constexpr int bc = decltype(BC)::value;
+        one ? go(k_symmetrize<bc, 1>, 1) : go(k_symmetrize<bc, kUnroll>, kUnroll);
+    };
+    if (P->b == 9) block(std::integral_constant<int, 9>{});
+    else if (P->b == 4) block(std::integral_constant<int, 4>{});
+    else block(std::integral_constant<int, 0>{});
     BSM_HIP_TRY(hipGetLastError());
 }
 
