@@ -100,14 +100,14 @@ __global__ void k_cell_scatter(int n, const int *__restrict__ cell, const int *_
     cellatoms[cellstart[c] + atomicAdd(&cellfill[c], 1)] = i;
 }
 
-constexpr int kRowsPerGroup = 4;   // atoms (wavefronts) of a workgroup
+constexpr int kNeighborThreads = 256;
 
-// One wavefront per atom: visit the neighbour cells, a lane per atom of a cell, and count
+// L lanes per atom: visit the neighbour cells, a lane per atom of a cell, and count
 // (mode 0) or write (mode 1) the columns j with d^2 < r^2 (and j == i); the rows are sorted
 // afterwards.  A thread per atom walked its cells alone, a chain of dependent loads and
 // divisions: 78 and 96 us for 216 atoms at 8 A, 415 and 452 for 4096 at 10 A, against 6 and 6, 26 and 27.
-template <int MODE>
-__global__ __launch_bounds__(64 * kRowsPerGroup) void k_neighbors(int n, const double *__restrict__ pos, Grid g,
+template <int MODE, int L>
+__global__ __launch_bounds__(kNeighborThreads) void k_neighbors(int n, const double *__restrict__ pos, Grid g,
                                                                   double r2, const int *__restrict__ cell,
                                                                   const int *__restrict__ cellstart,
                                                                   const int *__restrict__ cellatoms,
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(64 * kRowsPerGroup) void k_neighbors(int n, const d
                                                                   const int *__restrict__ rowptr,
                                                                   int *__restrict__ cols)
 {
-    const int i = blockIdx.x * kRowsPerGroup + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = blockIdx.x * (kNeighborThreads / L) + threadIdx.x / L, lane = threadIdx.x % L;
     if (i >= n) return;
     int c = cell[i];
     int cz = c % g.nc[2], cy = (c / g.nc[2]) % g.nc[1], cx = c / (g.nc[2] * g.nc[1]);
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64 * kRowsPerGroup) void k_neighbors(int n, const d
             // what wraps: below 0 the top cells, past the end the bottom ones (never both: noff <= nc)
             const int wl = first < 0 ? g.nc[2] + first : 0, wh = first < 0 ? g.nc[2] : last - hi;
             const int q1 = cellstart[base + wl], n1 = cellstart[base + wh] - q1;
-            for (int x0 = 0; x0 < n0 + n1; x0 += 64) {
+            for (int x0 = 0; x0 < n0 + n1; x0 += L) {
                 const int x = x0 + lane;
                 bool near = false;
                 int j = 0;
@@ -143,7 +143,8 @@ __global__ __launch_bounds__(64 * kRowsPerGroup) void k_neighbors(int n, const d
                     j = cellatoms[x < n0 ? q0 + x : q1 + (x - n0)];
                     near = j == i || min_image_d2(pos, g.box[0], g.box[1], g.box[2], i, j) < r2;
                 }
-                const unsigned long long m = __ballot(near);
+                // the lanes of this atom: they run together
+                const unsigned long long m = __ballot(near) >> (threadIdx.x % 64 / L * L) & (~0ull >> (64 - L));
                 if (MODE == 1 && near) row[cnt + __popcll(m & ((1ull << lane) - 1ull))] = j;
                 cnt += __popcll(m);
             }
@@ -286,10 +287,21 @@ bsm_pattern_s *make_pattern(Context *ctx, int natoms, int b, const double *pos_d
     k_cell_scatter<<<blocks_for(natoms, 256), 256, 0, st>>>(natoms, cell, cellstart,
                                                               cellfill, cellatoms);
     double r2 = cutoff * cutoff;
-    k_neighbors<0><<<blocks_for(natoms, kRowsPerGroup), 64 * kRowsPerGroup, 0, st>>>(natoms, p->pos.as<double>(), g, r2,
-                                                            cell, cellstart,
-                                                            cellatoms, rowcount,
-                                                            nullptr, nullptr);
+    // Lanes of an atom: a wavefront of 64 mostly idles where a run of cells along z holds few
+    // atoms, and many atoms fill the chip with 16 lanes each.  The whole pattern, 16 lanes and 64:
+    // 4096 atoms, 6 A (36 atoms a run) 150 and 152 us, 8 A (98) 213 and 181; 32768 atoms, 4 A (11)
+    // 309 and 409, 10 A (192) 1016 and 1046; 327680 atoms, 4 A (10) 2355 and 3401, a thread per atom 2411.
+    const double run = (double)natoms / (double)ncells * g.noff[2];
+    const bool narrow = run <= 40.0 || natoms >= 16384;
+    auto neighbors = [&](auto MODE, int *count, const int *rowptr, int *cols) {
+        auto go = [&](auto kern, int lanes) {
+            kern<<<blocks_for(natoms, kNeighborThreads / lanes), kNeighborThreads, 0, st>>>(
+                natoms, p->pos.as<double>(), g, r2, cell, cellstart, cellatoms, count, rowptr, cols);
+        };
+        constexpr int mode = decltype(MODE)::value;
+        narrow ? go(k_neighbors<mode, 16>, 16) : go(k_neighbors<mode, 64>, 64);
+    };
+    neighbors(std::integral_constant<int, 0>{}, rowcount, nullptr, nullptr);
     p->rowptr = DevBuf(ctx, sizeof(int) * (natoms + 1));
     k_scan<<<1, 1024, 0, st>>>(natoms, rowcount, p->rowptr.as<int>(), fl + 1);
     int *hostv = reinterpret_cast<int *>(ctx->host_scalars + kHostCounts);
@@ -304,10 +316,7 @@ bsm_pattern_s *make_pattern(Context *ctx, int natoms, int b, const double *pos_d
     p->max_row = hostv[2];
 
     p->cols = DevBuf(ctx, sizeof(int) * (size_t)total);
-    k_neighbors<1><<<blocks_for(natoms, kRowsPerGroup), 64 * kRowsPerGroup, 0, st>>>(natoms, p->pos.as<double>(), g, r2,
-                                                            cell, cellstart,
-                                                            cellatoms, nullptr,
-                                                            p->rowptr.as<int>(), p->cols.as<int>());
+    neighbors(std::integral_constant<int, 1>{}, nullptr, p->rowptr.as<int>(), p->cols.as<int>());
     k_sort_rows<<<natoms, 256, 0, st>>>(natoms, p->rowptr.as<int>(), p->cols.as<int>());
 
     p->rowidx = DevBuf(ctx, sizeof(int) * (size_t)total);
