@@ -58,14 +58,22 @@ __global__ void k_zero_counters(int n, unsigned *c)
 // One kernel per batch precision (F64 = true: FP64 operands; false: FP32) and
 // per tile kind: KB = 9 or 4 runs only the b = 9 or b = 4 tiles (a work list of
 // one orbital count, compiled with the registers and LDS that tile alone
-// needs), KB = 0 either (mixed lists).  BUF: every product's operands fit
-// buffer resources (a_bytes, b_bytes), and the tiles copy through them.
-template <bool F64, bool BUF, int KB>
+// needs), KB = 0 either (mixed lists).  How the tiles copy: through buffer
+// resources (a_bytes, b_bytes), which every product's operands fit, or with 64-bit
+// addresses; b = 4 blocks packed, except with kBatchUnpacked (FP64 operands off 8-byte
+// boundaries).  216 atoms, four products of b = 4 in one launch: 168 us unpacked when the
+// slots came by scalar loads, 225 when they come with the copies, packed 135.
+enum { kBatchBuffers = 0, kBatchPointers = 1, kBatchUnpacked = 2 };
+template <bool F64, int COPIES, int KB>
 __global__ __launch_bounds__(64) void k_product_batch(const BatchDesc *__restrict__ desc, const int2 *__restrict__ items,
                                                       const int64_t *__restrict__ qbeg, int nq,
                                                       unsigned *__restrict__ counters, const double *__restrict__ zblk)
 {
     using T = typename std::conditional<F64, double, float>::type;
+    constexpr int kCopies9 = COPIES == kBatchBuffers ? kBufferCopies : kPointerCopies;
+    constexpr int kCopies4 = COPIES == kBatchBuffers    ? kPackedBuffers
+                             : COPIES == kBatchPointers ? kPackedCopies
+                                                        : kPointerCopies;
     constexpr int kBytes9 = KB == 4 ? 0 : RingEntry<9, kBatchRows, T>::kStep;
     constexpr int kBytes4 = KB == 9 ? 0 : RingEntry<4, kBatchRows, T>::kStep;
     constexpr int kEntryBytes = kBytes9 > kBytes4 ? kBytes9 : kBytes4;
@@ -86,24 +94,24 @@ __global__ __launch_bounds__(64) void k_product_batch(const BatchDesc *__restric
         if constexpr (F64) {
             if (KB == 9 || (KB == 0 && kind == kKindF64Ring9)) {
                 if constexpr (KB != 4)
-                    tile_ring<9, kBatchRows, kBatchRing, double, BUF ? kBufferCopies : kPointerCopies>(it.y, d.hdr, d.ebeg, d.ent, (const double *)d.A,
+                    tile_ring<9, kBatchRows, kBatchRing, double, kCopies9>(it.y, d.hdr, d.ebeg, d.ent, (const double *)d.A,
                                                                  (const double *)d.B, zblk, d.C, d.alpha, d.beta,
                                                                  (lds_char_t *)ring, d.a_bytes, d.b_bytes);
             } else {
                 if constexpr (KB != 9)
-                    tile_ring<4, kBatchRows, kBatchRing, double, BUF ? kBufferCopies : kPointerCopies>(it.y, d.hdr, d.ebeg, d.ent, (const double *)d.A,
+                    tile_ring<4, kBatchRows, kBatchRing, double, kCopies4>(it.y, d.hdr, d.ebeg, d.ent, (const double *)d.A,
                                                                  (const double *)d.B, zblk, d.C, d.alpha, d.beta,
                                                                  (lds_char_t *)ring, d.a_bytes, d.b_bytes);
             }
         } else {
             if (KB == 9 || (KB == 0 && kind == kKindF32Ring9)) {
                 if constexpr (KB != 4)
-                    tile_ring<9, kBatchRows, kBatchRing, float, BUF ? kBufferCopies : kPointerCopies>(it.y, d.hdr, d.ebeg, d.ent, (const float *)d.A,
+                    tile_ring<9, kBatchRows, kBatchRing, float, kCopies9>(it.y, d.hdr, d.ebeg, d.ent, (const float *)d.A,
                                                                 (const float *)d.B, (const float *)zblk, d.C, d.alpha,
                                                                 d.beta, (lds_char_t *)ring, d.a_bytes, d.b_bytes);
             } else {
                 if constexpr (KB != 9)
-                    tile_ring<4, kBatchRows, kBatchRing, float, BUF ? kBufferCopies : kPointerCopies>(it.y, d.hdr, d.ebeg, d.ent, (const float *)d.A,
+                    tile_ring<4, kBatchRows, kBatchRing, float, kCopies4>(it.y, d.hdr, d.ebeg, d.ent, (const float *)d.A,
                                                                 (const float *)d.B, (const float *)zblk, d.C, d.alpha,
                                                                 d.beta, (lds_char_t *)ring, d.a_bytes, d.b_bytes);
             }
@@ -151,6 +159,7 @@ struct bsm_batch_s {
     double flops = 0.0;
     int64_t ntiles = 0;
     bool buf = true;          // every product's operands fit buffer resources
+    bool pack = true;         // every product of b = 4 can take packed copies
     bool tuned = false;
     bsm_batch_config best{};
     bsm_batch_config built{-1, -1, -1, -1};
@@ -278,9 +287,12 @@ void bsm_batch_s::run(const bsm_batch_config &cfg)
         };
 #define BATCH_KERNELS(KB)                                                                          \
         if (prec == BSM_F64)                                                                       \
-            buf ? go(k_product_batch<true, true, KB>) : go(k_product_batch<true, false, KB>);      \
+            !pack ? go(k_product_batch<true, kBatchUnpacked, KB>)                                  \
+            : buf ? go(k_product_batch<true, kBatchBuffers, KB>)                                   \
+                  : go(k_product_batch<true, kBatchPointers, KB>);                                 \
         else                                                                                       \
-            buf ? go(k_product_batch<false, true, KB>) : go(k_product_batch<false, false, KB>)
+            buf ? go(k_product_batch<false, kBatchBuffers, KB>)                                    \
+                : go(k_product_batch<false, kBatchPointers, KB>)
         if (groups[g].kb == 9) BATCH_KERNELS(9);
         else if (groups[g].kb == 4) BATCH_KERNELS(4);
         else BATCH_KERNELS(0);
@@ -360,8 +372,8 @@ int bsm_batch_create(bsm_ctx ctx, int n, const bsm_matrix *A, const bsm_matrix *
         }
         const int64_t esz = precision == BSM_F64 ? 8 : 4;
         const int64_t ab = esz * bt->a_n.back(), bb = esz * bt->b_n.back();
-        if (ab > (int64_t)kBufMaxBytes || bb > (int64_t)kBufMaxBytes || (((uintptr_t)x.A | (uintptr_t)x.B) & 15))
-            bt->buf = false;
+        if (ab > (int64_t)kBufMaxBytes || bb > (int64_t)kBufMaxBytes) bt->buf = false;
+        if (b == 4 && !can_pack(x.A, x.B)) bt->pack = false;
         x.a_bytes = (unsigned)std::min<int64_t>(ab, kBufMaxBytes);
         x.b_bytes = (unsigned)std::min<int64_t>(bb, kBufMaxBytes);
     }

@@ -725,11 +725,6 @@ void launch_wg(hipStream_t st, const Plan *plan, const double *A, const double *
                                                          plan->ent.as<int>(), A, Bm, C, alpha, beta);
 }
 
-// Packed copies read 16 bytes at a time; through buffer resources where both operands fit one.
-inline bool aligned16(const void *a, const void *b, const void *c = nullptr)
-{
-    return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | reinterpret_cast<uintptr_t>(c)) & 15) == 0;
-}
 constexpr int kPackedDepth = 3;   // ring depth of packed copies
 
 template <int B, int G, int D, class T = double, int W = 1, int TR = 0>
@@ -742,21 +737,19 @@ void launch_ring_t(hipStream_t st, const Plan *plan, const T *A, const T *Bm, do
             plan->ntiles, nwg_padded, plan->order.as<int>(), plan->hdr.as<int>(), plan->ebeg.as<int64_t>(),
             plan->ent.as<int>(), A, Bm, zblk, C, alpha, beta, buf ? (unsigned)a_bytes : 0u, buf ? (unsigned)b_bytes : 0u);
     };
-    if constexpr (B == 4 && W == 1 && D == 2) {
-        if (plan->variant == 4 && aligned16(A, Bm)) {
-            if (a_bytes <= (int64_t)kBufMaxBytes && b_bytes <= (int64_t)kBufMaxBytes)
-                go(k_product_ring<B, G, kPackedDepth, T, kPackedBuffers, W, TR>, true);
-            else
-                go(k_product_ring<B, G, kPackedDepth, T, kPackedCopies, W, TR>, false);
+    // variants 4 and 5: buffer copies when both operands fit a buffer resource; else 64-bit addresses
+    const bool buf = (plan->variant == 4 || plan->variant == 5) && a_bytes <= (int64_t)kBufMaxBytes &&
+                     b_bytes <= (int64_t)kBufMaxBytes;
+    if constexpr (B == 4) {
+        if (can_pack(A, Bm)) {
+            if (buf) go(k_product_ring<B, G, kPackedDepth, T, kPackedBuffers, W, TR>, true);
+            else go(k_product_ring<B, G, kPackedDepth, T, kPackedCopies, W, TR>, false);
             return;
         }
     }
     // two-row tiles serve products of few tiles, whose waves run alone on their SIMDs: one entry
     // further ahead covers the copies' latency
     constexpr int DD = G == 2 && D == 2 && W == 1 ? 3 : D;
-    // variants 4 and 5: buffer copies when both operands fit a buffer resource; else 64-bit addresses
-    const bool buf = (plan->variant == 4 || plan->variant == 5) && a_bytes <= (int64_t)kBufMaxBytes &&
-                     b_bytes <= (int64_t)kBufMaxBytes;
     if (buf) go(k_product_ring<B, G, DD, T, kBufferCopies, W, TR>, true);
     else go(k_product_ring<B, G, DD, T, kPointerCopies, W, TR>, false);
 }
@@ -1285,7 +1278,7 @@ void launch_pair_g(hipStream_t st, const Plan *plan, const double *A, const doub
             rs ? (unsigned)a_bytes : 0u, rs ? (unsigned)b_bytes : 0u);
     };
     if constexpr (B == 4) {
-        if (aligned16(A, A2, Bm)) {
+        if (can_pack(A, A2, Bm)) {
             if (buf) go(k_product_ring_pair<B, G, kPackedDepth, kPackedBuffers, TR>, true);
             else go(k_product_ring_pair<B, G, kPackedDepth, kPackedCopies, TR>, false);
             return;

@@ -682,7 +682,8 @@ __device__ inline void dma_block_buf(__amdgpu_buffer_rsrc_t rs, unsigned vo, lds
 // How a ring copies its blocks: 64-bit addresses or buffer resources, 4 bytes per
 // lane and one block per load; or, where a block is a multiple of 16 bytes that
 // divides a load (b = 4), 16 bytes per lane and 64 / lanes-per-block blocks per load.
-// The packed copies need operands at 16-byte boundaries.  An entry of an 8-row tile takes 3
+// A packed load takes 16 bytes at any 8-byte boundary, where FP64 operands lie; the others serve b = 4
+// only off those (can_pack).  An entry of an 8-row tile takes 3
 // such loads instead of 24: b = 4, 8 rows, 1000 atoms, 14 A x 8 A -> 8 A 175 -> 137 us,
 // 216 atoms, 16 A 184 -> 156 us; 4096 atoms, 16 A, 10.7 -> 10.5 ms.  Through buffer
 // resources, a load per operand and one multiply-add per load instead of the 64-bit
@@ -690,6 +691,11 @@ __device__ inline void dma_block_buf(__amdgpu_buffer_rsrc_t rs, unsigned vo, lds
 // three 137 -> 100 us, 156 -> 73 us, 10.5 -> 8.95 ms, and 64 atoms, 16 A, 2 rows, 19.7 -> 16.5 us.
 // (A deeper ring gives these last nothing: 20.3 and 20.6 us at depths 8 and 6.)
 enum { kPointerCopies = 0, kBufferCopies = 1, kPackedCopies = 2, kPackedBuffers = 3 };
+
+inline bool can_pack(const void *a, const void *b, const void *c = nullptr)
+{
+    return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | reinterpret_cast<uintptr_t>(c)) & 7) == 0;
+}
 
 constexpr int kMaxRingDepth = 4;   // entries of a ring, at most
 
