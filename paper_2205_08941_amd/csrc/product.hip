@@ -725,7 +725,10 @@ void launch_wg(hipStream_t st, const Plan *plan, const double *A, const double *
                                                          plan->ent.as<int>(), A, Bm, C, alpha, beta);
 }
 
-constexpr int kPackedDepth = 3;   // ring depth of packed copies
+// Ring depth of packed copies.  Paired tiles hold twice the sums to an entry and hide the copies one
+// entry ahead; a second one cost them: 512 atoms, b = 4, 16 A, 701 us with two, 851 with three; 1000
+// atoms, 14 A, 2429 and 2546 (216 atoms 104 and 107).
+constexpr int kPackedDepth = 3, kPackedPairDepth = 2;
 
 template <int B, int G, int D, class T = double, int W = 1, int TR = 0>
 void launch_ring_t(hipStream_t st, const Plan *plan, const T *A, const T *Bm, double *C, double alpha, double beta,
@@ -1279,8 +1282,8 @@ void launch_pair_g(hipStream_t st, const Plan *plan, const double *A, const doub
     };
     if constexpr (B == 4) {
         if (can_pack(A, A2, Bm)) {
-            if (buf) go(k_product_ring_pair<B, G, kPackedDepth, kPackedBuffers, TR>, true);
-            else go(k_product_ring_pair<B, G, kPackedDepth, kPackedCopies, TR>, false);
+            if (buf) go(k_product_ring_pair<B, G, kPackedPairDepth, kPackedBuffers, TR>, true);
+            else go(k_product_ring_pair<B, G, kPackedPairDepth, kPackedCopies, TR>, false);
             return;
         }
     }
