@@ -1467,12 +1467,18 @@ static std::unique_ptr<Plan> named_plan(const bsm_pattern_s *A, const bsm_patter
 // columns of PB: where the columns' own range cuts many k (its radius well below those of
 // the rows and outputs together).  Where it cuts few or none (a narrow matrix times a wide
 // one, 6 A x 16 A -> 10 A), a tile's k are its rows' k and the row-set order idles fewer
-// lanes (nor does any k fall to the columns of a nearly full PB): there counted cost 0.478 against 0.509 of the clustered tiles, against 0.426 and
-// 0.384 for 16 A x 16 A -> 16 A.
-static bool cluster_pays(const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC)
+// lanes: there counted cost 0.478 against 0.509 of the clustered tiles, against 0.426 and
+// 0.384 for 16 A x 16 A -> 16 A.  Nor does any k fall to the columns of a fuller PB, sooner so with
+// few rows to a tile.  b = 9, row sets and near columns: 4 rows, 0.38 full, 717 and 773 us (512
+// atoms, 10 A); paired, 0.59 full, 21.4 and 21.9 ms, 0.77 full, 37.7 and 38.9 (1000 atoms, 14 and
+// 16 A), 0.21 full, 134.3 and 130.3 (4096 atoms, 16 A); 2 rows, 0.50 full, 135.5 and 140.0 us, 0.21
+// full, 37.4 and 35.5 (216 atoms, 8 and 6 A); 8 rows, 0.59 full, 12.42 and 12.00 ms, 0.77 full,
+// 20.4 and 20.7.
+static bool cluster_pays(const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC, int G)
 {
     const double n = (double)PB->natoms;
-    return PA->cutoff + PC->cutoff - PB->cutoff >= 0.3 * PC->cutoff && (double)PB->nnzb < 0.8 * n * n;
+    return PA->cutoff + PC->cutoff - PB->cutoff >= 0.3 * PC->cutoff &&
+           (double)PB->nnzb < (G <= 4 ? 0.35 : 0.7) * n * n;
 }
 
 // direct, transposed, or (both) the one with the smaller estimated cost: both are
@@ -1485,7 +1491,7 @@ static std::unique_ptr<Plan> new_plan(Context *ctx, const bsm_pattern_s *A, cons
     EntryCount ec;
     TileSet *used = nullptr;
     for (int tr = direct ? 0 : 1; tr <= (transposed ? 1 : 0); ++tr) {
-        const bool near = variant == 4 && ctx->column_order == 1 && (tr ? cluster_pays(B, A, C) : cluster_pays(A, B, C));
+        const bool near = variant == 4 && ctx->column_order == 1 && (tr ? cluster_pays(B, A, C, G) : cluster_pays(A, B, C, G));
         TileSet &ts = tiles[near ? 1 : 0];
         if (ts.G == 0) make_tiles(ctx, C, G, variant == 5 ? 2 : 1, near, ts);
         std::unique_ptr<Plan> p = named_plan(A, B, C, variant);
