@@ -726,7 +726,7 @@ constexpr unsigned kBufMaxBytes = 0xfffff000u;
 // TR = 1 on a transposed plan: C = (B^T A^T)^T and C2 = (B^T A2^T)^T, i.e. two
 // products sharing their left operand).  Each product's elements sum the same
 // terms in the same order as its own launch.
-// Entries ebeg[tile] .. ebeg[tile + 1] are multiplied; `cont`: onto the sums in C.
+// Entries ebeg[tile] .. ebeg[tile + 1] are multiplied.
 template <int B, int G, int D, class T = double, int CP = kPointerCopies, int W = 1, int TR = 0, int DU = 1>
 __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, const int *__restrict__ hdr, const int64_t *__restrict__ ebeg,
                                  const int *__restrict__ ent, const T *__restrict__ vA, const T *__restrict__ vB,
@@ -821,6 +821,18 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
             from[v] = ((pa & first) | (pa2 & rows & ~first) | (pb & ~rows)) + 16 * (lane % LPB);
         }
     }
+    // 64-bit addresses: where the operand of a lane's slot begins, for the rows of A and B's columns
+    // and, with DU = 2, for the rows of A2.  The addresses of a vector's slots are formed at once and
+    // broadcast like the buffer copies' offsets: formed slot by slot on the scalar unit, from slots read
+    // back out of vector registers, they cost the products past 4 GB 4% (8192 atoms, b = 9, 18 A x 8 A ->
+    // 10 A 10.27 -> 9.84 ms, 6 A x 16 A -> 10 A 4.52 -> 4.32, 16 A 151.0 -> 148.2).
+    uint64_t base[CP == kPointerCopies ? NV : 1], base2 = 0;
+    if constexpr (CP == kPointerCopies) {
+        static_assert(GP <= 16, "the rows' slots are in the first vector");
+#pragma unroll
+        for (int v = 0; v < NV; ++v) base[v] = l16 + 16 * v < GP ? (uint64_t)vA : (uint64_t)vB;
+        base2 = (uint64_t)(DU == 2 ? vA2 : vA);
+    }
     auto load_slots = [&](int q, int (&sl)[NR]) {   // straight to registers: the tile's first entries
 #pragma unroll
         for (int v = 0; v < NR; ++v) sl[v] = entw[(int64_t)q * ES + at[v]];
@@ -867,29 +879,36 @@ __device__ __attribute__((always_inline)) inline void tile_ring(int64_t tile, co
             }
         } else {
             int off[NV];
+            uint64_t adr[NV], adr2 = 0;   // absent blocks (slot -1) copy the zero block
             gone = 0u;
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
                 gone |= ((unsigned)__ballot(sl[v] < 0) & 0xffffu) << (16 * (v & 1));
                 off[v] = (int)((unsigned)sl[v] * (unsigned)(BB * ESZ));
+                if constexpr (CP == kPointerCopies) {
+                    const uint64_t at_ = (uint64_t)(unsigned)sl[v] * (unsigned)(BB * ESZ);
+                    adr[v] = sl[v] < 0 ? (uint64_t)zblk : base[v] + at_;
+                    if (DU == 2 && v == 0) adr2 = sl[v] < 0 ? (uint64_t)zblk : base2 + at_;
+                }
             }
+            // a slot's value in every lane
+            const auto bcast = [&](int x, auto S) {
+                return __builtin_amdgcn_mov_dpp(x, 0x150 + decltype(S)::value % 16, 0xf, 0xf, true);
+            };
             slot_blocks([&](auto BLK) {
                 constexpr int blk = decltype(BLK)::value;
                 constexpr int s_at = blk < G ? blk % GP : GP + (blk - G);   // slot of the block in the entry
                 lds_void_t *l = (lds_void_t *)(slot + blk * (BB * ESZ));
                 if constexpr (CP == kBufferCopies) {
                     const unsigned vo =
-                        (unsigned)__builtin_amdgcn_mov_dpp(off[s_at / 16], 0x150 + s_at % 16, 0xf, 0xf, true) +
-                        (unsigned)lane4;
+                        (unsigned)bcast(off[s_at / 16], std::integral_constant<int, s_at>{}) + (unsigned)lane4;
                     dma_block_buf<IPB, DW>(blk < GP ? rsA : (blk < G ? rsA2 : rsB), vo, l, lane,
                                            std::make_integer_sequence<int, IPB>{});
                 } else {
-                    // absent blocks (slot -1) copy the zero block; selected with masks, not a branch
-                    const int s_ = __builtin_amdgcn_readlane(sl[s_at / 16], s_at % 16);
-                    const T *base = blk < GP ? vA : (blk < G ? (DU == 2 ? vA2 : vA) : vB);
-                    const uint64_t real = (uint64_t)base + (uint64_t)((int64_t)s_ * (BB * ESZ));
-                    const uint64_t neg = (uint64_t)(int64_t)(s_ >> 31);
-                    const char *g = reinterpret_cast<const char *>((real & ~neg) | ((uint64_t)zblk & neg)) + lane4;
+                    const uint64_t a = blk >= GP && blk < G ? adr2 : adr[s_at / 16];
+                    const unsigned lo = (unsigned)bcast((int)(unsigned)a, std::integral_constant<int, s_at>{});
+                    const unsigned hi = (unsigned)bcast((int)(unsigned)(a >> 32), std::integral_constant<int, s_at>{});
+                    const char *g = reinterpret_cast<const char *>((uint64_t)hi << 32 | lo) + lane4;
                     dma_block<IPB, DW>(g, l, lane, std::make_integer_sequence<int, IPB>{});
                 }
             }, std::make_integer_sequence<int, NB>{});

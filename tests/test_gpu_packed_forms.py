@@ -1,4 +1,4 @@
-"""How the ring tiles copy b = 4 blocks: packed (16 bytes a lane) from any 8-byte boundary, through
+"""How the ring tiles copy b = 4 blocks (and b = 9 past 4 GB): packed (16 bytes a lane) from any 8-byte boundary, through
 buffer resources or, for variant 3 and for operands past 4 GB, with 64-bit addresses; a block to a
 load only off 8-byte boundaries.  Every form sums the same terms in the same order: results equal
 the scalar-operand kernel's (variant 0) bit for bit.
@@ -99,25 +99,26 @@ def test_copies_of_pairs_and_batches(bsm, offset):
     ctx.close()
 
 
-def test_operands_past_4_GB(bsm):
-    """A full pattern of 5800 atoms: 4.3 GB of 4 x 4 blocks, past a buffer resource."""
+@pytest.mark.parametrize("n,b,side", [(5800, 4, 49.0), (2580, 9, 37.0)])
+def test_operands_past_4_GB(bsm, n, b, side):
+    """A full pattern: 4.3 GB of blocks, past a buffer resource."""
     ctx = bsm.Context(0)
     g = torch.Generator(device=ctx.device)
     g.manual_seed(7)
-    pos = torch.rand((5800, 3), dtype=torch.float64, device=ctx.device, generator=g) * 49.0
-    box = (49.0, 49.0, 49.0)
-    W, N = bsm.Pattern(ctx, pos, box, 100.0, 4), bsm.Pattern(ctx, pos, box, 6.0, 4)
-    assert W.nnzb * 128 > 0xfffff000
-    draw = lambda P: bsm.Matrix(P, torch.randn((P.nnzb, 4, 4), dtype=torch.float64, device=ctx.device, generator=g))
+    pos = torch.rand((n, 3), dtype=torch.float64, device=ctx.device, generator=g) * side
+    box = (side,) * 3
+    W, N = bsm.Pattern(ctx, pos, box, 100.0, b), bsm.Pattern(ctx, pos, box, 6.0, b)
+    assert W.nnzb * b * b * 8 > 0xfffff000
+    draw = lambda P: bsm.Matrix(P, torch.randn((P.nnzb, b, b), dtype=torch.float64, device=ctx.device, generator=g))
     A, A2, B, B2 = draw(W), draw(W), draw(N), draw(N)
     want = {k: reference(bsm, ctx, N, x, y) for k, x, y in (("AB", A, B), ("A2B", A2, B), ("AB2", A, B2))}
     C, D = bsm.Matrix(N), bsm.Matrix(N)
     for tmode in (0, 2):
         ctx.set_transposed_plans(tmode)
-        print("packed past 4 GB", tmode, flush=True)
+        print("past 4 GB", b, tmode, flush=True)
         bsm.multiply_truncate(1.0, A, B, 0.0, C)
         assert torch.equal(C.blocks, want["AB"]), tmode
-    print("packed pairs past 4 GB", flush=True)
+    print("pairs past 4 GB", b, flush=True)
     bsm.multiply_truncate_pair(1.0, A, A2, B, 0.0, C, D)
     assert torch.equal(C.blocks, want["AB"]) and torch.equal(D.blocks, want["A2B"])
     bsm.multiply_truncate_pair_a(1.0, A, B, B2, 0.0, C, D)
