@@ -14,7 +14,12 @@ __global__ void k_axpby(int64_t n, double a, const double *x, double b, double *
 {
     int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (e >= n) return;
-    y[e] = (b == 0.0) ? a * x[e] : fma(b, y[e], a * x[e]);
+    if (b == 0.0) {
+        y[e] = a * x[e];
+        return;
+    }
+    const double xv = x[e], yv = y[e];   // both loads under one wait
+    y[e] = fma(b, yv, a * xv);
 }
 
 // The same for 16-byte aligned arrays of an even count, a pair per thread (each element is the fma
