@@ -122,8 +122,9 @@ typedef struct {
 /* Rows of C per wavefront tile in product plans built from now on: 2, 4 or 8
  * (0 restores the default: for the default kernel with b = 4 and 9 by the number of
  * 8-row tiles C's pattern takes, 2 rows for products of few tiles, 4, then 8 for
- * large ones; else 4 for b >= 4 and 2 below); variant 2 plans always use
- * 16-row workgroup tiles.  Larger values reuse each B block across more rows at
+ * large ones, and 2 or 4 where all three patterns are narrow; for the default kernel
+ * of the other b from 5 to 16 2 for few tiles, else 8 up to b = 8 and 4 above; else 4
+ * for b >= 4 and 2 below); variant 2 plans always use 16-row workgroup tiles.  Larger values reuse each B block across more rows at
  * the cost of idle lanes.  Clears cached plans (destroy batches first). */
 int bsm_ctx_set_rows_per_wave(bsm_ctx ctx, int rows);
 /* FP64 product kernel of plans built from now on: 0 = the uniform A block read

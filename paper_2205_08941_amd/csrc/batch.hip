@@ -31,7 +31,7 @@ namespace bsm {
 // product kinds handled by the persistent kernel
 enum { kKindF64Ring9 = 0, kKindF64Ring4 = 1, kKindF32Ring9 = 2, kKindF32Ring4 = 3 };
 constexpr int kBatchRing = 2;   // LDS ring depth of the tiles
-constexpr int kBatchRows = 8;   // rows per tile (the separate launches' default for b = 4 and 9)
+constexpr int kBatchRows = 8;   // rows per tile (the separate launches' for products of many tiles)
 
 struct BatchDesc {
     int kind;
@@ -331,7 +331,7 @@ int bsm_batch_create(bsm_ctx ctx, int n, const bsm_matrix *A, const bsm_matrix *
         check_same_shape(&A[p], &C[p]);
         const int b = C[p].pattern->b;
         BSM_REQUIRE(b == 4 || b == 9, BSM_EINVAL, "batched products support b = 4 and 9");
-        // LDS-ring tiles of 8 rows (the plans the separate launches use by default)
+        // direct LDS-ring tiles of 8 rows (what a separate launch of many tiles uses, unless transposed)
         Plan *plan = get_plan_kind(c, A[p].pattern, B[p].pattern, C[p].pattern, 4, kBatchRows);
         bt->plans.push_back(plan);
         bt->pa.push_back(A[p].pattern);

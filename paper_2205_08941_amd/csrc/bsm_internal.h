@@ -202,14 +202,15 @@ void launch_product_f64(Context *ctx, const Plan *plan, double alpha, const bsm_
                         const double *A, const bsm_pattern_s *PB, const double *B, double beta,
                         const bsm_pattern_s *PC, double *C);
 // The plan of a paired FP64 launch (C = alpha A B + beta C and C2 = alpha A2 B + beta C2, A and A2
-// on PA): direct one-wave ring tiles of 4 rows, the pair run as 8-row tiles; nullptr when the
-// pair cannot run as one launch (b other than 4 and 9, or another kernel variant chosen).
+// on PA): direct one-wave ring tiles of 4 rows (2 where the product has few tiles), the pair run as
+// tiles of twice the rows; nullptr when the pair cannot run as one launch (b other than 4 and 9,
+// another kernel variant chosen, or too little free memory for a plan beside the class's own).
 Plan *get_pair_plan(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC);
 void launch_product_pair_f64(Context *ctx, const Plan *plan, double alpha, const bsm_pattern_s *PA,
                              const double *A, const double *A2, const bsm_pattern_s *PB, const double *B,
                              double beta, const bsm_pattern_s *PC, double *C, double *C2);
 // The same for two products sharing their left operand (C = alpha A B + beta C and C2 = alpha A B2 +
-// beta C2, B and B2 on PB), on a transposed 4-row plan (C = (B^T A^T)^T); nullptr as above.
+// beta C2, B and B2 on PB), on a transposed plan of as many rows (C = (B^T A^T)^T); nullptr as above.
 Plan *get_pair_plan_a(Context *ctx, const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC);
 void launch_product_pair_a_f64(Context *ctx, const Plan *plan, double alpha, const bsm_pattern_s *PA,
                                const double *A, const bsm_pattern_s *PB, const double *B, const double *B2,

@@ -1443,8 +1443,11 @@ void launch_product_mixed(Context *ctx, const Plan *plan, int prec, double alpha
 }
 
 // Estimated cost of a plan for the ring kernels: rows multiplied plus the
-// fixed work of an entry (copies, waits, B reads), worth about 4.5 rows by
-// measurement.
+// fixed work of an entry (copies, waits, B reads), worth some 4.5 rows as measured
+// on b = 9 entries of 8 rows.  It picks well for the others too: over 136 classes
+// of 216 to 1000 atoms, b = 4, 5, 9 and 13, the plan it takes is 0.1% slower than
+// the better of direct and transposed in the mean, and by more than 1% in two
+// (512 atoms, b = 13, 10 A x 8 A -> 16 A 2.76 ms, 2.54 transposed).
 static double plan_cost(const Plan *p) { return (double)p->rowwork + 4.5 * (double)p->nentries; }
 
 static std::unique_ptr<Plan> named_plan(const bsm_pattern_s *A, const bsm_pattern_s *B, const bsm_pattern_s *C,

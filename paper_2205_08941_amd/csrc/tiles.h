@@ -688,7 +688,7 @@ __device__ inline void dma_block_buf(__amdgpu_buffer_rsrc_t rs, unsigned vo, lds
 // 216 atoms, 16 A 184 -> 156 us; 4096 atoms, 16 A, 10.7 -> 10.5 ms.  Through buffer
 // resources, a load per operand and one multiply-add per load instead of the 64-bit
 // addresses and selects of every lane, which then took most of an entry's time: the same
-// three 137 -> 100 us, 156 -> 73 us, 10.5 -> 8.95 ms, and 64 atoms, 16 A, 2 rows, 19.7 -> 16.5 us.
+// three 137 -> 100 us, 156 -> 73 us, 10.5 -> 8.95 ms, and 64 atoms, 8 A, 2 rows, 19.7 -> 16.5 us.
 // (A deeper ring gives these last nothing: 20.3 and 20.6 us at depths 8 and 6.)
 enum { kPointerCopies = 0, kBufferCopies = 1, kPackedCopies = 2, kPackedBuffers = 3 };
 
