@@ -1476,12 +1476,14 @@ static std::unique_ptr<Plan> named_plan(const bsm_pattern_s *A, const bsm_patter
 // atoms, 10 A); paired, 0.59 full, 21.4 and 21.9 ms, 0.77 full, 37.7 and 38.9 (1000 atoms, 14 and
 // 16 A), 0.21 full, 134.3 and 130.3 (4096 atoms, 16 A); 2 rows, 0.50 full, 135.5 and 140.0 us, 0.21
 // full, 37.4 and 35.5 (216 atoms, 8 and 6 A); 8 rows, 0.59 full, 12.42 and 12.00 ms, 0.77 full,
-// 20.4 and 20.7.
+// 20.4 and 20.7.  b = 4 draws the second line at any rows (4 rows, 0.38 full, 142 and 133 us: 512
+// atoms, 12 A x 10 A -> 10 A; 8 rows, 0.77 full, 2.19 and 2.25 ms: 1000 atoms, 16 A), and the other
+// b's fewer columns a later one (480 atoms, b = 13, 10 A x 6 A -> 16 A, 0.40 full, 957 and 928 us).
 static bool cluster_pays(const bsm_pattern_s *PA, const bsm_pattern_s *PB, const bsm_pattern_s *PC, int G)
 {
     const double n = (double)PB->natoms;
-    return PA->cutoff + PC->cutoff - PB->cutoff >= 0.3 * PC->cutoff &&
-           (double)PB->nnzb < (G <= 4 ? 0.35 : 0.7) * n * n;
+    const double full = PC->b != 4 && PC->b != 9 ? 0.8 : PC->b == 9 && G <= 4 ? 0.35 : 0.7;
+    return PA->cutoff + PC->cutoff - PB->cutoff >= 0.3 * PC->cutoff && (double)PB->nnzb < full * n * n;
 }
 
 // direct, transposed, or (both) the one with the smaller estimated cost: both are

@@ -1,5 +1,5 @@
 """Products on both sides of the lines between tiles of near columns and runs of row sets (a pattern
-0.35 full with up to 4 rows a tile, 0.7 with 8), and a row group of more columns than the near-column
+0.35 full with up to 4 rows a tile of b = 9, else 0.7 or 0.8), and a row group of more columns than the near-column
 order holds in LDS (2048: it keeps the row sets).  Every choice sums the same terms in the same
 order: results equal those of tiles in ascending columns, bit for bit, and of the scalar-operand
 kernel (variant 0).
