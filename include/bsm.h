@@ -132,9 +132,9 @@ int bsm_ctx_set_rows_per_wave(bsm_ctx ctx, int rows);
  * (b = 4 and 9, rows per wave 2 or 4; other shapes use 0); 2 = workgroup tiles
  * of 16 rows (4 wavefronts of 4 rows sharing the tile's B blocks, staged in
  * LDS, A as in 1; b = 4 and 9, else 0); 3 and 4 = the wave tiles of 1 with
- * both operands copied into a per-wave LDS ring by asynchronous LDS-DMA loads,
- * 2 (3, at 2 or 4 rows) or 1 (4, and 3 at 8 rows) entries ahead (b = 4 and 9,
- * rows 2, 4 or 8, else 0); 3 addresses the copies with 64-bit pointers, 4
+ * both operands copied into a per-wave LDS ring by asynchronous LDS-DMA loads
+ * (b = 4 and 9, rows 2, 4 or 8, else 0), with b = 9 2 (3, at 2 or 4 rows; 4, at 2
+ * rows) or 1 entries ahead, with b = 4 several blocks to a load and 2 entries ahead; 3 addresses the copies with 64-bit pointers, 4
  * through buffer resources when A and B each hold at most 0xfffff000 bytes
  * (else as 3); 5 = the rings of 4 with each tile of twice the columns shared by
  * the two waves of a workgroup: one list of k per tile, a half entry per wave

@@ -12,7 +12,9 @@ import subprocess
 import numpy as np
 import pytest
 
-from test_planner_host import ROOT, SHIM
+import oracle as O
+import synth
+from test_planner_host import CASES, ROOT, SHIM
 
 N, REACH = 40000, 3
 
@@ -53,3 +55,34 @@ def test_planner_skips_windows_no_tile_reaches(tmp_path, ring):
     # a group: fewer than 20 barriers for its tiles' columns and their sort; a tile: counted and
     # written, each 1 before its windows and at most 5 in one, one window and sometimes two
     assert int(re.search(r"(\d+)", r.stderr).group(1)) <= 20 * groups + 2 * tiles * (1 + 5 * 1.5)
+
+
+@pytest.mark.parametrize("words,window", [(1, 64), (2, 50), (6, 1), (7, 216)])
+def test_planner_over_many_windows_in_one_chunk(tmp_path, words, window):
+    """Windows of a few atoms, each tile walking all its k as on the GPU (one chunk)."""
+    src = open(os.path.join(ROOT, "paper_2205_08941_amd", "csrc", "product.hip")).read()
+    a = src.index("// ---------------------------------------------------------------- planner")
+    b = src.index("__global__ __launch_bounds__(1024) void k_scan64")
+    part = src[a:b]
+    for name, value in (("kUnionWords", words), ("kEntryWindow", window)):
+        head = part.index(f"constexpr int {name} = ")
+        part = part[:head] + f"constexpr int {name} = {value};" + part[part.index(";", head) + 1:]
+    cpp, exe = tmp_path / "w.cpp", tmp_path / "w"
+    cpp.write_text(SHIM + part + open(os.path.join(ROOT, "tests", "host", "planner_main.cpp")).read())
+    subprocess.run(["g++", "-O2", "-std=c++17", "-o", str(exe), str(cpp)], check=True)
+    s = synth.make_system("d3", (3, 3, 3), 4, synth.SMALL_CUTOFFS, 6, displacement_sigma=0.1)
+    files, pats = {}, {}
+    for r in (4.0, 5.0, 7.0):
+        pats[r] = P = O.create_pattern(s.positions, s.box, r)
+        files[r] = str(tmp_path / f"p{r}.bin")
+        with open(files[r], "wb") as f:
+            np.array([P.natoms, P.nnz], np.int32).tofile(f)
+            P.rowptr.astype(np.int32).tofile(f)
+            P.cols.astype(np.int32).tofile(f)
+    for G, JT, W, order, tr in ((8, 7, 1, 1, 0), (2, 16, 1, 1, 1), (4, 16, 2, 1, 0), (8, 16, 1, 0, 1)):
+        for ra, rb, rc in CASES:
+            r = subprocess.run([str(exe), files[ra], files[rb], files[rc], str(G), str(JT), str(W), str(order),
+                                str(tr), "1"], capture_output=True, text=True, timeout=120)
+            seen, bad = (int(v) for v in r.stdout.split())
+            assert r.returncode == 0 and bad == 0, (G, JT, W, order, tr, ra, rb, rc, r.stdout)
+            assert seen == int(O.count_triples(pats[ra], pats[rb], pats[rc]).sum()), (ra, rb, rc)
